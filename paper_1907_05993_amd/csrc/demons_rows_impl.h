@@ -110,14 +110,14 @@ __device__ inline void taps_h(float2* rows, unsigned rb, const Taps& tp, float& 
 // other R rows and the u rows of the last 2r + 1 steps stay in registers.
 // Row offsets are uniform (scalar offset operands of the buffer accesses).
 // Returns the workgroup's sum of |u_new - u|^2 (all threads) when want_ss.
-template <int NW, int RAD, int TY>
+template <int NW, int RAD, int TY, bool ONE = false>
 __device__ float demons_strip(const float* __restrict__ Rg, const float* __restrict__ Tg,
                               const float* __restrict__ ug, float* __restrict__ ung, int h, int w,
                               int y0, int sx0, int ws, int we, const Taps& tp, bool want_ss)
 {
     const unsigned img_bytes = 4u * (unsigned)h * (unsigned)w;
     const __amdgpu_buffer_rsrc_t R = make_rsrc(Rg, img_bytes);
-    const __amdgpu_buffer_rsrc_t T = make_rsrc(Tg, img_bytes);
+    const GatherBase T = gather_base(Tg, h, w);
     const __amdgpu_buffer_rsrc_t U = make_rsrc(ug, 2u * img_bytes);
     const __amdgpu_buffer_rsrc_t UN = make_rsrc(ung, 2u * img_bytes);
     constexpr int NR = 2 * RAD + 1;  // ring rows
@@ -153,7 +153,7 @@ __device__ float demons_strip(const float* __restrict__ Rg, const float* __restr
     const int yc1 = rowc(y0 - RAD + 1);
     float ux1 = bload_s(U, x4, (unsigned)yc1 * uw4);
     float uy1 = bload_s(U, x4, ch1 + (unsigned)yc1 * uw4);
-    Bilin g = bilinear_issue_g(T, gg, (float)x + ux, (float)yc + uy);
+    Bilin g = bilinear_issue_g<ONE>(T, gg, (float)x + ux, (float)yc + uy);
     put_r(L.r, cur.r, gx, w, r_c);
     __syncthreads();
 
@@ -181,7 +181,7 @@ __device__ float demons_strip(const float* __restrict__ Rg, const float* __restr
             }
             // 2. gathers of row y + 1 (its field was requested one step ago)
             Bilin g1 = g;
-            if (more) g1 = bilinear_issue_g(T, gg, (float)x + ux1, (float)nyc + uy1);
+            if (more) g1 = bilinear_issue_g<ONE>(T, gg, (float)x + ux1, (float)nyc + uy1);
             // rows ym/yc of the next step are this step's yc/yp, or repeat at a clamped border
             const float n_rm = (nym == yc) ? r_c : (nym == yp ? r_p : r_m);
             const float n_rc = (nyc == yp) ? r_p : r_c;
@@ -282,7 +282,8 @@ __device__ __forceinline__ void static_for(F&& f)
 // Loop-invariant context of demons_strip2.
 template <int NW, int RAD>
 struct Strip2Ctx {
-    __amdgpu_buffer_rsrc_t R, T, U, UN;
+    __amdgpu_buffer_rsrc_t R, U, UN;
+    GatherBase T;
     BilGeom gg;
     unsigned uw4, x4, ch1;
     int c, gx, x, h, w, y0;
@@ -496,7 +497,7 @@ __device__ float2 demons_strip2(const float* __restrict__ Rg, const float* __res
     Strip2Ctx<NW, RAD> k;
     const unsigned img_bytes = 4u * (unsigned)h * (unsigned)w;
     k.R = make_rsrc(Rg, img_bytes);
-    k.T = make_rsrc(Tg, img_bytes);
+    k.T = gather_base(Tg, h, w);
     k.U = make_rsrc(ug, 2u * img_bytes);
     k.UN = make_rsrc(ung, 2u * img_bytes);
     k.c = threadIdx.x;
@@ -727,7 +728,7 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3)
 }
 
 // Stand-alone variant: one workgroup per pair walks its strips in order.
-template <int NW, int RAD, int TY>
+template <int NW, int RAD, int TY, bool ONE>
 __global__ void __launch_bounds__(64 * NW)
     k_demons_rows_stage(const float* __restrict__ R, const float* __restrict__ T, int h, int w,
                         const float* __restrict__ u, Taps tp, float* __restrict__ un,
@@ -737,8 +738,8 @@ __global__ void __launch_bounds__(64 * NW)
     const int64_t hw = (int64_t)h * w;
     double acc = 0.0;
     for (int y0 = 0; y0 < h; y0 += TY)
-        acc += (double)demons_strip<NW, RAD, TY>(R + b * hw, T + b * hw, u + 2 * b * hw,
-                                                  un + 2 * b * hw, h, w, y0, 0, 0, w, tp, true);
+        acc += (double)demons_strip<NW, RAD, TY, ONE>(R + b * hw, T + b * hw, u + 2 * b * hw,
+                                                       un + 2 * b * hw, h, w, y0, 0, 0, w, tp, true);
     if (rms && threadIdx.x == 0) rms[b] = sqrt(acc / (double)hw);
 }
 
@@ -840,7 +841,14 @@ template <int CPL, int RAD>
 void launch_rows_stage(const float* R, const float* T, int n, int h, int w, const float* u,
                        const Taps& tp, float* un, double* rms, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_demons_rows_stage<CPL, RAD, kStageTY>), dim3(n), dim3(64 * CPL), 0, s, R, T,
+    if constexpr (CPL == 1) {
+        if (w == 1) {  // no second pixel in a row (the registration's levels have at least 4)
+            hipLaunchKernelGGL((k_demons_rows_stage<CPL, RAD, kStageTY, true>), dim3(n), dim3(64 * CPL), 0, s, R, T,
+                               h, w, u, tp, un, rms);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_demons_rows_stage<CPL, RAD, kStageTY, false>), dim3(n), dim3(64 * CPL), 0, s, R, T,
                        h, w, u, tp, un, rms);
 }
 

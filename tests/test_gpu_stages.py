@@ -84,6 +84,25 @@ def test_stage_demons_iter(E, orc, shape, sigma):
         assert abs(rms[i] - r) <= 1e-5 * max(1.0, r)
 
 
+@pytest.mark.parametrize("n,length", [(2, 40), (1, 1), (3, 5), (1, 200)])
+@pytest.mark.parametrize("axis", [2, 1])
+def test_stage_demons_iter_one_pixel_thin(E, n, length, axis):
+    """An image one pixel thin steps as the same image with that row or column
+    doubled (its gradient along that axis is 0 and every sample the same), so
+    the 8-byte gather of a row's two pixels neither reads past it nor takes
+    another row's pixel.  Small integers and field values in quarters make
+    every sample exact: equal bit for bit."""
+    print("case: thin demons step", n, length, axis, flush=True)
+    shape = (n, length, 1) if axis == 2 else (n, 1, length)
+    R, T = (torch.from_numpy(rng(s).integers(-8, 9, size=shape).astype(np.float32)).cuda() for s in (31, 32))
+    u = torch.from_numpy(rng(33).integers(-9, 10, size=(n, 2) + shape[1:]).astype(np.float32) / 4).cuda()
+    two = lambda v, d: torch.cat([v, v], dim=d).contiguous()
+    for sigma in (0.0, 1.0):
+        thin, _ = E.stage_demons_iter(R, T, u, sigma)
+        wide, _ = E.stage_demons_iter(two(R, axis), two(T, axis), two(u, axis + 1), sigma)
+        assert torch.equal(two(thin, axis + 1), wide)
+
+
 def test_stage_demons_identical_images_exact(E):
     R = ndi.gaussian_filter(rng(5).normal(size=(1, 64, 80)), (0, 2, 2)).astype(np.float32)
     un, rms = E.stage_demons_iter(cuda(R), cuda(R), torch.zeros(1, 2, 64, 80, device="cuda"), 1.0)
