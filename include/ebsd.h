@@ -286,12 +286,11 @@ int ebsd_autotune(ebsd_handle* h, const ebsd_pair* pairs, int32_t n, void* strea
  * Results are identical either way. */
 int ebsd_set_graphs(ebsd_handle* h, int enable);
 
-/* Demons levels of at most 64 x 64 pixels of a size bucket of at most 256
- * pairs run in one launch per level (default, enable = 1): one workgroup per
- * pair keeps the level's reference, test and field in LDS and iterates to the
- * cap or to its own tolerance (multi-resolution demons, section 1).  Larger
- * buckets, and enable = 0, run them like the finer levels, one or two
- * iterations per launch.  The fields are bit-identical either way; the squared
+/* Demons levels of at most 64 x 64 pixels run in one launch per level
+ * (default, enable = 1): one workgroup per pair keeps the level's reference,
+ * test and field on chip and iterates to the cap or to its own tolerance
+ * (multi-resolution demons, section 1).  enable = 0 runs them like the finer
+ * levels, one or two iterations per launch.  The fields are bit-identical either way; the squared
  * update is summed in another order, so a stop on the tolerance can differ
  * only when the RMS update lies within rounding of it. */
 int ebsd_set_resident(ebsd_handle* h, int enable);

@@ -228,10 +228,6 @@ int check_params(const ebsd_params* p)
     return EBSD_OK;
 }
 
-// Largest size bucket whose coarse levels run level-resident (one workgroup per
-// pair; 256 compute units).
-constexpr int kResidentMaxPairs = 256;
-
 // The network's input and output grid: 256 x 256 patterns, 3 pyramid levels.
 constexpr int kWarmRes = 256, kWarmLevels = 3;
 constexpr int kWarmBatch = 256;  // pairs per network launch sequence
@@ -841,10 +837,10 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         for (int l = L - 1; l >= 0; l--) {
             const int ty = strip_ty_for(h, b.lh[l], b.lw[l], nb);
             const int fty = fused_ty_for(h, b.lh[l], b.lw[l], nb);
-            // one workgroup per pair and CU: a win while the batch leaves CUs idle in the
-            // per-iteration launches (measured: single pair 5.1 -> 3.6 ms; 1024 pairs at
-            // 64 x 64 px 4.0 -> 4.5 ms, so large batches keep the row kernels)
-            const bool res = h->resident && nb <= kResidentMaxPairs && demons_resident_ok(b.lh[l], b.lw[l]);
+            // one workgroup per pair and CU, at any batch size: 64 x 64 px take 2.1 us per
+            // iteration and round of 256 pairs (8.5 us for 1024 pairs), the row kernels
+            // 16 us for one pair and 27 us for 1024 (two iterations per launch)
+            const bool res = h->resident && demons_resident_ok(b.lh[l], b.lw[l]);
             if (tm) EBSD_TRY(hipEventRecord(h->ev[2 + 2 * l], s));
             if (res) {
                 EBSD_TRY(launch_demons_resident(d_bk, b, l, h->taps, h->radius, p.tol_px, p.max_iters[l], s));
