@@ -289,10 +289,15 @@ int ebsd_set_graphs(ebsd_handle* h, int enable);
 /* Demons levels of at most 64 x 64 pixels run in one launch per level
  * (default, enable = 1): one workgroup per pair keeps the level's reference,
  * test and field on chip and iterates to the cap or to its own tolerance
- * (multi-resolution demons, section 1).  enable = 0 runs them like the finer
- * levels, one or two iterations per launch.  The fields are bit-identical either way; the squared
- * update is summed in another order, so a stop on the tolerance can differ
- * only when the RMS update lies within rounding of it. */
+ * (multi-resolution demons, section 1).  Finer levels whose size was not
+ * set by ebsd_set_strip_height / ebsd_set_fused_height also run several
+ * iterations per launch by rule: all of them without smoothing and tolerance,
+ * four (three at the widest smoothing) on 2-D tiles where the batch is too
+ * small to fill the device, two on row strips where the size was not tuned.
+ * enable = 0 turns all of that off: every level runs as tuned or set, one
+ * iteration per launch otherwise.  The fields are bit-identical either way;
+ * the squared update is summed in another order, so a stop on the tolerance
+ * can differ only when the RMS update lies within rounding of it. */
 int ebsd_set_resident(ebsd_handle* h, int enable);
 
 /* Per-pair convergence across launches (multi-resolution demons, section 1,
@@ -323,7 +328,9 @@ int ebsd_get_launch_counts(const ebsd_handle* h, int32_t* issued, int32_t* plann
  * recomputing 9 columns on either side, or, at strip height 0, on the 2-D
  * tile kernel when the autotuner found that faster): the tuned or forced
  * value, else 64.  Untuned levels of a batch with fewer than 512
- * strips of 64 rows use 32 or 16 rows (more workgroups for small batches). */
+ * strips of 64 rows use 32 or 16 rows (more workgroups for small batches).
+ * This is the height of the one-iteration launches; a level that runs several
+ * iterations per launch by rule (ebsd_set_resident) does not use it. */
 int ebsd_get_strip_height(const ebsd_handle* h, int32_t level_h, int32_t level_w);
 
 /* Force the strip height (16, 32, 64 or 128; 0 = the 2-D tile kernel, for

@@ -15,6 +15,7 @@
 #include <condition_variable>
 #include <deque>
 #include <map>
+#include <set>
 #include <mutex>
 #include <thread>
 #include <fstream>
@@ -58,6 +59,9 @@ struct ebsd_handle {
     // height were tuned on (absent: forced or read from the cache file); kept
     // apart so that forcing one of them leaves the other's record in place
     std::map<std::pair<int, int>, int> tuned_nb_strip, tuned_nb_fused;
+    // level sizes whose strip height or two-iteration strip height the caller set
+    // (ebsd_set_strip_height, ebsd_set_fused_height): they run as set
+    std::set<std::pair<int, int>> forced;
     std::string tune_cache;  // EBSD_TUNE_CACHE at create time (may be empty)
     // captured launch sequences per bucket configuration (replayed with
     // hipGraphLaunch); the capture itself runs on a private stream
@@ -115,7 +119,69 @@ int fused_ty_for(const ebsd_handle* h, int lh, int lw, int nb = 1 << 20)
     return it == h->fused_ty.end() ? 0 : it->second;
 }
 
-// Tuning cache: one line "gfx950 <level h> <level w> <strip height>" per entry.
+// How a level's iterations are launched.
+struct LevelPlan {
+    enum Kind { Rows, Rows2, Tiles, Points } kind;
+    int rows;        // strip height (0: the 2-D tile kernel of one iteration), or region rows of Tiles
+    int per_launch;  // iterations per launch
+    int units;       // partial sums per pair and iteration
+};
+
+// Strip height of the two-iteration row kernel for a level that was not tuned:
+// the tallest (least recomputed halo) that still gives 2048 wavefronts, two per
+// SIMD, else 16.  Measured per iteration, heights 16 / 32 / 64: 128 pairs of
+// 256 x 256 45.8 / 43.9 / 41.9 us (64 rows: 2048 wavefronts), 48 pairs 17.8 /
+// 24.1 / 37.7 (16 rows: 3072); one iteration per launch takes 51.1 and 25.3.
+// 0 (one iteration per launch) for rows of eight wavefronts, whose state allows
+// two wavefronts per SIMD only: 4 pairs of 1244 x 1024 34.0 us with one
+// iteration per launch, 41.8-47.4 with two; 192 pairs of 400 x 400 48.8
+// against 51.7 ms per call.
+int default_fused_ty(int lh, int lw, int nb)
+{
+    if (rows_cpl(lw) > 4) return 0;
+    for (int ty = 128; ty > 16; ty /= 2)
+        if ((int64_t)nb * demons_units(lh, lw, ty) * rows_cpl(lw) >= 2048) return ty;
+    return 16;
+}
+
+// Region rows (32 or 64) of the tile kernel where it is the faster one for nb
+// levels of lh x lw px, else 0.  Microseconds per iteration, fitted to the
+// measurements at radius 3: n regions of 32 rows take max(2.6, 1.2 + 0.0050 n) (256
+// regions 2.65, 1024 6.4, 4096 20.4), of 64 rows 3.5 up to 256 regions, then
+// 0.7 + 0.0115 n (784 regions 10.8, 6272 71); the row kernels never less than
+// 12.5 (their chain of row steps), else 5.3 us per million pixels (128 pairs
+// of 256 x 256 41.9, 48 pairs 17.8).
+int tile_rows_for(int lh, int lw, int nb, int radius)
+{
+    if (!tile_iters(radius)) return 0;
+    const double n32 = (double)nb * tile_units(lh, lw, radius, 32), n64 = (double)nb * tile_units(lh, lw, radius, 64);
+    const double t32 = std::max(2.6, 1.2 + 0.0050 * n32), t64 = n64 <= 256 ? 3.5 : 0.7 + 0.0115 * n64;
+    const double rows = std::max(12.5, 5.3e-6 * nb * lh * lw);
+    if (std::min(t32, t64) >= rows) return 0;
+    return t32 <= t64 ? 32 : 64;
+}
+
+// A level size the caller set runs as set.  Otherwise, unless ebsd_set_resident
+// turned off running several iterations per launch by rule: without smoothing
+// and tolerance all iterations in one launch; small batches on the tile kernel;
+// else as tuned, and untuned two iterations per launch.
+LevelPlan level_plan(const ebsd_handle* h, int lh, int lw, int nb, int cap)
+{
+    const auto key = std::make_pair(lh, lw);
+    const bool rule = h->resident && !h->forced.count(key);
+    if (rule) {
+        if (h->radius == 0 && h->p.tol_px == 0.0f) return {LevelPlan::Points, 0, std::max(cap, 1), 0};
+        if (const int rows = tile_rows_for(lh, lw, nb, h->radius))
+            return {LevelPlan::Tiles, rows, tile_iters(h->radius), tile_units(lh, lw, h->radius, rows)};
+    }
+    int fty = fused_ty_for(h, lh, lw, nb);
+    const bool tuned = h->strip_ty.count(key) && tuned_applies(h->tuned_nb_strip, lh, lw, nb);
+    if (rule && !fty && !tuned && rows_cpl(lw)) fty = default_fused_ty(lh, lw, nb);
+    if (fty) return {LevelPlan::Rows2, fty, 2, demons_units(lh, lw, fty)};
+    const int ty = strip_ty_for(h, lh, lw, nb);
+    return {LevelPlan::Rows, ty, 1, demons_units(lh, lw, ty)};
+}
+
 // Tuning cache: one line "gfx950 <level h> <level w> <strip height> <fused strip height>"
 // per level size (fused strip height 0: one iteration per launch).
 void load_tune_cache(ebsd_handle* h)
@@ -430,6 +496,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     b.L = L;
     int64_t pe = 0;
     int max_units = 1;
+    LevelPlan plan[EBSD_MAX_LEVELS];
     for (int l = 0; l < L; l++) {
         // level sizes halve rounding up (odd sizes keep their last pixel)
         b.lh[l] = l == 0 ? H : (b.lh[l - 1] + 1) / 2;
@@ -439,6 +506,8 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         pe = (pe + 63) / 64 * 64;  // every level 256 B aligned
         max_units = std::max(max_units, demons_units(b.lh[l], b.lw[l], kMinStripTY2));
         if (b.lw[l] > 512) max_units = std::max(max_units, demons_tiles(b.lh[l], b.lw[l]));
+        plan[l] = level_plan(h, b.lh[l], b.lw[l], nb, p.max_iters[l]);
+        max_units = std::max(max_units, plan[l].units);
     }
     b.pyr_elems = pe;
     b.max_tiles = max_units;
@@ -468,7 +537,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     const size_t o_f0 = w.take(field_bytes);
     const size_t o_f1 = w.take(field_bytes);
     const size_t o_state = w.take(sizeof(PairState) * nb);
-    const size_t o_partial = w.take(sizeof(float) * 4 * (size_t)nb * max_tiles);
+    const size_t o_partial = w.take(sizeof(float) * 8 * (size_t)nb * max_tiles);
     const size_t o_iters = w.take(sizeof(int32_t) * (size_t)nb * L);
     const size_t o_q1 = w.take(sizeof(float) * 2 * (size_t)nb * nr);
     const size_t o_q2 = w.take(sizeof(float) * 2 * (size_t)nb * nr);
@@ -706,27 +775,38 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     // static sequence for a given configuration: captured once into a graph
     // (per chunk of launches when the level is gated) and replayed; the few
     // other launches and the timing events stay on the stream.
-    // fty > 0: two iterations per launch (ceil(cap / 2) launches, plus the
-    // decision-only launch that follows an even cap when a tolerance is set)
-    auto n_launches = [&](int l, int fty) -> int {
-        const int cap = p.max_iters[l];
-        if (fty) return (cap + 1) / 2 + ((p.tol_px > 0.0f && cap > 0 && cap % 2 == 0) ? 1 : 0);
-        return cap;
+    // K iterations per launch: ceil(cap / K) launches, plus a decision-only one with a
+    // tolerance when the last of them runs more than one iteration
+    auto n_launches = [&](int l) -> int {
+        const int cap = p.max_iters[l], K = plan[l].per_launch;
+        return (cap + K - 1) / K + ((p.tol_px > 0.0f && cap > 0 && (cap - 1) % K != 0) ? 1 : 0);
     };
-    auto launch_range = [&](int l, int ty, int fty, int a, int e, hipStream_t st) -> int {
+    auto launch_range = [&](int l, int a, int e, hipStream_t st) -> int {
+        const int rows = plan[l].rows, cap = p.max_iters[l];
         for (int k = a; k < e; k++) {
-            if (fty)
-                EBSD_TRY(launch_demons_iter2(d_bk, b, l, k, h->taps, h->radius, p.tol_px, p.max_iters[l], fty, st));
-            else
-                EBSD_TRY(launch_demons_iter(d_bk, b, l, k, h->taps, h->radius, p.tol_px, ty, st));
+            switch (plan[l].kind) {
+            case LevelPlan::Rows:
+                EBSD_TRY(launch_demons_iter(d_bk, b, l, k, h->taps, h->radius, p.tol_px, rows, st));
+                break;
+            case LevelPlan::Rows2:
+                EBSD_TRY(launch_demons_iter2(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));
+                break;
+            case LevelPlan::Tiles:
+                EBSD_TRY(launch_demons_tiles(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));
+                break;
+            case LevelPlan::Points:
+                EBSD_TRY(launch_demons_points(d_bk, b, l, h->taps, cap, st));
+                break;
+            }
         }
         return EBSD_OK;
     };
-    auto run_range = [&](int l, int ty, int fty, int a, int e) -> int {
+    auto run_range = [&](int l, int a, int e) -> int {
         if (h->graphs && e > a) {
             std::ostringstream key;
             key << H << ' ' << W << ' ' << nb << ' ' << nref << ' ' << l << ' ' << p.max_iters[l]
-                << ' ' << p.tol_px << ' ' << h->radius << ' ' << ty << ' ' << fty << ' ' << a << ' ' << e
+                << ' ' << p.tol_px << ' ' << h->radius << ' ' << (int)plan[l].kind << ' ' << plan[l].rows << ' ' << a
+                << ' ' << e
                 << ' ' << (void*)base;
             auto it = h->graph_cache.find(key.str());
             hipGraphExec_t exec = nullptr;
@@ -740,7 +820,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
                 std::shared_lock<std::shared_mutex> cap_lk(capture_mutex());
                 if (h->cap_stream &&
                     hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
-                    const int e2 = launch_range(l, ty, fty, a, e, h->cap_stream);
+                    const int e2 = launch_range(l, a, e, h->cap_stream);
                     const hipError_t ec = hipStreamEndCapture(h->cap_stream, &graph);
                     if (e2 == EBSD_OK && ec == hipSuccess && graph &&
                         hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess)
@@ -755,7 +835,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
                 return EBSD_OK;
             }
         }
-        return launch_range(l, ty, fty, a, e, s);
+        return launch_range(l, a, e, s);
     };
     // gating needs a stream the host may wait on: not while the caller captures it
     bool gate = p.tol_px > 0.0f && h->gate_chunk > 0 && mode == Mode::Full;
@@ -777,18 +857,18 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         for (auto& ev : h->gate_ev)
             EBSD_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
     }
-    auto run_level = [&](int l, int ty, int fty) -> int {
-        const int nl = n_launches(l, fty);
+    auto run_level = [&](int l) -> int {
+        const int nl = n_launches(l);
         h->launches_planned[l] += nl;
         const int chunk = gate ? h->gate_chunk : 0;
         if (chunk <= 0 || nl <= chunk) {
             h->launches_issued[l] += nl;
-            return run_range(l, ty, fty, 0, nl);
+            return run_range(l, 0, nl);
         }
         int done = 0;
         for (int c = 0, a = 0; a < nl; c++, a += chunk) {
             const int e = std::min(nl, a + chunk);
-            const int r = run_range(l, ty, fty, a, e);
+            const int r = run_range(l, a, e);
             if (r) return r;
             done = e;
             if (e == nl) break;
@@ -835,8 +915,6 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     } else if (mode == Mode::Full) {
         EBSD_TRY(launch_demons_init(d_bk, b, s));
         for (int l = L - 1; l >= 0; l--) {
-            const int ty = strip_ty_for(h, b.lh[l], b.lw[l], nb);
-            const int fty = fused_ty_for(h, b.lh[l], b.lw[l], nb);
             // one workgroup per pair and CU, at any batch size: 64 x 64 px take 2.1 us per
             // iteration and round of 256 pairs (8.5 us for 1024 pairs), the row kernels
             // 16 us for one pair and 27 us for 1024 (two iterations per launch)
@@ -845,12 +923,12 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
             if (res) {
                 EBSD_TRY(launch_demons_resident(d_bk, b, l, h->taps, h->radius, p.tol_px, p.max_iters[l], s));
             } else {
-                const int e = run_level(l, ty, fty);
+                const int e = run_level(l);
                 if (e) return e;
             }
             if (tm) EBSD_TRY(hipEventRecord(h->ev[3 + 2 * l], s));
             if (!res)
-                EBSD_TRY(launch_level_end(d_bk, b, l, p.max_iters[l], p.tol_px, fty ? fty : ty, fty != 0, s));
+                EBSD_TRY(launch_level_end(d_bk, b, l, p.max_iters[l], p.tol_px, plan[l].units, plan[l].per_launch, s));
             if (l > 0) EBSD_TRY(launch_prolong_level(d_bk, b, l, s));
         }
         EBSD_TRY(launch_sample_q1(d_bk, b, s));
@@ -1103,6 +1181,7 @@ int ebsd_set_strip_height(ebsd_handle* h, int32_t level_h, int32_t level_w, int3
     if (!h || level_h <= 0 || level_w <= 0 || !strip_ty_ok(level_w, ty)) return EBSD_EINVAL;
     try {
         h->strip_ty[std::make_pair((int)level_h, (int)level_w)] = ty;
+        h->forced.insert(std::make_pair((int)level_h, (int)level_w));
     } catch (const std::bad_alloc&) {
         return EBSD_ENOMEM;
     }
@@ -1124,6 +1203,7 @@ int ebsd_set_fused_height(ebsd_handle* h, int32_t level_h, int32_t level_w, int3
     try {
         if (rows) h->fused_ty[key] = rows;
         else h->fused_ty.erase(key);
+        h->forced.insert(key);
     } catch (const std::bad_alloc&) {
         return EBSD_ENOMEM;
     }

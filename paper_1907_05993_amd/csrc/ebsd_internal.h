@@ -109,8 +109,8 @@ struct Bucket {
     PatStat* ref_stat;          // [nref]
     float* field[2];            // [nb][2][H][W] each (level l uses the leading 2 h w)
     PairState* state;           // [nb]
-    float* partial;             // [4][nb][max tiles] per-tile sums of squared updates (slot k & 1 for one
-                                // iteration per launch, k & 3 for two)
+    float* partial;             // [8][nb][max tiles] per-tile sums of squared updates (slot k & 1 for one
+                                // iteration per launch, k & 3 for two, k & 7 for the tile kernel's)
     int32_t max_tiles;          // tiles of the finest level
     int32_t* iters;             // [nb][L]
     int32_t n_roi, roi_N;
@@ -170,12 +170,27 @@ hipError_t launch_demons_iter2(const Bucket* d_bk, const Bucket& hb, int level, 
 bool demons_resident_ok(int h, int w);
 hipError_t launch_demons_resident(const Bucket* d_bk, const Bucket& hb, int level, const float* taps, int radius,
                                   float tol, int cap, hipStream_t s);
+// Launch L of level l runs iterations L K .. L K + K - 1 (K = tile_iters(radius),
+// 0: no tile kernel for this radius) on 2-D tiles cut from regions of 64
+// columns x `rows` (32 or 64) rows; partial sums in slot iteration & 7, one per
+// tile (tile_units).  ceil(cap / K) launches, plus one that only takes the
+// decisions when tol > 0 and the last launch runs more than one iteration.
+int tile_iters(int radius);
+int tile_units(int h, int w, int radius, int rows);
+hipError_t launch_demons_tiles(const Bucket* d_bk, const Bucket& hb, int level, int L, const float* taps, int radius,
+                               float tol, int cap, int rows, hipStream_t s);
+// All `cap` iterations of level l in one launch without smoothing (radius 0,
+// taps[0] the single tap), fixed iteration count.
+hipError_t launch_demons_points(const Bucket* d_bk, const Bucket& hb, int level, const float* taps, int cap,
+                                hipStream_t s);
 // *out = number of pairs whose demons state has not recorded a stop (out may
 // be pinned host memory mapped into the device's address space).
 hipError_t launch_count_active(const Bucket* d_bk, int32_t* out, hipStream_t s);
-// Close level l: iteration counts, convergence of the last iteration, final buffer.
+// Close level l: iteration counts, convergence of the last iteration, final
+// buffer.  per_launch: iterations per launch the level ran with; units: partial
+// sums per pair and iteration.
 hipError_t launch_level_end(const Bucket* d_bk, const Bucket& hb, int level, int cap, float tol,
-                            int ty, bool fused, hipStream_t s);
+                            int units, int per_launch, hipStream_t s);
 // Prolong the field of every pair from level l to level l-1 and re-arm the pairs.
 hipError_t launch_prolong_level(const Bucket* d_bk, const Bucket& hb, int level, hipStream_t s);
 // Sample the finest field at the ROI centres -> q1.

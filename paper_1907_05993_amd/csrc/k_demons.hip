@@ -178,9 +178,9 @@ __global__ void __launch_bounds__(NT)
 
 // End of level l, one thread per pair: iteration count, convergence on the
 // last iteration (the in-loop check sees iteration k - 1 only), final buffer.
-// fused != 0: the level ran two iterations per launch (partial slot i & 3,
-// final field after n iterations in buffer (base + ceil(n / 2)) & 1).
-__global__ void k_level_end(const Bucket* __restrict__ bk, int level, int cap, float tol, int ntiles, int fused)
+// per_launch iterations per launch: partial slot i & 1 (one), i & 3 (two) or
+// i & 7, final field after n iterations in buffer (base + ceil(n / per_launch)) & 1.
+__global__ void k_level_end(const Bucket* __restrict__ bk, int level, int cap, float tol, int ntiles, int per_launch)
 {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= bk->nb) return;
@@ -188,7 +188,7 @@ __global__ void k_level_end(const Bucket* __restrict__ bk, int level, int cap, f
     int n = st.stop >= 0 ? st.stop : cap;
     if (st.stop < 0 && tol > 0.0f && cap > 0) {
         const int64_t npart = (int64_t)bk->nb * bk->max_tiles;
-        const int slot = fused ? ((cap - 1) & 3) : ((cap - 1) & 1);
+        const int slot = (cap - 1) & (per_launch == 1 ? 1 : per_launch == 2 ? 3 : 7);
         const float* last = bk->partial + slot * npart + (int64_t)b * bk->max_tiles;
         // same fixed order as pair_sum: 64 strided lanes, then the xor tree
         double lane[64];
@@ -208,7 +208,7 @@ __global__ void k_level_end(const Bucket* __restrict__ bk, int level, int cap, f
         if (delta < (double)tol) st.convmask |= 1u << level;
     }
     bk->iters[(int64_t)b * bk->L + level] = n;
-    st.cur = fused ? (st.base + (n + 1) / 2) & 1 : (st.base + n) & 1;
+    st.cur = (st.base + (n + per_launch - 1) / per_launch) & 1;
     st.stop = -1;
     bk->state[b] = st;
 }
@@ -300,11 +300,10 @@ hipError_t launch_count_active(const Bucket* d_bk, int32_t* out, hipStream_t s)
 }
 
 hipError_t launch_level_end(const Bucket* d_bk, const Bucket& hb, int level, int cap, float tol,
-                            int ty, bool fused, hipStream_t s)
+                            int units, int per_launch, hipStream_t s)
 {
-    const int ntiles = demons_units(hb.lh[level], hb.lw[level], ty);
-    hipLaunchKernelGGL(k_level_end, dim3((hb.nb + 63) / 64), dim3(64), 0, s, d_bk, level, cap, tol,
-                       ntiles, fused ? 1 : 0);
+    hipLaunchKernelGGL(k_level_end, dim3((hb.nb + 63) / 64), dim3(64), 0, s, d_bk, level, cap, tol, units,
+                       per_launch);
     return hipGetLastError();
 }
 

@@ -1,0 +1,246 @@
+// Several demons iterations per launch on 2-D tiles (multi-resolution demons,
+// section 1, Eq. (1)), for levels whose pixels of the whole batch do not fill
+// the device: there a launch of the row-marching kernels lasts as long as its
+// chain of row steps (about 0.7 us each, 22 and more per launch), whatever the
+// batch.  A workgroup takes an output tile with a halo of K r pixels and runs K
+// iterations on it (demons_region.h: state in registers, one barrier per
+// iteration), the valid part shrinking by r on every side per iteration.
+// Bound: the chain of K iterations (about 1 us each at 32 region rows) and a
+// launch's fixed cost (about 5 us); the recomputed halo is idle capacity.
+//
+// Stops on a tolerance: launch L runs iterations L K .. L K + K - 1 and
+// leaves their partial sums (slot: iteration mod 8); the next launch takes the
+// decisions in order, and if the pair should have stopped in between, runs
+// the iterations up to there again from the previous launch's input, which is
+// still in the other buffer.  Counts, status and fields are those of one
+// iteration per launch.
+#include "demons_region.h"
+#include "ebsd_internal.h"
+
+namespace ebsd {
+
+namespace {
+
+constexpr int kTileRPT = 4;  // rows per wavefront
+
+template <int RAD, int K, int NWV>
+__global__ void __launch_bounds__(64 * NWV)
+    k_demons_tiles(const Bucket* __restrict__ bk, int level, int L, Taps tp, float tol, int ntx, int ntiles, int cap)
+{
+    constexpr int RPT = kTileRPT, RH = NWV * RPT, HALO = RAD * K;
+    constexpr int TX = 64 - 2 * HALO, TY = RH - 2 * HALO;
+    static_assert(TX > 0 && TY > 0, "halo covers the region");
+    extern __shared__ float2 lds[];  // [2][RH][64] filtered rows
+    __shared__ float red[K][NWV];
+    __shared__ double sh_sum;
+    const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int b = lb / ntiles, tile = lb - b * ntiles;
+    const PairState st = bk->state[b];
+    const int k0 = L * K;
+    // a stop inside the previous launch's iterations can only have been written by tile 0
+    // of this launch: the other tiles still owe the recompute below
+    if (st.stop >= 0 && !(st.stop > k0 - K && st.stop < k0)) return;  // uniform
+    const int h = bk->lh[level], w = bk->lw[level];
+    const int64_t npart = (int64_t)bk->nb * bk->max_tiles;
+    const int64_t pofs = (int64_t)b * bk->max_tiles;
+    int niter = min(K, cap - k0), again = 0;
+    if (tol > 0.0f && L > 0) {
+        const double hw = (double)h * (double)w, sc = (double)(1 << level);
+        const int last = min(k0, cap);  // iterations run so far
+        for (int i = k0 - K; i < last; i++) {
+            const double ss = pair_sum(bk->partial + (i & 7) * npart + pofs, ntiles, &sh_sum);
+            if (sqrt(ss / hw) * sc < (double)tol) {
+                if (tile == 0 && threadIdx.x == 0) {
+                    bk->state[b].stop = i + 1;
+                    bk->state[b].convmask = st.convmask | (1u << level);
+                }
+                if (i + 1 == last) return;  // the field is in place
+                again = i + 1 - (k0 - K);
+                break;
+            }
+        }
+    }
+    if (again) niter = again;
+    else if (niter <= 0) return;
+    const int64_t slot = (int64_t)b * 2 * bk->H * bk->W;
+    const float* R = bk->ref_pyr + (int64_t)bk->ref_slot[b] * bk->pyr_elems + bk->lvl_off[level];
+    const float* Tg = bk->test_pyr + (int64_t)b * bk->pyr_elems + bk->lvl_off[level];
+    // recompute: from the previous launch's input into the buffer its output is in
+    const float* u = bk->field[(st.base + L + (again ? 1 : 0)) & 1] + slot;
+    float* un = bk->field[(st.base + L + (again ? 0 : 1)) & 1] + slot;
+
+    const int ty = tile / ntx, tx = tile - ty * ntx;
+    const int lane = threadIdx.x & 63, wave = uniform_int(threadIdx.x >> 6);
+    const int gx0 = tx * TX - HALO, gy0 = ty * TY - HALO;
+    const int x = gx0 + lane, r0 = wave * RPT, y0 = gy0 + r0;
+    const bool fix = gx0 < 0 || gx0 + 64 > w;  // uniform: some lanes lie outside the image
+    const int fix_lane = clampi(x, 0, w - 1) - gx0;
+    RegionRows<RPT> s;
+    region_load(s, R, u, h, w, x, y0);
+    const GatherBase T = gather_base(Tg, h, w);
+    const BilGeom g = bil_geom(h, w);
+    const float xf = (float)clampi(x, 0, w - 1), yf = (float)y0;
+    int off[RPT + 2 * RAD];
+#pragma unroll
+    for (int j = 0; j < RPT + 2 * RAD; j++)
+        off[j] = 64 * clampi(clampi(y0 - RAD + j, 0, h - 1) - gy0, 0, RH - 1) + lane;
+    const bool own_x = lane >= HALO && lane < 64 - HALO && x < w;
+    unsigned own = 0;
+#pragma unroll
+    for (int k = 0; k < RPT; k++)
+        if (own_x && r0 + k >= HALO && r0 + k < RH - HALO && y0 + k < h) own |= 1u << k;
+
+    for (int i = 0; i < niter; i++) {
+        float2* hb = lds + (i & 1) * RH * 64;
+        // the rows still needed: inside the image, and in the region shrunk by r per
+        // finished iteration (for v), by r more for the field
+        const auto needed = [&](int m) { return r0 < min(RH - m, h - gy0) && r0 + RPT > max(m, -gy0); };
+        if (needed(RAD * i))
+            region_rows<RAD, RPT>(s, T, g, tp, xf, yf, fix, fix_lane, hb + 64 * r0 + lane);
+        __syncthreads();
+        float ss = 0.0f;
+        if (needed(RAD * (i + 1))) ss = region_cols<RAD, RPT>(s, hb, off, tp, own);
+        if (tol > 0.0f && !again) {
+            ss = wave_sum(ss);
+            if (lane == 0) red[i][wave] = ss;
+        }
+    }
+    if (own) {
+        EBSD_GLOBAL float* out = gptr(un);
+        const int64_t hw = (int64_t)h * w;
+#pragma unroll
+        for (int k = 0; k < RPT; k++)
+            if (own & (1u << k)) {
+                const int o = (y0 + k) * w + x;
+                out[o] = s.ux[k];
+                out[hw + o] = s.uy[k];
+            }
+    }
+    if (tol > 0.0f && !again) {
+        __syncthreads();
+        if ((int)threadIdx.x < niter) {
+            float tot = 0.0f;
+#pragma unroll
+            for (int i = 0; i < NWV; i++) tot += red[threadIdx.x][i];
+            bk->partial[((k0 + threadIdx.x) & 7) * npart + pofs + tile] = tot;
+        }
+    }
+}
+
+// Without smoothing (r = 0) pixels do not interact: one launch runs all `cap`
+// iterations of a level, each thread its own pixel, field in registers (the
+// field is read and written once per level instead of once per iteration).
+// Fixed iteration count only.  Bound: the iteration's vector ALU work and its
+// two 8-byte gathers (L1 / L2); two pixels per thread overlap their gathers.
+constexpr int kPointThreads = 256, kPointPx = 2;
+
+__global__ void __launch_bounds__(kPointThreads)
+    k_demons_points(const Bucket* __restrict__ bk, int level, float w0, int nblocks, int cap)
+{
+    const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int b = lb / nblocks, blk = lb - b * nblocks;
+    const int h = bk->lh[level], w = bk->lw[level], n = h * w;
+    const int base = bk->state[b].base;
+    const int64_t slot = (int64_t)b * 2 * bk->H * bk->W;
+    const EBSD_GLOBAL float* __restrict__ R =
+        gptr(bk->ref_pyr + (int64_t)bk->ref_slot[b] * bk->pyr_elems + bk->lvl_off[level]);
+    const GatherBase T = gather_base(bk->test_pyr + (int64_t)b * bk->pyr_elems + bk->lvl_off[level], h, w);
+    const EBSD_GLOBAL float* __restrict__ u = gptr(bk->field[base & 1] + slot);
+    EBSD_GLOBAL float* __restrict__ un = gptr(bk->field[(base + 1) & 1] + slot);
+    const BilGeom g = bil_geom(h, w);
+    float ux[kPointPx], uy[kPointPx], r[kPointPx], gx[kPointPx], gy[kPointPx], px[kPointPx], py[kPointPx];
+    int at[kPointPx];
+#pragma unroll
+    for (int k = 0; k < kPointPx; k++) {
+        at[k] = (blk * kPointPx + k) * kPointThreads + (int)threadIdx.x;
+        const int o = min(at[k], n - 1);
+        const int y = o / w, x = o - y * w;
+        const int xm = max(x - 1, 0), xp = min(x + 1, w - 1);
+        const int ym = max(y - 1, 0), yp = min(y + 1, h - 1);
+        ux[k] = u[o];
+        uy[k] = u[n + o];
+        r[k] = R[o];
+        gx[k] = (R[y * w + xp] - R[y * w + xm]) * ((xp - xm == 2) ? 0.5f : 1.0f);
+        gy[k] = (R[yp * w + x] - R[ym * w + x]) * ((yp - ym == 2) ? 0.5f : 1.0f);
+        px[k] = (float)x;
+        py[k] = (float)y;
+    }
+    for (int i = 0; i < cap; i++) {
+        Bilin t[kPointPx];
+#pragma unroll
+        for (int k = 0; k < kPointPx; k++) t[k] = bilinear_issue_g(T, g, px[k] + ux[k], py[k] + uy[k]);
+#pragma unroll
+        for (int k = 0; k < kPointPx; k++) {
+            float vx, vy;
+            demons_force(bilinear_blend_g(t[k]), r[k], gx[k], gy[k], ux[k], uy[k], vx, vy);
+            // the one-tap smoothing, both passes (w0 = 1)
+            ux[k] = fmaf(w0, fmaf(w0, vx, 0.0f), 0.0f);
+            uy[k] = fmaf(w0, fmaf(w0, vy, 0.0f), 0.0f);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kPointPx; k++)
+        if (at[k] < n) {
+            un[at[k]] = ux[k];
+            un[n + at[k]] = uy[k];
+        }
+}
+
+template <int RAD, int K, int NWV>
+hipError_t launch_tiles(const Bucket* d_bk, const Bucket& hb, int level, int L, const Taps& tp, float tol, int cap,
+                        hipStream_t s)
+{
+    constexpr int RH = NWV * kTileRPT;
+    constexpr size_t lds = sizeof(float2) * 2 * RH * 64;
+    static std::atomic<uint64_t> attr_done{0};
+    const hipError_t e = ensure_dynamic_lds((const void*)k_demons_tiles<RAD, K, NWV>, (int)lds, attr_done);
+    if (e != hipSuccess) return e;
+    const int tx = 64 - 2 * RAD * K, ty = RH - 2 * RAD * K;
+    const int ntx = (hb.lw[level] + tx - 1) / tx, ntiles = ntx * ((hb.lh[level] + ty - 1) / ty);
+    hipLaunchKernelGGL((k_demons_tiles<RAD, K, NWV>), dim3((unsigned)((int64_t)hb.nb * ntiles)), dim3(64 * NWV), lds,
+                       s, d_bk, level, L, tp, tol, ntx, ntiles, cap);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+int tile_iters(int radius) { return radius >= 1 && radius <= 3 ? 4 : radius == 4 ? 3 : 0; }
+
+int tile_units(int h, int w, int radius, int rows)
+{
+    const int halo = 2 * radius * tile_iters(radius);
+    const int tx = 64 - halo, ty = rows - halo;
+    return ((w + tx - 1) / tx) * ((h + ty - 1) / ty);
+}
+
+hipError_t launch_demons_tiles(const Bucket* d_bk, const Bucket& hb, int level, int L, const float* taps, int radius,
+                               float tol, int cap, int rows, hipStream_t s)
+{
+    Taps tp;
+    for (int i = 0; i < 2 * kMaxRadius + 1; i++) tp.w[i] = i <= 2 * radius ? taps[i] : 0.0f;
+    if (hb.nb <= 0 || hb.lh[level] < 2 || hb.lw[level] < 2 || (rows != 32 && rows != 64)) return hipErrorInvalidValue;
+    switch (radius + (rows == 64 ? 8 : 0)) {
+    case 1: return launch_tiles<1, 4, 8>(d_bk, hb, level, L, tp, tol, cap, s);
+    case 2: return launch_tiles<2, 4, 8>(d_bk, hb, level, L, tp, tol, cap, s);
+    case 3: return launch_tiles<3, 4, 8>(d_bk, hb, level, L, tp, tol, cap, s);
+    case 4: return launch_tiles<4, 3, 8>(d_bk, hb, level, L, tp, tol, cap, s);
+    case 9: return launch_tiles<1, 4, 16>(d_bk, hb, level, L, tp, tol, cap, s);
+    case 10: return launch_tiles<2, 4, 16>(d_bk, hb, level, L, tp, tol, cap, s);
+    case 11: return launch_tiles<3, 4, 16>(d_bk, hb, level, L, tp, tol, cap, s);
+    case 12: return launch_tiles<4, 3, 16>(d_bk, hb, level, L, tp, tol, cap, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_demons_points(const Bucket* d_bk, const Bucket& hb, int level, const float* taps, int cap,
+                                hipStream_t s)
+{
+    if (hb.nb <= 0 || hb.lh[level] < 2 || hb.lw[level] < 2) return hipErrorInvalidValue;
+    const int n = hb.lh[level] * hb.lw[level];
+    const int nblocks = (n + kPointThreads * kPointPx - 1) / (kPointThreads * kPointPx);
+    hipLaunchKernelGGL(k_demons_points, dim3((unsigned)((int64_t)hb.nb * nblocks)), dim3(kPointThreads), 0, s, d_bk,
+                       level, taps[0], nblocks, cap);
+    return hipGetLastError();
+}
+
+}  // namespace ebsd
