@@ -527,7 +527,7 @@ int ebsd_stage_prolong(const float* u, int32_t n, int32_t h, int32_t w, float* o
  * lowest row-major index), 2-D quadratic sub-pixel fit.  q: [n][2] (x, y)
  * shift of B relative to A; ph: [n] normalised peak height (may be NULL).
  * N = 256 (the paper's ROI size) allocates a device temporary of 768 KiB per
- * ROI in flight (at most 512 ROIs: 384 MiB) and waits on the stream before
+ * ROI in flight (at most 256 ROIs: 192 MiB) and waits on the stream before
  * it returns; smaller N run in LDS and never wait. */
 int ebsd_stage_xcf(const float* A, const float* B, int32_t n, int32_t N, int32_t window, float* q,
                    float* ph, void* stream);

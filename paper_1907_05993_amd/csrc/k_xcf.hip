@@ -78,6 +78,9 @@ __device__ inline int mirror1(int i, int n)
     return i > n - 1 ? 2 * n - 2 - i : i;
 }
 
+#define EBSD_XG __attribute__((address_space(1)))
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
 // Cubic B-spline interpolant with coefficients c (h x w, whole-sample mirror
 // extension) at double-precision coordinates clamped to the image: weights
 // beta3(t + 1), beta3(t), beta3(t - 1), beta3(t - 2) on the four nodes
@@ -103,10 +106,29 @@ __device__ inline float bspline_d(const float* __restrict__ c, int h, int w, dou
         wy[2] = (-3.0f * t3 + 3.0f * t2 + 3.0f * t + 1.0f) * (1.0f / 6.0f);
         wy[3] = t3 * (1.0f / 6.0f);
     }
+    float acc = 0.0f;
+    // all lanes inside (no mirrored node): a row's four nodes are one 16-byte load
+    // at 4-byte alignment (16 single loads before: the gather was half of the
+    // second pass's time at ROIs of 64)
+    const bool inside = ix >= 1 && ix + 2 < w && iy >= 1 && iy + 2 < h;
+    if (__all(inside)) {
+        const EBSD_XG float* base = (const EBSD_XG float*)c;
+        const unsigned o = (unsigned)(iy - 1) * (unsigned)w + (unsigned)(ix - 1);
+        f32x4_a4 n[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) n[j] = *(const EBSD_XG f32x4_a4*)(base + (o + (unsigned)j * (unsigned)w));
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            float r = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 4; k++) r += wx[k] * n[j][k];
+            acc += wy[j] * r;
+        }
+        return acc;
+    }
     int cx[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) cx[k] = mirror1(ix - 1 + k, w);
-    float acc = 0.0f;
 #pragma unroll
     for (int j = 0; j < 4; j++) {
         const float* row = c + (int64_t)mirror1(iy - 1 + j, h) * w;
@@ -525,14 +547,15 @@ __device__ void xcf_core(XcfShared<N>& S, Loader load, int window, float* q, flo
 }
 
 // ---- ROIs of 256 x 256 (the paper's ROI size) ----------------------------------
-// The 256 x 256 complex tile (512 KiB) does not fit in LDS, so one workgroup
-// per ROI keeps it in a slot of global scratch (L2 / MALL resident while the
-// workgroup works on it) and moves 32 lines at a time through an LDS tile:
-//   gather   z = a + i b of the ROI (remapped reference, test) into the slot,
-//            natural order, and the two means;
-//   rows     per 32 rows: mean removed, Hann window, energies, forward
-//            transform along x (decimation in frequency: bit-reversed out),
-//            written back in that order;
+// The 256 x 256 complex tile (512 KiB) does not fit in LDS, so a ROI keeps it in
+// a slot of global scratch and moves 32 lines at a time through an LDS tile.  A
+// ROI's 8 chunks of 32 lines go to 8 workgroups, one kernel per step of the
+// transform (a step needs all of the previous one's chunks):
+//   gather   z = a + i b of 32 rows of the ROI (remapped reference, test) into
+//            the slot, natural order;
+//   sums     the two means, one workgroup per ROI (its column sums in row order);
+//   rows     mean removal, Hann window, energies, forward transform along x
+//            (decimation in frequency: bit-reversed out);
 //   columns  per 32 physical columns: forward transform along y, the cross
 //            power spectrum P(k) = B(k) conj A(k) (A, B separated from Z(k)
 //            and Z(-k) as for the smaller ROIs), inverse transform along y;
@@ -542,22 +565,35 @@ __device__ void xcf_core(XcfShared<N>& S, Loader load, int window, float* q, flo
 //            logical kx = 16 rev4(i) + rev4(j) onto the block rev4((16 -
 //            rev4(j)) mod 16) of the partners -kx; blocks 0 and 1 are their own
 //            partners, the others pair up);
-//   inverse  per 32 rows: inverse transform along x (bit-reversed in, natural
-//            out), the real part into the slot's correlation plane, each
-//            thread's argmax (ties to the lowest row-major index);
-// then the block's argmax and the 2-D quadratic fit of its neighbourhood.
+//   inverse  inverse transform along x (bit-reversed in, natural out), the real
+//            part into the slot's correlation plane, the chunk's argmax (ties to
+//            the lowest row-major index);
+//   finish   the ROI's argmax and the 2-D quadratic fit of its neighbourhood.
+// ROIs go through in groups of at most kX2Slots, sized so that the slots in use
+// stay in the last-level cache (196 MB of 256).  Bound: the LDS passes and the
+// slots' traffic (3.75 MB per ROI).  With one workgroup per ROI for all steps a
+// single pattern's 101 ROIs left most of the chip idle (621 us).
 // Every butterfly is the one the LDS-resident kernels compute for N = 256.
-constexpr int kX2 = 256, kX2Lines = 32, kX2Pitch = kX2 + 1;
-constexpr int64_t kX2SlotFloats = (int64_t)2 * kX2 * kX2 + (int64_t)kX2 * kX2;  // complex tile + real plane
-constexpr int kX2Slots = 512;  // workgroups (two per compute unit at 68 KiB of LDS each)
+constexpr int kX2 = 256, kX2Lines = 32, kX2Pitch = kX2 + 1, kX2Chunks = kX2 / kX2Lines;
+constexpr int kX2Threads = 512;
+// a slot: complex tile, real plane, then the ROI's means and per-chunk results
+constexpr int64_t kX2Plane = (int64_t)2 * kX2 * kX2, kX2Stats = kX2Plane + (int64_t)kX2 * kX2;
+constexpr int64_t kX2SlotFloats = kX2Stats + 64;
+constexpr int kX2Slots = 256;
+struct X2Stats {
+    float ma, mb;
+    float ea[kX2Chunks], eb[kX2Chunks];
+    float bv[kX2Chunks];
+    int bi[kX2Chunks];
+};
+static_assert(sizeof(X2Stats) <= 64 * sizeof(float), "statistics exceed their part of the slot");
 
 struct Xcf256Shared {
     float2 t[kX2Lines][kX2Pitch];
     float2 tw[kX2 / 2];
     float win[kX2];
-    float red[4][NT / 64];
-    float bv[NT / 64];
-    int bi[NT / 64];
+    float ra[kX2Threads / 64], rb[kX2Threads / 64];
+    int ri[kX2Threads / 64];
 };
 
 __device__ inline int rev4(int v) { return (int)(__brev((unsigned)v) >> 28); }
@@ -572,7 +608,7 @@ __device__ void line_pass(Xcf256Shared& S)
     constexpr int N = kX2;
     constexpr int s = 1 << SL, M = 1 << R, span = M * s;
     constexpr int per_line = N / M;
-    for (int c = threadIdx.x; c < kX2Lines * per_line; c += NT) {
+    for (int c = threadIdx.x; c < kX2Lines * per_line; c += kX2Threads) {
         const int line = c % kX2Lines, k = c / kX2Lines;
         const int t = k % s, g = k / s;
         const int base = g * span + t;
@@ -643,115 +679,187 @@ __device__ inline void x2_chunk_blocks(int c, int& ba, int& bb)
     ba = bb = 0;  // not reached for c < 8
 }
 
-template <class Loader>
-__device__ void xcf256_core(Xcf256Shared& S, float2* __restrict__ Z, float* __restrict__ Cr, Loader load,
-                            int window, float* q, float* ph)
+__device__ inline void x2_twiddles(Xcf256Shared& S)
 {
-    constexpr int N = kX2, L = kX2Lines;
-    const int tid = threadIdx.x;
-    for (int k = tid; k < N / 2; k += NT) {
+    for (int k = threadIdx.x; k < kX2 / 2; k += kX2Threads) {
         double sn, cs;
-        sincospi(-2.0 * (double)k / (double)N, &sn, &cs);
+        sincospi(-2.0 * (double)k / (double)kX2, &sn, &cs);
         S.tw[k] = make_float2((float)cs, (float)sn);
     }
-    for (int n = tid; n < N; n += NT)
-        S.win[n] = window ? (float)(0.5 - 0.5 * cospi(2.0 * (double)n / (double)(N - 1))) : 1.0f;
+}
 
-    // gather + means
+// Workgroup of a per-chunk kernel: its ROI's slot and its chunk (the chunks of a
+// ROI on one XCD).
+__device__ inline float* x2_slot(float* scratch, int& chunk, int& r)
+{
+    const int lb = (int)gridDim.x % 8 == 0 ? ((int)blockIdx.x & 7) * ((int)gridDim.x >> 3) + ((int)blockIdx.x >> 3)
+                                           : (int)blockIdx.x;
+    r = lb / kX2Chunks;
+    chunk = lb - r * kX2Chunks;
+    return scratch + (int64_t)r * kX2SlotFloats;
+}
+
+// 32 rows of the ROI, thread = column (two row groups)
+template <class Loader>
+__device__ void x2_gather(float* slot, int chunk, const Loader& load)
+{
+    float2* __restrict__ Z = reinterpret_cast<float2*>(slot);
+    const int x = threadIdx.x & (kX2 - 1);
+#pragma unroll 2
+    for (int y = chunk * kX2Lines + (threadIdx.x >> 8); y < (chunk + 1) * kX2Lines; y += kX2Threads / kX2)
+        Z[y * kX2 + x] = load(x, y);
+}
+
+// The means: thread = column, rows in order, then the block's sum.
+__global__ void __launch_bounds__(NT) k_x2_sums(float* __restrict__ scratch)
+{
+    __shared__ float red[4][NT / 64];
+    float* slot = scratch + (int64_t)blockIdx.x * kX2SlotFloats;
+    const float2* __restrict__ Z = reinterpret_cast<const float2*>(slot) + threadIdx.x;
     float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int p = tid; p < N * N; p += NT) {
-        const float2 ab = load(p & (N - 1), p >> 8);
-        Z[p] = ab;
-        acc[0] += ab.x;
-        acc[1] += ab.y;
+    for (int y = 0; y < kX2; y += 16) {
+        float2 v[16];
+#pragma unroll
+        for (int k = 0; k < 16; k++) v[k] = Z[(y + k) * kX2];
+#pragma unroll
+        for (int k = 0; k < 16; k++) {
+            acc[0] += v[k].x;
+            acc[1] += v[k].y;
+        }
     }
-    block_sum4(acc, S.red, 2);  // its barriers also order the slot's writes before the reads below
-    const float ma = acc[0] / (float)(N * N), mb = acc[1] / (float)(N * N);
+    block_sum4(acc, red, 2);
+    if (threadIdx.x == 0) {
+        X2Stats* st = reinterpret_cast<X2Stats*>(slot + kX2Stats);
+        st->ma = acc[0] / (float)(kX2 * kX2);
+        st->mb = acc[1] / (float)(kX2 * kX2);
+    }
+}
 
-    // rows: window, energies, forward transform
+__global__ void __launch_bounds__(kX2Threads) k_x2_rows(float* __restrict__ scratch, int window)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    Xcf256Shared& S = *reinterpret_cast<Xcf256Shared*>(smem);
+    constexpr int N = kX2, L = kX2Lines;
+    const int tid = threadIdx.x;
+    int chunk, r;
+    float* slot = x2_slot(scratch, chunk, r);
+    float2* __restrict__ Z = reinterpret_cast<float2*>(slot) + chunk * L * N;
+    X2Stats* st = reinterpret_cast<X2Stats*>(slot + kX2Stats);
+    const float ma = st->ma, mb = st->mb;
+    x2_twiddles(S);
+    for (int n = tid; n < N; n += kX2Threads)
+        S.win[n] = window ? (float)(0.5 - 0.5 * cospi(2.0 * (double)n / (double)(N - 1))) : 1.0f;
+    __syncthreads();
     float en0 = 0.0f, en1 = 0.0f;
-    for (int r0 = 0; r0 < N; r0 += L) {
-        for (int i = tid; i < L * N; i += NT) {
-            const int line = i >> 8, x = i & (N - 1);
-            const float2 ab = Z[(r0 + line) * N + x];
-            const float wgt = S.win[r0 + line] * S.win[x];
-            const float a = (ab.x - ma) * wgt, b = (ab.y - mb) * wgt;
-            en0 += a * a;
-            en1 += b * b;
-            S.t[line][x] = make_float2(a, b);
-        }
-        __syncthreads();
-        lines_dif(S);
-        for (int i = tid; i < L * N; i += NT) {
-            const int line = i >> 8, x = i & (N - 1);
-            Z[(r0 + line) * N + x] = S.t[line][x];
-        }
-        __syncthreads();
+#pragma unroll 4
+    for (int i = tid; i < L * N; i += kX2Threads) {
+        const int line = i >> 8, x = i & (N - 1);
+        const float2 ab = Z[i];
+        const float wgt = S.win[chunk * L + line] * S.win[x];
+        const float a = (ab.x - ma) * wgt, b = (ab.y - mb) * wgt;
+        en0 += a * a;
+        en1 += b * b;
+        S.t[line][x] = make_float2(a, b);
     }
+    __syncthreads();
+    lines_dif(S);
+#pragma unroll 4
+    for (int i = tid; i < L * N; i += kX2Threads) Z[i] = S.t[i >> 8][i & (N - 1)];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        en0 += __shfl_xor(en0, off, 64);
+        en1 += __shfl_xor(en1, off, 64);
+    }
+    if ((tid & 63) == 0) {
+        S.ra[tid >> 6] = en0;
+        S.rb[tid >> 6] = en1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        float ea = 0.0f, eb = 0.0f;
+        for (int i = 0; i < kX2Threads / 64; i++) {
+            ea += S.ra[i];
+            eb += S.rb[i];
+        }
+        st->ea[chunk] = ea;
+        st->eb[chunk] = eb;
+    }
+}
 
-    // columns: forward transform, cross power spectrum, inverse transform
+__global__ void __launch_bounds__(kX2Threads) k_x2_cols(float* __restrict__ scratch)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    Xcf256Shared& S = *reinterpret_cast<Xcf256Shared*>(smem);
+    constexpr int N = kX2, L = kX2Lines;
+    const int tid = threadIdx.x;
+    int chunk, r;
+    float2* __restrict__ Z = reinterpret_cast<float2*>(x2_slot(scratch, chunk, r));
+    x2_twiddles(S);
     const float scale = 1.0f / (float)(N * N);
-    for (int c = 0; c < 8; c++) {
-        int ba, bb;
-        x2_chunk_blocks(c, ba, bb);
-        for (int i = tid; i < L * N; i += NT) {
-            const int y = i >> 5, l = i & (L - 1);
-            const int px = (l < 16 ? ba : bb) * 16 + (l & 15);
-            S.t[l][y] = Z[y * N + px];
-        }
-        __syncthreads();
-        lines_dif(S);
-        for (int i = tid; i < L * N; i += NT) {
-            const int l = i >> 8, py = i & (N - 1);
-            const int px = (l < 16 ? ba : bb) * 16 + (l & 15);
-            const int ky = rev8(py), kx = rev8(px);
-            const int qy = rev8((N - ky) & (N - 1)), qx = rev8((N - kx) & (N - 1));
-            const int ql = ((qx >> 4) == ba ? 0 : 16) + (qx & 15);
-            if (ql * N + qy < i) continue;  // each pair once
-            const float2 z1 = S.t[l][py], z2 = S.t[ql][qy];
-            const float2 A = make_float2(0.5f * (z1.x + z2.x), 0.5f * (z1.y - z2.y));
-            const float2 B = make_float2(0.5f * (z1.y + z2.y), -0.5f * (z1.x - z2.x));
-            float2 P = cmulc(B, A);
-            P.x *= scale;
-            P.y *= scale;
-            if (ql * N + qy == i) {
-                S.t[l][py] = make_float2(P.x, 0.0f);
-            } else {
-                S.t[l][py] = P;
-                S.t[ql][qy] = make_float2(P.x, -P.y);
-            }
-        }
-        __syncthreads();
-        lines_dit(S);
-        for (int i = tid; i < L * N; i += NT) {
-            const int y = i >> 5, l = i & (L - 1);
-            const int px = (l < 16 ? ba : bb) * 16 + (l & 15);
-            Z[y * N + px] = S.t[l][y];
-        }
-        __syncthreads();
+    int ba, bb;
+    x2_chunk_blocks(chunk, ba, bb);
+#pragma unroll 4
+    for (int i = tid; i < L * N; i += kX2Threads) {
+        const int y = i >> 5, l = i & (L - 1);
+        S.t[l][y] = Z[y * N + (l < 16 ? ba : bb) * 16 + (l & 15)];
     }
+    __syncthreads();
+    lines_dif(S);
+    for (int i = tid; i < L * N; i += kX2Threads) {
+        const int l = i >> 8, py = i & (N - 1);
+        const int px = (l < 16 ? ba : bb) * 16 + (l & 15);
+        const int ky = rev8(py), kx = rev8(px);
+        const int qy = rev8((N - ky) & (N - 1)), qx = rev8((N - kx) & (N - 1));
+        const int ql = ((qx >> 4) == ba ? 0 : 16) + (qx & 15);
+        if (ql * N + qy < i) continue;  // each pair once
+        const float2 z1 = S.t[l][py], z2 = S.t[ql][qy];
+        const float2 A = make_float2(0.5f * (z1.x + z2.x), 0.5f * (z1.y - z2.y));
+        const float2 B = make_float2(0.5f * (z1.y + z2.y), -0.5f * (z1.x - z2.x));
+        float2 P = cmulc(B, A);
+        P.x *= scale;
+        P.y *= scale;
+        if (ql * N + qy == i) {
+            S.t[l][py] = make_float2(P.x, 0.0f);
+        } else {
+            S.t[l][py] = P;
+            S.t[ql][qy] = make_float2(P.x, -P.y);
+        }
+    }
+    __syncthreads();
+    lines_dit(S);
+#pragma unroll 4
+    for (int i = tid; i < L * N; i += kX2Threads) {
+        const int y = i >> 5, l = i & (L - 1);
+        Z[y * N + (l < 16 ? ba : bb) * 16 + (l & 15)] = S.t[l][y];
+    }
+}
 
-    // rows: inverse transform, real part, argmax (NaNs never win)
-    float bv = -INFINITY;
+__global__ void __launch_bounds__(kX2Threads) k_x2_inverse(float* __restrict__ scratch)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    Xcf256Shared& S = *reinterpret_cast<Xcf256Shared*>(smem);
+    constexpr int N = kX2, L = kX2Lines;
+    const int tid = threadIdx.x;
+    int chunk, r;
+    float* slot = x2_slot(scratch, chunk, r);
+    const float2* __restrict__ Z = reinterpret_cast<const float2*>(slot) + chunk * L * N;
+    float* __restrict__ Cr = slot + kX2Plane;
+    X2Stats* st = reinterpret_cast<X2Stats*>(slot + kX2Stats);
+    x2_twiddles(S);
+#pragma unroll 4
+    for (int i = tid; i < L * N; i += kX2Threads) S.t[i >> 8][i & (N - 1)] = Z[i];
+    __syncthreads();
+    lines_dit(S);
+    float bv = -INFINITY;  // NaNs never win
     int bi = 0x7fffffff;
-    for (int r0 = 0; r0 < N; r0 += L) {
-        for (int i = tid; i < L * N; i += NT) {
-            const int line = i >> 8, x = i & (N - 1);
-            S.t[line][x] = Z[(r0 + line) * N + x];
+    for (int i = tid; i < L * N; i += kX2Threads) {
+        const int p = chunk * L * N + i;
+        const float v = S.t[i >> 8][i & (N - 1)].x;
+        Cr[p] = v;
+        if (v > bv || (v == bv && p < bi)) {
+            bv = v;
+            bi = p;
         }
-        __syncthreads();
-        lines_dit(S);
-        for (int i = tid; i < L * N; i += NT) {
-            const int line = i >> 8, x = i & (N - 1);
-            const int p = (r0 + line) * N + x;
-            const float v = S.t[line][x].x;
-            Cr[p] = v;
-            if (v > bv || (v == bv && p < bi)) {
-                bv = v;
-                bi = p;
-            }
-        }
-        __syncthreads();
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -761,37 +869,43 @@ __device__ void xcf256_core(Xcf256Shared& S, float2* __restrict__ Z, float* __re
             bv = ov;
             bi = oi;
         }
-        en0 += __shfl_xor(en0, off, 64);
-        en1 += __shfl_xor(en1, off, 64);
     }
-    const int lane = tid & 63, wv = tid >> 6;
-    if (lane == 0) {
-        S.bv[wv] = bv;
-        S.bi[wv] = bi;
-        S.red[0][wv] = en0;
-        S.red[1][wv] = en1;
+    if ((tid & 63) == 0) {
+        S.ra[tid >> 6] = bv;
+        S.ri[tid >> 6] = bi;
     }
     __syncthreads();
     if (tid == 0) {
-        float ea = 0.0f, eb = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NT / 64; i++) {
-            ea += S.red[0][i];
-            eb += S.red[1][i];
-        }
-        bv = S.bv[0];
-        bi = S.bi[0];
-        for (int i = 1; i < NT / 64; i++)
-            if (S.bv[i] > bv || (S.bv[i] == bv && S.bi[i] < bi)) {
-                bv = S.bv[i];
-                bi = S.bi[i];
+        for (int i = 1; i < kX2Threads / 64; i++)
+            if (S.ra[i] > bv || (S.ra[i] == bv && S.ri[i] < bi)) {
+                bv = S.ra[i];
+                bi = S.ri[i];
             }
-        if (bi < 0 || bi >= N * N) bi = 0;  // all-NaN correlation
-        const int ky = bi >> 8, kx = bi & (N - 1);
-        auto C = [&](int dy, int dx) -> double { return (double)Cr[((ky + dy) & (N - 1)) * N + ((kx + dx) & (N - 1))]; };
-        peak_fit<N>(C, ky, kx, ea, eb, q, ph);
+        st->bv[chunk] = bv;
+        st->bi[chunk] = bi;
     }
-    __syncthreads();  // the slot is reused by the workgroup's next ROI
+}
+
+// One thread per ROI of the group: q [rois][2], ph [rois] (may be NULL).
+__device__ inline void x2_finish(float* slot, float* q, float* ph)
+{
+    constexpr int N = kX2;
+    const float* __restrict__ Cr = slot + kX2Plane;
+    const X2Stats* st = reinterpret_cast<const X2Stats*>(slot + kX2Stats);
+    float ea = 0.0f, eb = 0.0f, bv = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int c = 0; c < kX2Chunks; c++) {
+        ea += st->ea[c];
+        eb += st->eb[c];
+        if (st->bv[c] > bv || (st->bv[c] == bv && st->bi[c] < bi)) {
+            bv = st->bv[c];
+            bi = st->bi[c];
+        }
+    }
+    if (bi < 0 || bi >= N * N) bi = 0;  // all-NaN correlation
+    const int ky = bi >> 8, kx = bi & (N - 1);
+    auto C = [&](int dy, int dx) -> double { return (double)Cr[((ky + dy) & (N - 1)) * N + ((kx + dx) & (N - 1))]; };
+    peak_fit<N>(C, ky, kx, ea, eb, q, ph);
 }
 
 // One workgroup per (pair, ROI).  INTERP 3 / 1: the second pass, the
@@ -857,7 +971,11 @@ struct RoiLoader {
         const double v0 = r00 * p0 + r10 * p1 + r20 * p2;
         const double v1 = r01 * p0 + r11 * p1 + r21 * p2;
         const double v2 = r02 * p0 + r12 * p1 + r22 * p2;
-        const double sx = xs + zs * v0 / v2, sy = ys + zs * v1 / v2;
+        // both quotients from one reciprocal: a correction step gives the correctly
+        // rounded quotient (Markstein 1990)
+        const double iv = 1.0 / v2, n0 = zs * v0, n1 = zs * v1;
+        const double q0 = n0 * iv, q1 = n1 * iv;
+        const double sx = xs + fma(fma(-q0, v2, n0), iv, q0), sy = ys + fma(fma(-q1, v2, n1), iv, q1);
         const float a = INTERP == 3 ? bspline_d(Cf, H, W, sx, sy) : bilinear_d(Rn, H, W, sx, sy);
         return make_float2(a, Tn[(int64_t)Y * W + X]);
     }
@@ -877,38 +995,66 @@ __global__ void __launch_bounds__(NT) k_xcf_pairs(const Bucket* __restrict__ bk,
     xcf_core<N>(S, load, window, (INTERP == 0 ? bk->q1 : bk->q2) + 2 * o, bk->ph + o);
 }
 
-// ROIs of 256: a grid of at most kX2Slots workgroups walks the (pair, ROI)
-// list; workgroup g works in scratch slot g.
+// ROIs of 256, first + r of the (pair, ROI) list in slot r.
 template <int INTERP>
-__global__ void __launch_bounds__(NT) k_xcf256_pairs(const Bucket* __restrict__ bk, int window, int pass,
-                                                     float* __restrict__ scratch)
+__global__ void __launch_bounds__(kX2Threads)
+    k_x2_gather_pairs(const Bucket* __restrict__ bk, int pass, int first, float* __restrict__ scratch)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    Xcf256Shared& S = *reinterpret_cast<Xcf256Shared*>(smem);
-    float* slot = scratch + (int64_t)blockIdx.x * kX2SlotFloats;
-    const int total = bk->nb * bk->n_roi;
-    for (int r = blockIdx.x; r < total; r += gridDim.x) {
-        const int b = r / bk->n_roi, j = r - (r / bk->n_roi) * bk->n_roi;
-        const RoiLoader<INTERP> load(bk, b, j, pass);
-        xcf256_core(S, reinterpret_cast<float2*>(slot), slot + 2 * kX2 * kX2, load, window,
-                    (INTERP == 0 ? bk->q1 : bk->q2) + 2 * (int64_t)r, bk->ph + r);
-    }
+    int chunk, r;
+    float* slot = x2_slot(scratch, chunk, r);
+    const int b = (first + r) / bk->n_roi, j = first + r - b * bk->n_roi;
+    x2_gather(slot, chunk, RoiLoader<INTERP>(bk, b, j, pass));
+}
+template <int INTERP>
+__global__ void __launch_bounds__(64) k_x2_finish_pairs(const Bucket* __restrict__ bk, int first, int rois,
+                                                        float* __restrict__ scratch)
+{
+    const int r = blockIdx.x * 64 + threadIdx.x;
+    if (r < rois)
+        x2_finish(scratch + (int64_t)r * kX2SlotFloats, (INTERP == 0 ? bk->q1 : bk->q2) + 2 * (int64_t)(first + r),
+                  bk->ph + first + r);
 }
 
-__global__ void __launch_bounds__(NT)
-    k_xcf256_stage(const float* __restrict__ A, const float* __restrict__ B, int n, int window,
-                   float* __restrict__ q, float* __restrict__ ph, float* __restrict__ scratch)
+__global__ void __launch_bounds__(kX2Threads)
+    k_x2_gather_stage(const float* __restrict__ A, const float* __restrict__ B, int first, float* __restrict__ scratch)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    Xcf256Shared& S = *reinterpret_cast<Xcf256Shared*>(smem);
-    float* slot = scratch + (int64_t)blockIdx.x * kX2SlotFloats;
-    for (int r = blockIdx.x; r < n; r += gridDim.x) {
-        const float* a = A + (int64_t)r * kX2 * kX2;
-        const float* bb = B + (int64_t)r * kX2 * kX2;
-        auto load = [&](int x, int y) -> float2 { return make_float2(a[y * kX2 + x], bb[y * kX2 + x]); };
-        xcf256_core(S, reinterpret_cast<float2*>(slot), slot + 2 * kX2 * kX2, load, window, q + 2 * (int64_t)r,
-                    ph ? ph + r : nullptr);
+    int chunk, r;
+    float* slot = x2_slot(scratch, chunk, r);
+    const float* a = A + (int64_t)(first + r) * kX2 * kX2;
+    const float* bb = B + (int64_t)(first + r) * kX2 * kX2;
+    x2_gather(slot, chunk, [&](int x, int y) -> float2 { return make_float2(a[y * kX2 + x], bb[y * kX2 + x]); });
+}
+__global__ void __launch_bounds__(64) k_x2_finish_stage(int first, int rois, float* __restrict__ scratch,
+                                                        float* __restrict__ q, float* __restrict__ ph)
+{
+    const int r = blockIdx.x * 64 + threadIdx.x;
+    if (r < rois)
+        x2_finish(scratch + (int64_t)r * kX2SlotFloats, q + 2 * (int64_t)(first + r), ph ? ph + first + r : nullptr);
+}
+
+// The ROIs in equal groups; gather(first, rois) and finish(first, rois) launch
+// the steps that read the inputs and write the results.
+template <class Gather, class Finish>
+hipError_t launch_x2(int total, int window, float* scratch, hipStream_t s, Gather gather, Finish finish)
+{
+    const size_t sm = sizeof(Xcf256Shared);
+    static std::atomic<uint64_t> done_r{0}, done_c{0}, done_i{0};
+    hipError_t e = ensure_dynamic_lds((const void*)k_x2_rows, (int)sm, done_r);
+    if (e == hipSuccess) e = ensure_dynamic_lds((const void*)k_x2_cols, (int)sm, done_c);
+    if (e == hipSuccess) e = ensure_dynamic_lds((const void*)k_x2_inverse, (int)sm, done_i);
+    if (e != hipSuccess) return e;
+    const int groups = (total + kX2Slots - 1) / kX2Slots, per = (total + groups - 1) / groups;
+    for (int first = 0; first < total; first += per) {
+        const int rois = std::min(per, total - first);
+        const dim3 grid((unsigned)(rois * kX2Chunks));
+        gather(first, grid);
+        hipLaunchKernelGGL(k_x2_sums, dim3((unsigned)rois), dim3(NT), 0, s, scratch);
+        hipLaunchKernelGGL(k_x2_rows, grid, dim3(kX2Threads), sm, s, scratch, window);
+        hipLaunchKernelGGL(k_x2_cols, grid, dim3(kX2Threads), sm, s, scratch);
+        hipLaunchKernelGGL(k_x2_inverse, grid, dim3(kX2Threads), sm, s, scratch);
+        finish(first, rois);
     }
+    return hipGetLastError();
 }
 
 template <int N>
@@ -940,14 +1086,17 @@ template <int INTERP>
 hipError_t launch_pairs256(const Bucket* d_bk, const Bucket& hb, int window, int pass, hipStream_t s)
 {
     const int total = hb.nb * hb.n_roi;
-    if (!hb.xcf_scratch || total <= 0) return hipErrorInvalidValue;
-    const size_t sm = sizeof(Xcf256Shared);
-    static std::atomic<uint64_t> attr_done{0};
-    const hipError_t e = ensure_dynamic_lds((const void*)k_xcf256_pairs<INTERP>, (int)sm, attr_done);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_xcf256_pairs<INTERP>), dim3(std::min(total, kX2Slots)), dim3(NT), sm, s, d_bk, window,
-                       pass, hb.xcf_scratch);
-    return hipGetLastError();
+    float* scratch = hb.xcf_scratch;
+    if (!scratch || total <= 0) return hipErrorInvalidValue;
+    return launch_x2(
+        total, window, scratch, s,
+        [&](int first, dim3 grid) {
+            hipLaunchKernelGGL((k_x2_gather_pairs<INTERP>), grid, dim3(kX2Threads), 0, s, d_bk, pass, first, scratch);
+        },
+        [&](int first, int rois) {
+            hipLaunchKernelGGL((k_x2_finish_pairs<INTERP>), dim3((unsigned)((rois + 63) / 64)), dim3(64), 0, s, d_bk,
+                               first, rois, scratch);
+        });
 }
 
 template <int INTERP>
@@ -1023,16 +1172,17 @@ hipError_t launch_stage_xcf(const float* A, const float* B, int n, int N, int wi
     case 32: return launch_stage_n<32>(A, B, n, window, q, ph, s);
     case 64: return launch_stage_n<64>(A, B, n, window, q, ph, s);
     case 128: return launch_stage_n<128>(A, B, n, window, q, ph, s);
-    case 256: {
-        if (!scratch) return hipErrorInvalidValue;
-        const size_t sm = sizeof(Xcf256Shared);
-        static std::atomic<uint64_t> attr_done{0};
-        const hipError_t e = ensure_dynamic_lds((const void*)k_xcf256_stage, (int)sm, attr_done);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_xcf256_stage, dim3(std::min(n, kX2Slots)), dim3(NT), sm, s, A, B, n, window, q, ph,
-                           scratch);
-        return hipGetLastError();
-    }
+    case 256:
+        if (!scratch || n <= 0) return hipErrorInvalidValue;
+        return launch_x2(
+            n, window, scratch, s,
+            [&](int first, dim3 grid) {
+                hipLaunchKernelGGL(k_x2_gather_stage, grid, dim3(kX2Threads), 0, s, A, B, first, scratch);
+            },
+            [&](int first, int rois) {
+                hipLaunchKernelGGL(k_x2_finish_stage, dim3((unsigned)((rois + 63) / 64)), dim3(64), 0, s, first, rois,
+                                   scratch, q, ph);
+            });
     default: return hipErrorInvalidValue;
     }
 }
