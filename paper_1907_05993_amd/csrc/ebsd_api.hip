@@ -533,6 +533,11 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     const size_t o_ref_pyr = w.take(sizeof(float) * (size_t)nref * pe);
     const size_t o_tstat = w.take(sizeof(PatStat) * nb);
     const size_t o_rstat = w.take(sizeof(PatStat) * nref);
+    const auto aligned16 = [](const float* q) { return ((uintptr_t)q & 15) == 0; };
+    const bool aligned = std::all_of(hbk.test_in.begin(), hbk.test_in.end(), aligned16) &&
+                         std::all_of(hbk.ref_in.begin(), hbk.ref_in.end(), aligned16);
+    const int64_t chain_doubles = stat_chain_doubles(nb + nref, (int64_t)H * W, aligned);
+    const size_t o_chain = w.take(sizeof(double) * (size_t)chain_doubles);
     const size_t field_bytes = mode == Mode::Full ? sizeof(float) * 2 * (size_t)nb * H * W : 0;
     const size_t o_f0 = w.take(field_bytes);
     const size_t o_f1 = w.take(field_bytes);
@@ -715,7 +720,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         }
         if (bandpass) EBSD_TRY(launch_bandpass(lv, make_band_taps(p.bandpass_lo_px, p.bandpass_hi_px), s));
     }
-    EBSD_TRY(launch_stats(d_bk, nb, nref, s));
+    EBSD_TRY(launch_stats(d_bk, nb, nref, chain_doubles ? reinterpret_cast<double*>(base + o_chain) : nullptr, s));
     EBSD_TRY(launch_pyramids(d_bk, b, s));
     if (tune_only) {
         // time each supported strip height for every row-marching level

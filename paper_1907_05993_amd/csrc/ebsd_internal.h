@@ -150,7 +150,12 @@ struct Bucket {
 // ---- launchers (defined next to their kernels) -------------------------------
 
 // Normalisation statistics for nb test patterns and nref reference patterns.
-hipError_t launch_stats(const Bucket* d_bk, int nb, int nref, hipStream_t s);
+// chains (stat_chain_doubles, NULL where that is 0): a pattern's sums by several
+// workgroups, for few (at most 256) large (at least 2^17 pixels) patterns whose
+// data is 16-byte aligned; else one workgroup per pattern, which many patterns
+// fill the device with and small ones finish in a few us.  Same results.
+int64_t stat_chain_doubles(int npat, int64_t n, bool aligned);
+hipError_t launch_stats(const Bucket* d_bk, int nb, int nref, double* chains, hipStream_t s);
 // Normalise level 0 of every pyramid and build levels 1..L-1.
 hipError_t launch_pyramids(const Bucket* d_bk, const Bucket& hb, hipStream_t s);
 // Reset per-pair state and set the coarsest-level initial field

@@ -128,62 +128,126 @@ __global__ void __launch_bounds__(64 * NWV)
 }
 
 // Without smoothing (r = 0) pixels do not interact: one launch runs all `cap`
-// iterations of a level, each thread its own pixel, field in registers (the
+// iterations of a level, each thread its own pixels, field in registers (the
 // field is read and written once per level instead of once per iteration).
-// Fixed iteration count only.  Bound: the iteration's vector ALU work and its
-// two 8-byte gathers (L1 / L2); two pixels per thread overlap their gathers.
-constexpr int kPointThreads = 256, kPointPx = 2;
+// Fixed iteration count only.  The unsmoothed field is irregular, so the lanes'
+// gathers fall on different cache lines; from the vector cache (one line per
+// clock) 12 patterns of 1244 x 1024 took 1.91 ms for 25 iterations.  A workgroup
+// therefore keeps the test pattern around its tile's displaced position in LDS
+// (64 columns x 4 PX rows, a margin of 32 px on every side, placed by the
+// tile's mean displacement) and gathers there; lanes whose cell lies outside
+// the window read memory instead (1.16 ms; a margin of 20 px 1.33, of 44 px
+// 1.20).  Bound: vector ALU.  PX = 8 pixels per thread, or 2 where that leaves
+// CUs without work (the levels of one or few patterns).
+constexpr int kPointThreads = 256, kPointTX = 64, kPointMargin = 32;
 
+template <int PX>
 __global__ void __launch_bounds__(kPointThreads)
-    k_demons_points(const Bucket* __restrict__ bk, int level, float w0, int nblocks, int cap)
+    k_demons_points(const Bucket* __restrict__ bk, int level, float w0, int ntx, int ntiles, int cap)
 {
+    constexpr int kPointPx = PX, kPointGroup = PX < 4 ? PX : 4;  // pixels of a thread, and iterated together
+    constexpr int kPointTY = PX * kPointThreads / kPointTX;
+    constexpr int kPointWW = kPointTX + 2 * kPointMargin, kPointWH = kPointTY + 2 * kPointMargin;
+    __shared__ float win[kPointWH * kPointWW];
+    __shared__ float red[2][kPointThreads / 64];
     const int lb = xcd_logical_block(blockIdx.x, gridDim.x);
-    const int b = lb / nblocks, blk = lb - b * nblocks;
+    const int b = lb / ntiles, tile = lb - b * ntiles;
+    const int tx0 = (tile % ntx) * kPointTX, ty0 = (tile / ntx) * kPointTY;
     const int h = bk->lh[level], w = bk->lw[level], n = h * w;
     const int base = bk->state[b].base;
     const int64_t slot = (int64_t)b * 2 * bk->H * bk->W;
+    const float* __restrict__ Tg = bk->test_pyr + (int64_t)b * bk->pyr_elems + bk->lvl_off[level];
     const EBSD_GLOBAL float* __restrict__ R =
         gptr(bk->ref_pyr + (int64_t)bk->ref_slot[b] * bk->pyr_elems + bk->lvl_off[level]);
-    const GatherBase T = gather_base(bk->test_pyr + (int64_t)b * bk->pyr_elems + bk->lvl_off[level], h, w);
+    const GatherBase T = gather_base(Tg, h, w);
     const EBSD_GLOBAL float* __restrict__ u = gptr(bk->field[base & 1] + slot);
     EBSD_GLOBAL float* __restrict__ un = gptr(bk->field[(base + 1) & 1] + slot);
     const BilGeom g = bil_geom(h, w);
-    float ux[kPointPx], uy[kPointPx], r[kPointPx], gx[kPointPx], gy[kPointPx], px[kPointPx], py[kPointPx];
-    int at[kPointPx];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int x = min(tx0 + lane, w - 1);
+    float ux[kPointPx], uy[kPointPx];
+    float mx = 0.0f, my = 0.0f;
 #pragma unroll
     for (int k = 0; k < kPointPx; k++) {
-        at[k] = (blk * kPointPx + k) * kPointThreads + (int)threadIdx.x;
-        const int o = min(at[k], n - 1);
-        const int y = o / w, x = o - y * w;
-        const int xm = max(x - 1, 0), xp = min(x + 1, w - 1);
-        const int ym = max(y - 1, 0), yp = min(y + 1, h - 1);
-        ux[k] = u[o];
-        uy[k] = u[n + o];
-        r[k] = R[o];
-        gx[k] = (R[y * w + xp] - R[y * w + xm]) * ((xp - xm == 2) ? 0.5f : 1.0f);
-        gy[k] = (R[yp * w + x] - R[ym * w + x]) * ((yp - ym == 2) ? 0.5f : 1.0f);
-        px[k] = (float)x;
-        py[k] = (float)y;
+        const int y = min(ty0 + wave + k * (kPointThreads / 64), h - 1);
+        ux[k] = u[y * w + x];
+        uy[k] = u[n + y * w + x];
+        mx += ux[k];
+        my += uy[k];
     }
-    for (int i = 0; i < cap; i++) {
-        Bilin t[kPointPx];
+    // the window's corner (any value is valid: it only decides which gathers are from LDS)
+    mx = wave_sum(mx);
+    my = wave_sum(my);
+    if (lane == 0) {
+        red[0][wave] = mx;
+        red[1][wave] = my;
+    }
+    __syncthreads();
+    mx = my = 0.0f;
 #pragma unroll
-        for (int k = 0; k < kPointPx; k++) t[k] = bilinear_issue_g(T, g, px[k] + ux[k], py[k] + uy[k]);
+    for (int i = 0; i < kPointThreads / 64; i++) {
+        mx += red[0][i];
+        my += red[1][i];
+    }
+    const float sc = 1.0f / (kPointTX * kPointTY);
+    const int wx0 = tx0 - kPointMargin + (int)fminf(fmaxf(mx * sc, -(float)w), (float)w);
+    const int wy0 = ty0 - kPointMargin + (int)fminf(fmaxf(my * sc, -(float)h), (float)h);
+    for (int i = threadIdx.x; i < kPointWH * kPointWW; i += kPointThreads) {
+        const int yy = i / kPointWW, xx = i - yy * kPointWW;
+        win[i] = Tg[clampi(wy0 + yy, 0, h - 1) * w + clampi(wx0 + xx, 0, w - 1)];
+    }
+    __syncthreads();
+    const float fx0 = (float)wx0, fy0 = (float)wy0;
 #pragma unroll
-        for (int k = 0; k < kPointPx; k++) {
-            float vx, vy;
-            demons_force(bilinear_blend_g(t[k]), r[k], gx[k], gy[k], ux[k], uy[k], vx, vy);
-            // the one-tap smoothing, both passes (w0 = 1)
-            ux[k] = fmaf(w0, fmaf(w0, vx, 0.0f), 0.0f);
-            uy[k] = fmaf(w0, fmaf(w0, vy, 0.0f), 0.0f);
+    for (int k0 = 0; k0 < kPointPx; k0 += kPointGroup) {
+        float r[kPointGroup], gx[kPointGroup], gy[kPointGroup], py[kPointGroup];
+#pragma unroll
+        for (int k = 0; k < kPointGroup; k++) {
+            const int y = min(ty0 + wave + (k0 + k) * (kPointThreads / 64), h - 1);
+            const int xm = max(x - 1, 0), xp = min(x + 1, w - 1);
+            const int ym = max(y - 1, 0), yp = min(y + 1, h - 1);
+            r[k] = R[y * w + x];
+            gx[k] = (R[y * w + xp] - R[y * w + xm]) * ((xp - xm == 2) ? 0.5f : 1.0f);
+            gy[k] = (R[yp * w + x] - R[ym * w + x]) * ((yp - ym == 2) ? 0.5f : 1.0f);
+            py[k] = (float)y;
+        }
+        for (int i = 0; i < cap; i++) {
+            Bilin t[kPointGroup];
+#pragma unroll
+            for (int k = 0; k < kPointGroup; k++) {
+                const float sx = (float)x + ux[k0 + k], sy = py[k] + uy[k0 + k];
+                // bilinear_issue_g's cell and weights
+                const float xc = fminf(fmaxf(sx, 0.0f), g.wm1), yc = fminf(fmaxf(sy, 0.0f), g.hm1);
+                const float xf = fminf(floorf(xc), g.wm2), yf = fminf(floorf(yc), g.hm2);
+                const float dx = xf - fx0, dy = yf - fy0;
+                const bool in = dx >= 0.0f && dx <= (float)(kPointWW - 2) && dy >= 0.0f && dy <= (float)(kPointWH - 2);
+                const int o = in ? (int)fmaf(dy, (float)kPointWW, dx) : 0;
+                t[k].v00 = win[o];
+                t[k].v01 = win[o + 1];
+                t[k].v10 = win[o + kPointWW];
+                t[k].v11 = win[o + kPointWW + 1];
+                t[k].fx = xc - xf;
+                t[k].fy = yc - yf;
+                if (!in) t[k] = bilinear_issue_g(T, g, sx, sy);
+            }
+#pragma unroll
+            for (int k = 0; k < kPointGroup; k++) {
+                float vx, vy;
+                demons_force(bilinear_blend_g(t[k]), r[k], gx[k], gy[k], ux[k0 + k], uy[k0 + k], vx, vy);
+                // the one-tap smoothing, both passes (w0 = 1)
+                ux[k0 + k] = fmaf(w0, fmaf(w0, vx, 0.0f), 0.0f);
+                uy[k0 + k] = fmaf(w0, fmaf(w0, vy, 0.0f), 0.0f);
+            }
         }
     }
 #pragma unroll
-    for (int k = 0; k < kPointPx; k++)
-        if (at[k] < n) {
-            un[at[k]] = ux[k];
-            un[n + at[k]] = uy[k];
+    for (int k = 0; k < kPointPx; k++) {
+        const int y = ty0 + wave + k * (kPointThreads / 64);
+        if (tx0 + lane < w && y < h) {
+            un[y * w + x] = ux[k];
+            un[n + y * w + x] = uy[k];
         }
+    }
 }
 
 template <int RAD, int K, int NWV>
@@ -236,10 +300,15 @@ hipError_t launch_demons_points(const Bucket* d_bk, const Bucket& hb, int level,
                                 hipStream_t s)
 {
     if (hb.nb <= 0 || hb.lh[level] < 2 || hb.lw[level] < 2) return hipErrorInvalidValue;
-    const int n = hb.lh[level] * hb.lw[level];
-    const int nblocks = (n + kPointThreads * kPointPx - 1) / (kPointThreads * kPointPx);
-    hipLaunchKernelGGL(k_demons_points, dim3((unsigned)((int64_t)hb.nb * nblocks)), dim3(kPointThreads), 0, s, d_bk,
-                       level, taps[0], nblocks, cap);
+    const int ntx = (hb.lw[level] + kPointTX - 1) / kPointTX;
+    const auto tiles = [&](int ty) { return ntx * ((hb.lh[level] + ty - 1) / ty); };
+    constexpr int rows = kPointThreads / kPointTX;  // of one pixel per thread
+    if ((int64_t)hb.nb * tiles(8 * rows) >= 1024)
+        hipLaunchKernelGGL(k_demons_points<8>, dim3((unsigned)((int64_t)hb.nb * tiles(8 * rows))), dim3(kPointThreads),
+                           0, s, d_bk, level, taps[0], ntx, tiles(8 * rows), cap);
+    else
+        hipLaunchKernelGGL(k_demons_points<2>, dim3((unsigned)((int64_t)hb.nb * tiles(2 * rows))), dim3(kPointThreads),
+                           0, s, d_bk, level, taps[0], ntx, tiles(2 * rows), cap);
     return hipGetLastError();
 }
 

@@ -59,41 +59,155 @@ __device__ double pattern_sum(const float* __restrict__ p, int64_t n, F f)
     return acc;
 }
 
-// Mean and 1/std of one pattern in FP64 (two passes: mean, then centred sum
-// of squares).  Non-finite values or zero contrast are flagged.
-__device__ void pattern_stats(const float* __restrict__ p, int64_t n, PatStat* out, double* sh)
+// Mean and 1/std from the sum and the centred sum of squares of n values.
+// Non-finite values or zero contrast are flagged.
+__device__ void pattern_stat(double tot, double ss, int64_t n, PatStat* out)
 {
     // the FP64 sum of finite floats cannot overflow (n < 2^40), so it is finite exactly
     // when every value is
-    double tot = block_sum(pattern_sum(p, n, [](float v) { return (double)v; }), sh);
-    const bool bad = !isfinite(tot);
-    double mean = tot / (double)n;
-    double ss = bad ? 0.0 : pattern_sum(p, n, [mean](float v) {
+    const double mean = tot / (double)n, sd = sqrt(ss / (double)n);
+    PatStat st;
+    st.pad = 0;
+    st.mean = 0.0;
+    st.inv_std = 0.0;
+    if (!isfinite(tot)) {
+        st.flags = EBSD_NONFINITE_INPUT;
+    } else if (!(sd > 1e-12 * (fabs(mean) + 1.0))) {
+        st.flags = EBSD_DEGENERATE_INPUT;
+    } else {
+        st.mean = mean;
+        st.inv_std = 1.0 / sd;
+        st.flags = 0;
+    }
+    *out = st;
+}
+
+// Mean and 1/std of one pattern in FP64 (two passes: mean, then centred sum
+// of squares).
+__device__ void pattern_stats(const float* __restrict__ p, int64_t n, PatStat* out, double* sh)
+{
+    const double tot = block_sum(pattern_sum(p, n, [](float v) { return (double)v; }), sh);
+    const double mean = tot / (double)n;
+    const double ss = !isfinite(tot) ? 0.0 : pattern_sum(p, n, [mean](float v) {
         const double d = (double)v - mean;
         return d * d;
     });
-    double var = block_sum(ss, sh) / (double)n;
-    if (threadIdx.x == 0) {
-        PatStat st;
-        st.pad = 0;
-        if (bad) {
-            st.mean = 0.0;
-            st.inv_std = 0.0;
-            st.flags = EBSD_NONFINITE_INPUT;
-        } else {
-            double sd = sqrt(var);
-            if (!(sd > 1e-12 * (fabs(mean) + 1.0))) {
-                st.mean = 0.0;
-                st.inv_std = 0.0;
-                st.flags = EBSD_DEGENERATE_INPUT;
+    const double sum = block_sum(ss, sh);
+    if (threadIdx.x == 0) pattern_stat(tot, sum, n, out);
+}
+
+// The same sums spread over kChainGroups workgroups per pattern, for calls of a
+// few large patterns (one workgroup streams a pattern at one CU's rate: 132 us
+// per pass at 1244 x 1024).  A pattern's sum is kStatThreads chains, chain t over
+// the vectors t, t + 256, ... in order, then the block's tree; a workgroup takes 16
+// chains: all of its threads load and convert, 64 vectors of each chain at a
+// time, and leave a vector's sum in LDS, from which 16 lanes add each chain in
+// order.  Every addition is pattern_sum's, so the result is the same bit for bit.
+// Needs 16-byte alignment (all chains are scalar without it).
+constexpr int kChainGroups = 16, kChainThreads = 1024, kChainLoads = 2;
+constexpr int kChainBatch = kChainThreads / 16 * kChainLoads;  // vectors per chain and batch
+
+template <class F>
+__device__ double chain_sum(const float* __restrict__ p, int64_t n, int group, double (*buf)[kChainBatch * 16], F f)
+{
+    const int c = threadIdx.x & 15, row = threadIdx.x >> 4, t = group * 16 + c;
+    const int64_t nv = n / 4;
+    const float4* __restrict__ p4 = reinterpret_cast<const float4*>(p);
+    const int64_t vecs = (nv + kStatThreads - 1) / kStatThreads;  // of the longest chain
+    float4 v[kChainLoads];
+    auto at = [&](int64_t base, int u) { return t + kStatThreads * (base + u * (kChainThreads / 16) + row); };
+    auto load = [&](int64_t base) {
+#pragma unroll
+        for (int u = 0; u < kChainLoads; u++)
+            if (at(base, u) < nv) v[u] = p4[at(base, u)];
+    };
+    load(0);
+    double acc = 0.0;
+    int par = 0;
+    for (int64_t base = 0; base < vecs; base += kChainBatch, par ^= 1) {
+#pragma unroll
+        for (int u = 0; u < kChainLoads; u++)
+            if (at(base, u) < nv)
+                buf[par][(u * (kChainThreads / 16) + row) * 16 + c] = f(v[u].x) + f(v[u].y) + f(v[u].z) + f(v[u].w);
+        load(base + kChainBatch);
+        __syncthreads();
+        if (threadIdx.x < 16) {
+            const int64_t left = nv - t - kStatThreads * base;  // vectors of this chain from here on
+            const int m = (int)min((int64_t)kChainBatch, left <= 0 ? 0 : (left + kStatThreads - 1) / kStatThreads);
+            if (m == kChainBatch) {
+#pragma unroll 16
+                for (int k = 0; k < kChainBatch; k++) acc += buf[par][k * 16 + c];
             } else {
-                st.mean = mean;
-                st.inv_std = 1.0 / sd;
-                st.flags = 0;
+                for (int k = 0; k < m; k++) acc += buf[par][k * 16 + c];
             }
         }
-        *out = st;
     }
+    if (threadIdx.x < 16)
+        for (int64_t j = 4 * nv + t; j < n; j += kStatThreads) acc += f(p[j]);
+    return acc;  // chain t, threads 0..15
+}
+
+__device__ inline const float* stat_pattern(const Bucket* __restrict__ bk, int i)
+{
+    if (i < bk->nb) return bk->prefilter ? bk->test_pyr + (int64_t)i * bk->pyr_elems : bk->test_in[i];
+    i -= bk->nb;
+    return bk->prefilter ? bk->ref_pyr + (int64_t)i * bk->pyr_elems : bk->ref_in[i];
+}
+
+// block_sum of the kStatThreads chains at `chain` (all threads).
+__device__ double chain_tree(const double* __restrict__ chain, double* sh)
+{
+    const int t = threadIdx.x;
+    if (t < kStatThreads) sh[t] = chain[t];
+    __syncthreads();
+    for (int s = kStatThreads / 2; s > 0; s >>= 1) {
+        if (t < s) sh[t] += sh[t + s];
+        __syncthreads();
+    }
+    return sh[0];
+}
+
+// CENTRED: the squares around the mean (from the first pass's chains).  chains:
+// [2][patterns][kStatThreads]
+template <bool CENTRED>
+__global__ void __launch_bounds__(kChainThreads)
+    k_stat_chains(const Bucket* __restrict__ bk, double* __restrict__ chains)
+{
+    __shared__ double buf[2][kChainBatch * 16];
+    __shared__ double sh[kStatThreads];
+    const int i = blockIdx.y, npat = gridDim.y;
+    const int64_t n = (int64_t)bk->H * bk->W;
+    const float* p = stat_pattern(bk, i);
+    double* first = chains + (int64_t)i * kStatThreads;
+    double acc;
+    if (!CENTRED) {
+        acc = chain_sum(p, n, blockIdx.x, buf, [](float v) { return (double)v; });
+    } else {
+        const double tot = chain_tree(first, sh);
+        if (!isfinite(tot)) {
+            acc = 0.0;
+        } else {
+            const double mean = tot / (double)n;
+            acc = chain_sum(p, n, blockIdx.x, buf, [mean](float v) {
+                const double d = (double)v - mean;
+                return d * d;
+            });
+        }
+        first += (int64_t)npat * kStatThreads;
+    }
+    if (threadIdx.x < 16) first[blockIdx.x * 16 + threadIdx.x] = acc;
+}
+
+__global__ void __launch_bounds__(kStatThreads) k_stat_finish(const Bucket* __restrict__ bk, const double* __restrict__ chains)
+{
+    __shared__ double sh[kStatThreads];
+    const int i = blockIdx.x;
+    const double* c = chains + (int64_t)i * kStatThreads;
+    const double tot = chain_tree(c, sh);
+    __syncthreads();
+    const double ss = chain_tree(c + (int64_t)gridDim.x * kStatThreads, sh);
+    if (threadIdx.x == 0)
+        pattern_stat(tot, ss, (int64_t)bk->H * bk->W, i < bk->nb ? &bk->test_stat[i] : &bk->ref_stat[i - bk->nb]);
 }
 
 // Statistics of each raw pattern, or of its pre-filtered copy in level 0.
@@ -101,13 +215,8 @@ __global__ void __launch_bounds__(kStatThreads) k_stats(const Bucket* __restrict
 {
     __shared__ double sh[kStatThreads];
     const int i = blockIdx.x;
-    const int64_t n = (int64_t)bk->H * bk->W;
-    if (i < bk->nb)
-        pattern_stats(bk->prefilter ? bk->test_pyr + (int64_t)i * bk->pyr_elems : bk->test_in[i], n,
-                      &bk->test_stat[i], sh);
-    else
-        pattern_stats(bk->prefilter ? bk->ref_pyr + (int64_t)(i - bk->nb) * bk->pyr_elems : bk->ref_in[i - bk->nb],
-                      n, &bk->ref_stat[i - bk->nb], sh);
+    pattern_stats(stat_pattern(bk, i), (int64_t)bk->H * bk->W,
+                  i < bk->nb ? &bk->test_stat[i] : &bk->ref_stat[i - bk->nb], sh);
 }
 
 // Level 0 of every pyramid: (p - mean) / std, zeros for flagged patterns.
@@ -326,28 +435,63 @@ __global__ void k_bg_dynamic(BandIO io, const float* __restrict__ blur)
     }
 }
 
+// The row in LDS with its border replicated kBandMaxR columns out on either
+// side, so a tap is at a fixed offset from the thread's column.
 __global__ void __launch_bounds__(256) k_band_rows(BandIO io, BandTaps tp)
 {
     extern __shared__ float row[];
     const int y = blockIdx.x, p = blockIdx.y, W = io.W;
     const float* __restrict__ src = band_src(io, p) + (int64_t)y * W;
-    for (int x = threadIdx.x; x < W; x += 256) row[x] = src[x];
+    for (int i = threadIdx.x; i < W + 2 * kBandMaxR; i += 256) row[i] = src[clampi(i - kBandMaxR, 0, W - 1)];
     __syncthreads();
     const int64_t HW = (int64_t)io.H * W;
     float* tlo = io.tmp + (2 * (int64_t)p) * HW + (int64_t)y * W;
     float* thi = tlo + HW;
     for (int x = threadIdx.x; x < W; x += 256) {
         if (tp.rlo >= 0) {
+            const float* __restrict__ r = row + x + kBandMaxR - tp.rlo;
             float acc = 0.0f;
-            for (int j = -tp.rlo; j <= tp.rlo; j++) acc += tp.lo[j + tp.rlo] * row[clampi(x + j, 0, W - 1)];
+#pragma unroll 8
+            for (int j = 0; j <= 2 * tp.rlo; j++) acc += tp.lo[j] * r[j];
             tlo[x] = acc;
         }
         if (tp.rhi >= 0) {
+            const float* __restrict__ r = row + x + kBandMaxR - tp.rhi;
             float acc = 0.0f;
-            for (int j = -tp.rhi; j <= tp.rhi; j++) acc += tp.hi[j + tp.rhi] * row[clampi(x + j, 0, W - 1)];
+#pragma unroll 8
+            for (int j = 0; j <= 2 * tp.rhi; j++) acc += tp.hi[j] * r[j];
             thi[x] = acc;
         }
     }
+}
+
+// Column sums of kBandRows consecutive outputs of column x: a row is loaded once
+// and enters every output it is a tap of, so an output's terms come in tap
+// order as in a sum of its own.
+constexpr int kBandRows = 8;
+__device__ inline void band_col(const float* __restrict__ t, int H, int W, int x, int y0, const float* __restrict__ w,
+                                int r, float (&acc)[kBandRows])
+{
+#pragma unroll
+    for (int k = 0; k < kBandRows; k++) acc[k] = 0.0f;
+    auto row = [&](int i) { return t[(int64_t)clampi(y0 - r + i, 0, H - 1) * W + x]; };
+    const int n = 2 * r + 1;  // taps; row i is tap i - k of output k
+    auto part = [&](int i) {  // rows that are not a tap of every output
+        const float v = row(i);
+#pragma unroll
+        for (int k = 0; k < kBandRows; k++)
+            if (i >= k && i - k < n) acc[k] += w[i - k] * v;
+    };
+    const int lead = min(kBandRows - 1, n + kBandRows - 1);
+    int i = 0;
+    for (; i < lead; i++) part(i);
+#pragma unroll 4
+    for (; i < n; i++) {
+        const float v = row(i);
+#pragma unroll
+        for (int k = 0; k < kBandRows; k++) acc[k] += w[i - k] * v;
+    }
+    for (; i < n + kBandRows - 1; i++) part(i);
 }
 
 __global__ void __launch_bounds__(256) k_band_cols(BandIO io, BandTaps tp)
@@ -358,21 +502,20 @@ __global__ void __launch_bounds__(256) k_band_cols(BandIO io, BandTaps tp)
     const float* __restrict__ thi = tlo + HW;
     const float* src = band_src(io, p);  // may be dst (in place): read before the write of each element
     float* dst = band_dst(io, p);
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < HW; t += (int64_t)gridDim.x * blockDim.x) {
-        const int y = (int)(t / W), x = (int)(t - (int64_t)W * (t / W));
-        float v;
+    const int groups = (H + kBandRows - 1) / kBandRows;
+    for (int t = blockIdx.x * 256 + threadIdx.x; t < groups * W; t += gridDim.x * 256) {
+        const int x = t % W, y0 = (t / W) * kBandRows;
+        float lo[kBandRows], hi[kBandRows];
         if (tp.rlo >= 0) {
-            v = 0.0f;
-            for (int j = -tp.rlo; j <= tp.rlo; j++) v += tp.lo[j + tp.rlo] * tlo[(int64_t)clampi(y + j, 0, H - 1) * W + x];
+            band_col(tlo, H, W, x, y0, tp.lo, tp.rlo, lo);
         } else {
-            v = src[t];
+#pragma unroll
+            for (int k = 0; k < kBandRows; k++) lo[k] = src[(int64_t)min(y0 + k, H - 1) * W + x];
         }
-        if (tp.rhi >= 0) {
-            float b = 0.0f;
-            for (int j = -tp.rhi; j <= tp.rhi; j++) b += tp.hi[j + tp.rhi] * thi[(int64_t)clampi(y + j, 0, H - 1) * W + x];
-            v -= b;
-        }
-        dst[t] = v;
+        if (tp.rhi >= 0) band_col(thi, H, W, x, y0, tp.hi, tp.rhi, hi);
+#pragma unroll
+        for (int k = 0; k < kBandRows; k++)
+            if (y0 + k < H) dst[(int64_t)(y0 + k) * W + x] = tp.rhi >= 0 ? lo[k] - hi[k] : lo[k];
     }
 }
 
@@ -537,8 +680,20 @@ inline unsigned grid_for(int64_t n, int per_pattern_max = 1024)
 
 }  // namespace
 
-hipError_t launch_stats(const Bucket* d_bk, int nb, int nref, hipStream_t s)
+int64_t stat_chain_doubles(int npat, int64_t n, bool aligned)
 {
+    return aligned && npat <= 256 && n >= (1 << 17) ? (int64_t)2 * npat * kStatThreads : 0;
+}
+
+hipError_t launch_stats(const Bucket* d_bk, int nb, int nref, double* chains, hipStream_t s)
+{
+    if (chains) {
+        const dim3 grid(kChainGroups, (unsigned)(nb + nref));
+        hipLaunchKernelGGL(k_stat_chains<false>, grid, dim3(kChainThreads), 0, s, d_bk, chains);
+        hipLaunchKernelGGL(k_stat_chains<true>, grid, dim3(kChainThreads), 0, s, d_bk, chains);
+        hipLaunchKernelGGL(k_stat_finish, dim3((unsigned)(nb + nref)), dim3(kStatThreads), 0, s, d_bk, chains);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_stats, dim3(nb + nref), dim3(kStatThreads), 0, s, d_bk);
     return hipGetLastError();
 }
@@ -599,10 +754,15 @@ hipError_t launch_bandpass(const BandIO& io, const BandTaps& tp, hipStream_t s)
     if (io.npat <= 0) return hipSuccess;
     if (io.W > 16384 || io.H > 65535 || io.npat > 65535 || tp.rlo > kBandMaxR || tp.rhi > kBandMaxR)
         return hipErrorInvalidValue;
-    const size_t lds = sizeof(float) * (size_t)io.W;  // <= 64 KiB
+    const size_t lds = sizeof(float) * (size_t)(io.W + 2 * kBandMaxR);  // at most 66304 bytes
+    static std::atomic<uint64_t> attr_done{0};
+    const hipError_t e = ensure_dynamic_lds((const void*)k_band_rows, (int)(sizeof(float) * (16384 + 2 * kBandMaxR)),
+                                            attr_done);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_band_rows, dim3((unsigned)io.H, (unsigned)io.npat), dim3(256), lds, s, io, tp);
-    hipLaunchKernelGGL(k_band_cols, dim3(grid_for((int64_t)io.H * io.W, 256), (unsigned)io.npat), dim3(256), 0, s,
-                       io, tp);
+    hipLaunchKernelGGL(k_band_cols,
+                       dim3(grid_for((int64_t)((io.H + kBandRows - 1) / kBandRows) * io.W, 256), (unsigned)io.npat),
+                       dim3(256), 0, s, io, tp);
     return hipGetLastError();
 }
 
