@@ -121,7 +121,7 @@ int fused_ty_for(const ebsd_handle* h, int lh, int lw, int nb = 1 << 20)
 
 // How a level's iterations are launched.
 struct LevelPlan {
-    enum Kind { Rows, Rows2, Tiles, Points } kind;
+    enum Kind { Rows, Rows2, March, Tiles, Points } kind;
     int rows;        // strip height (0: the 2-D tile kernel of one iteration), or region rows of Tiles
     int per_launch;  // iterations per launch
     int units;       // partial sums per pair and iteration
@@ -144,35 +144,84 @@ int default_fused_ty(int lh, int lw, int nb)
     return 16;
 }
 
-// Region rows (32 or 64) of the tile kernel where it is the faster one for nb
-// levels of lh x lw px, else 0.  Microseconds per iteration, fitted to the
+// Region rows (32 or 64) of the tile kernel for nb levels of lh x lw px (0: no tile
+// kernel at this radius) and the microseconds per iteration, fitted to the
 // measurements at radius 3: n regions of 32 rows take max(2.6, 1.2 + 0.0050 n) (256
 // regions 2.65, 1024 6.4, 4096 20.4), of 64 rows 3.5 up to 256 regions, then
-// 0.7 + 0.0115 n (784 regions 10.8, 6272 71); the row kernels never less than
-// 12.5 (their chain of row steps), else 5.3 us per million pixels (128 pairs
-// of 256 x 256 41.9, 48 pairs 17.8).
-int tile_rows_for(int lh, int lw, int nb, int radius)
+// 0.7 + 0.0115 n (784 regions 10.8, 6272 71).
+int tile_rows_for(int lh, int lw, int nb, int radius, double& us)
 {
     if (!tile_iters(radius)) return 0;
     const double n32 = (double)nb * tile_units(lh, lw, radius, 32), n64 = (double)nb * tile_units(lh, lw, radius, 64);
     const double t32 = std::max(2.6, 1.2 + 0.0050 * n32), t64 = n64 <= 256 ? 3.5 : 0.7 + 0.0115 * n64;
-    const double rows = std::max(12.5, 5.3e-6 * nb * lh * lw);
-    if (std::min(t32, t64) >= rows) return 0;
+    us = std::min(t32, t64);
     return t32 <= t64 ? 32 : 64;
+}
+
+// Strip height of the marching wavefronts for nb levels of lh x lw px, and the
+// microseconds per iteration that it predicts; rows 0: level not supported.  A
+// launch takes `rounds` of the device's wavefront slots, each as long as a
+// strip's row steps.  Four columns per lane: 1024 slots (one per SIMD); a step
+// takes 1.36 us while the batch's level (24 B per pixel) fits the last-level
+// cache, 1.85 us from 400 MB (256 x 256 px: 128 pairs at 36 rows 66.7 us for 49
+// steps, 192 at 64 rows 114 / 77, 256 at 64 rows 142 / 77, 1024 at 256 rows 518 /
+// 273).  Two columns: up to three wavefronts per SIMD, 0.9 / 1.5 / 2.6 us
+// (128 x 128 px: 1024 pairs at 64 rows, two per SIMD, 117 us for 77 steps; at 43
+// rows, three, 158 / 56).
+struct MarchPlan {
+    int rows = 0;
+    double us = 1e30;
+};
+MarchPlan march_plan(int H, int W, int lh, int lw, int nb, int radius)
+{
+    MarchPlan best;
+    const int c = march_cols(lh, lw, radius);
+    if (!c || (c == 4 && (int64_t)H * W % 2)) return best;
+    const double mb = 24e-6 * nb * lh * lw;
+    const double step4 = 1.36 + 0.49 * std::min(1.0, std::max(0.0, (mb - 200.0) / 200.0));
+    const double step2[4] = {0.0, 0.9, 1.5, 2.6};
+    for (int n = 1; (lh + n - 1) / n >= std::min(lh, 16); n++) {
+        const int rows = std::max((lh + n - 1) / n, kMarchMinRows);
+        const int64_t units = (int64_t)nb * march_units(lh, lw, radius, rows), per_simd = (units + 1023) / 1024;
+        const double steps = march_steps(rows, radius);
+        const double t = c == 4 ? per_simd * step4 : per_simd / 3 * step2[3] + step2[per_simd % 3];
+        if (0.5 * t * steps < best.us) {
+            best.us = 0.5 * t * steps;
+            best.rows = rows;
+        }
+        if (rows == kMarchMinRows) break;
+    }
+    return best;
+}
+
+// Microseconds per iteration of the row kernels: 4.5 us per million pixels (rows
+// of up to four wavefronts, two iterations per launch: 128 pairs of 256 x 256
+// 41, 1024 pairs 270) or 5.4 (eight, one iteration: 128 of 512 x 512 178), more
+// by the idle lanes, and at least their chain of row steps.
+double rows_us(int lw, double px)
+{
+    const int lanes = 64 * rows_cpl(lw) * rows_segs(lw, rows_cpl(lw));
+    return std::max(12.5, (rows_cpl(lw) > 4 ? 5.4e-6 : 4.5e-6) * px * lanes / lw);
 }
 
 // A level size the caller set runs as set.  Otherwise, unless ebsd_set_resident
 // turned off running several iterations per launch by rule: without smoothing
-// and tolerance all iterations in one launch; small batches on the tile kernel;
-// else as tuned, and untuned two iterations per launch.
-LevelPlan level_plan(const ebsd_handle* h, int lh, int lw, int nb, int cap)
+// and tolerance all iterations in one launch; else the tile kernel, the marching
+// wavefronts or the row kernels, whichever is predicted to be the fastest, the
+// row kernels as tuned, or untuned two iterations per launch.
+LevelPlan level_plan(const ebsd_handle* h, int H, int W, int lh, int lw, int nb, int cap)
 {
     const auto key = std::make_pair(lh, lw);
     const bool rule = h->resident && !h->forced.count(key);
     if (rule) {
         if (h->radius == 0 && h->p.tol_px == 0.0f) return {LevelPlan::Points, 0, std::max(cap, 1), 0};
-        if (const int rows = tile_rows_for(lh, lw, nb, h->radius))
-            return {LevelPlan::Tiles, rows, tile_iters(h->radius), tile_units(lh, lw, h->radius, rows)};
+        const MarchPlan m = march_plan(H, W, lh, lw, nb, h->radius);
+        const double rows = rows_us(lw, (double)nb * lh * lw);
+        double tiles = 1e30;
+        const int tr = tile_rows_for(lh, lw, nb, h->radius, tiles);
+        if (tiles < std::min(rows, m.us))
+            return {LevelPlan::Tiles, tr, tile_iters(h->radius), tile_units(lh, lw, h->radius, tr)};
+        if (m.us < rows) return {LevelPlan::March, m.rows, 2, march_units(lh, lw, h->radius, m.rows)};
     }
     int fty = fused_ty_for(h, lh, lw, nb);
     const bool tuned = h->strip_ty.count(key) && tuned_applies(h->tuned_nb_strip, lh, lw, nb);
@@ -506,7 +555,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         pe = (pe + 63) / 64 * 64;  // every level 256 B aligned
         max_units = std::max(max_units, demons_units(b.lh[l], b.lw[l], kMinStripTY2));
         if (b.lw[l] > 512) max_units = std::max(max_units, demons_tiles(b.lh[l], b.lw[l]));
-        plan[l] = level_plan(h, b.lh[l], b.lw[l], nb, p.max_iters[l]);
+        plan[l] = level_plan(h, H, W, b.lh[l], b.lw[l], nb, p.max_iters[l]);
         max_units = std::max(max_units, plan[l].units);
     }
     b.pyr_elems = pe;
@@ -795,6 +844,9 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
                 break;
             case LevelPlan::Rows2:
                 EBSD_TRY(launch_demons_iter2(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));
+                break;
+            case LevelPlan::March:
+                EBSD_TRY(launch_demons_march(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));
                 break;
             case LevelPlan::Tiles:
                 EBSD_TRY(launch_demons_tiles(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));

@@ -188,6 +188,39 @@ hipError_t launch_demons_tiles(const Bucket* d_bk, const Bucket& hb, int level, 
 // taps[0] the single tap), fixed iteration count.
 hipError_t launch_demons_points(const Bucket* d_bk, const Bucket& hb, int level, const float* taps, int cap,
                                 hipStream_t s);
+// Launch L of level l runs iterations 2L and 2L + 1 by wavefronts of 64 x
+// march_cols columns (0: level not supported) and `rows` (at least
+// kMarchMinRows) output rows; partial sums and launches as for
+// launch_demons_iter2, one unit per (strip, column segment).
+constexpr int kMarchMinRows = 2 * kMaxRadius + 1;
+int march_cols(int h, int w, int radius);
+int march_units(int h, int w, int radius, int rows);
+// Row steps of a wavefront's strip: its rows, the halo of two iterations and the
+// step between the stages, in whole groups of 2 radius + 1.
+inline int march_steps(int rows, int radius)
+{
+    const int nr = 2 * radius + 1;
+    return (rows + 4 * radius + 1 + nr - 1) / nr * nr;
+}
+hipError_t launch_demons_march(const Bucket* d_bk, const Bucket& hb, int level, int L, const float* taps, int radius,
+                               float tol, int cap, int rows, hipStream_t s);
+// Columns a segment recomputes next to a neighbouring one: two iterations carry a
+// wrong end column 2r + 1 columns inward; a multiple of the lane's columns.
+__host__ __device__ inline int march_halo(int c, int radius) { return (2 * radius + c) / c * c; }
+__host__ __device__ inline int march_segs(int w, int c, int radius)
+{
+    if (c <= 0 || w <= 64 * c) return 1;
+    const int halo = march_halo(c, radius), end = 64 * c - halo, mid = end - halo;
+    return w <= 2 * end ? 2 : 2 + (w - 2 * end + mid - 1) / mid;
+}
+// Columns of segment seg: lanes start at column sx0; columns [ws, we) are written.
+__host__ __device__ inline void march_seg(int seg, int nsegs, int w, int c, int radius, int& sx0, int& ws, int& we)
+{
+    const int halo = march_halo(c, radius), end = 64 * c - halo, mid = end - halo;
+    ws = seg == 0 ? 0 : end + (seg - 1) * mid;
+    sx0 = seg == 0 ? 0 : ws - halo;
+    we = seg == nsegs - 1 ? w : end + seg * mid;
+}
 // *out = number of pairs whose demons state has not recorded a stop (out may
 // be pinned host memory mapped into the device's address space).
 hipError_t launch_count_active(const Bucket* d_bk, int32_t* out, hipStream_t s);

@@ -1,6 +1,6 @@
 """Several demons iterations per launch by rule (2-D tiles for small batches,
-all iterations of a level at once without smoothing) against one iteration
-per launch: fields, iteration counts and status equal bit for bit at the
+marching wavefronts for larger ones, all iterations of a level at once
+without smoothing) against one iteration per launch: fields, iteration counts and status equal bit for bit at the
 sizes where the tiling can go wrong.  Needs an MI355X."""
 import pytest
 import torch
@@ -36,6 +36,25 @@ def test_tiles_equal_single_iterations(E, n, H, W, sigma):
             assert ib[0] < ia[0]
         stops.update(int(v) % 4 for v in a["iters"].flatten() if v < iters)
     print("  stops (iteration mod 4):", sorted(stops))
+
+
+# batches that the marching wavefronts take: two and four columns per lane, lanes
+# past the last column, two and four segments, strips that do not divide the
+# height (the last of a few rows)
+@pytest.mark.parametrize("n,H,W", [(1024, 90, 126), (1000, 66, 128), (200, 110, 132), (128, 128, 256), (160, 100, 260),
+                                   (64, 140, 700)])
+@pytest.mark.parametrize("sigma", [0.7, 1.0])
+def test_marching_wavefronts_equal_single_iterations(E, n, H, W, sigma):
+    from paper_1907_05993_amd import synth as S
+    print("case: marching wavefronts", n, H, W, sigma, flush=True)
+    refs, tests, _ = E.gen_pairs([S.make_spec(83, i, H, W, mis_deg=(0.0, 5.0)) for i in range(n)], labels=False)
+    for iters, tol in ((1, 0.0), (9, 0.0), (12, 0.0), (40, 0.2), (31, 0.05)):
+        a, (ia, _) = call(E, refs, tests, False, iters=(iters,), sigma_px=sigma, tol_px=tol)
+        b, (ib, _) = call(E, refs, tests, True, iters=(iters,), sigma_px=sigma, tol_px=tol)
+        for k in ("field", "iters", "q1"):
+            assert torch.equal(a[k], b[k]), (k, iters, tol)
+        if iters > 4:
+            assert ib[0] < ia[0]
 
 
 @pytest.mark.parametrize("n,H,W", [(1, 40, 37), (2, 65, 513), (1, 70, 1000)])
