@@ -149,7 +149,9 @@ __global__ void __launch_bounds__(NT)
     const int b = lb / ntiles;
     const int tile = lb - b * ntiles;
     const PairState st = bk->state[b];
-    if (st.stop >= 0) return;  // uniform over the block
+    // a stop after k iterations may be written by tile 0 of this launch while this
+    // workgroup's wavefronts read the state: it must not take some of them out
+    if (st.stop >= 0 && st.stop < k) return;  // uniform over the block
     const int h = bk->lh[level], w = bk->lw[level];
     const int64_t npart = (int64_t)bk->nb * bk->max_tiles;
     if (tol > 0.0f && k > 0) {

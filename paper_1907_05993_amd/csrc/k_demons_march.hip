@@ -504,7 +504,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(C == 4 
     const int strip = unit / nsegs, seg = unit - strip * nsegs;
     const PairState st = bk->state[b];
     const int k0 = 2 * L;
-    if (st.stop >= 0 && st.stop != k0 - 1) return;  // uniform
+    if (st.stop >= 0 && st.stop < k0 - 1) return;  // uniform
     const int h = bk->lh[level], w = bk->lw[level];
     const int64_t npart = (int64_t)bk->nb * bk->max_tiles;
     const int64_t pofs = (int64_t)b * bk->max_tiles;

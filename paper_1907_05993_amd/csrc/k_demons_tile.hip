@@ -37,9 +37,10 @@ __global__ void __launch_bounds__(64 * NWV)
     const int b = lb / ntiles, tile = lb - b * ntiles;
     const PairState st = bk->state[b];
     const int k0 = L * K;
-    // a stop inside the previous launch's iterations can only have been written by tile 0
-    // of this launch: the other tiles still owe the recompute below
-    if (st.stop >= 0 && !(st.stop > k0 - K && st.stop < k0)) return;  // uniform
+    // a stop after more than k0 - K iterations can only have been written by tile 0 of
+    // this launch, perhaps between the reads of two wavefronts of this workgroup: all of
+    // them take the decision below from the sums
+    if (st.stop >= 0 && st.stop <= k0 - K) return;  // uniform
     const int h = bk->lh[level], w = bk->lw[level];
     const int64_t npart = (int64_t)bk->nb * bk->max_tiles;
     const int64_t pofs = (int64_t)b * bk->max_tiles;

@@ -76,3 +76,27 @@ def E():
     from paper_1907_05993_amd import ebsd
     ebsd.lib()
     return ebsd
+
+
+# The stop decisions of a launch are taken by every workgroup of a pair, also by
+# those that start (in a later round of the device) after the first one has
+# written the stop: strips of a few rows over several rounds, repeated calls
+@pytest.mark.parametrize("n,H,W", [(257, 519, 519), (900, 135, 150), (700, 66, 128)])
+def test_stops_over_several_rounds(E, n, H, W):
+    from paper_1907_05993_amd import synth as S
+    print("case: stops", n, H, W, flush=True)
+    m = 64
+    refs, tests, _ = E.gen_pairs([S.make_spec(85, i, H, W, mis_deg=(0.0, 8.0)) for i in range(m)], labels=False)
+    refs, tests = (x.repeat(-(-n // m), 1, 1)[:n].contiguous() for x in (refs, tests))
+    p = dict(levels=1, iters=(12,), sigma_px=1.0, tol_px=0.1, roi_size=32, n_roi=5, roi_radius_frac=0.002)
+    one, _ = call(E, refs, tests, False, **{k: v for k, v in p.items() if k in ("iters", "sigma_px", "tol_px")})
+    for ty in (0, 32, 64, 128):
+        reg = E.Registrar(E.Params(**p))
+        if ty:
+            reg.set_fused_height(H, W, ty)
+        for _ in range(6):
+            out = reg.register(refs, tests)
+            torch.cuda.synchronize()
+            assert torch.equal(one["iters"], out["iters"]), ty
+            assert torch.equal(one["field"], out["field"]), ty
+        reg.close()
