@@ -24,33 +24,47 @@
 
 namespace ebsd {
 
-// The value of the next / previous lane; the last / first lane keeps its own.
-__device__ __forceinline__ float lane_next(float v)
+// src of the previous / next lane; `end` in the first / last lane.
+__device__ __forceinline__ float from_prev(float src, float end)
 {
-    const int i = __builtin_bit_cast(int, v);
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, 0x130, 0xf, 0xf, false));  // wave_shl:1
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, end),
+                                                                 __builtin_bit_cast(int, src), 0x138, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float lane_prev(float v)
+__device__ __forceinline__ float from_next(float src, float end)
 {
-    const int i = __builtin_bit_cast(int, v);
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, 0x138, 0xf, 0xf, false));  // wave_shr:1
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, end),
+                                                                 __builtin_bit_cast(int, src), 0x130, 0xf, 0xf, false));
 }
 
-// Horizontal taps of v across the lanes of a wavefront (all lanes active).
+// Horizontal taps of v across the lanes of a wavefront (all lanes active), C
+// consecutive columns per lane, in place; the end columns repeat outside.
+template <int C, int RAD>
+__device__ __forceinline__ void lane_taps(float (&v)[C], const Taps& tp)
+{
+    float e[C + 2 * RAD];
+#pragma unroll
+    for (int c = 0; c < C; c++) e[RAD + c] = v[c];
+#pragma unroll
+    for (int j = 1; j <= RAD; j++) {
+        // the columns j to the left of the first and j to the right of the last: C columns
+        // further in for each lane passed
+        e[RAD - j] = from_prev(j <= C ? v[j <= C ? C - j : 0] : e[RAD - j + C], v[0]);
+        e[RAD + C - 1 + j] = from_next(j <= C ? v[j <= C ? j - 1 : 0] : e[RAD - 1 + j], v[C - 1]);
+    }
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        float a = 0.0f;
+#pragma unroll
+        for (int j = 0; j <= 2 * RAD; j++) a = fmaf(tp.w[j], e[c + j], a);
+        v[c] = a;
+    }
+}
 template <int RAD>
 __device__ __forceinline__ float lane_taps(float v, const Taps& tp)
 {
-    float t[2 * RAD + 1];
-    t[RAD] = v;
-#pragma unroll
-    for (int j = 1; j <= RAD; j++) {
-        t[RAD - j] = lane_prev(t[RAD - j + 1]);
-        t[RAD + j] = lane_next(t[RAD + j - 1]);
-    }
-    float a = 0.0f;
-#pragma unroll
-    for (int j = 0; j <= 2 * RAD; j++) a = fmaf(tp.w[j], t[j], a);
-    return a;
+    float t[1] = {v};
+    lane_taps<1, RAD>(t, tp);
+    return t[0];
 }
 
 // A wavefront's rows of a region: rows y .. y + RPT - 1 of the level at column

@@ -132,42 +132,49 @@ struct LevelPlan {
 // SIMD, else 16.  Measured per iteration, heights 16 / 32 / 64: 128 pairs of
 // 256 x 256 45.8 / 43.9 / 41.9 us (64 rows: 2048 wavefronts), 48 pairs 17.8 /
 // 24.1 / 37.7 (16 rows: 3072); one iteration per launch takes 51.1 and 25.3.
-// 0 (one iteration per launch) for rows of eight wavefronts, whose state allows
-// two wavefronts per SIMD only: 4 pairs of 1244 x 1024 34.0 us with one
-// iteration per launch, 41.8-47.4 with two; 192 pairs of 400 x 400 48.8
-// against 51.7 ms per call.
-int default_fused_ty(int lh, int lw, int nb)
+// 0 (one iteration per launch) where the state of two iterations does not fit the
+// registers: rows of eight wavefronts (4 pairs of 1244 x 1024 34.0 us with one
+// iteration per launch, 41.8-47.4 with two; 192 pairs of 400 x 400 48.8 against
+// 51.7 ms per call) and radius 4 (400 pairs of 160 x 160 73 us with one, 441 with
+// two; 64 pairs of 256 x 256 45 against 81).
+int default_fused_ty(int lh, int lw, int nb, int radius)
 {
-    if (rows_cpl(lw) > 4) return 0;
+    if (rows_cpl(lw) > 4 || radius > 3) return 0;
     for (int ty = 128; ty > 16; ty /= 2)
         if ((int64_t)nb * demons_units(lh, lw, ty) * rows_cpl(lw) >= 2048) return ty;
     return 16;
 }
 
-// Region rows (32 or 64) of the tile kernel for nb levels of lh x lw px (0: no tile
-// kernel at this radius) and the microseconds per iteration, fitted to the
-// measurements at radius 3: n regions of 32 rows take max(2.6, 1.2 + 0.0050 n) (256
-// regions 2.65, 1024 6.4, 4096 20.4), of 64 rows 3.5 up to 256 regions, then
-// 0.7 + 0.0115 n (784 regions 10.8, 6272 71).
+// The microseconds per iteration below are fitted to the times of all kernels on
+// levels of 66 x 78 to 1244 x 1024 px in batches of 1 to 1000 at radius 1 to 4
+// (976 points).  Over radius 2 to 4 the kernel predicted to be the fastest takes
+// 0.5 % more than the fastest one on average and 38 % at worst.
+
+// Region rows (32, 64 or 80) of the tile kernels for nb levels of lh x lw px (0: no
+// tile kernel at this radius).  Regions of 64 and 80 rows (these twice as wide) run
+// in rounds of one per compute unit: at radius 3 64 rows 4.0 us up to 256 regions,
+// 7.1 up to 512, 13 for 1024, 29 for 2560; 80 rows 9.0, 16.6, 31, 78.  Those of 32
+// rows overlap: 256 regions 3.1, 1024 6.9, 4096 22.
 int tile_rows_for(int lh, int lw, int nb, int radius, double& us)
 {
-    if (!tile_iters(radius)) return 0;
-    const double n32 = (double)nb * tile_units(lh, lw, radius, 32), n64 = (double)nb * tile_units(lh, lw, radius, 64);
-    const double t32 = std::max(2.6, 1.2 + 0.0050 * n32), t64 = n64 <= 256 ? 3.5 : 0.7 + 0.0115 * n64;
-    us = std::min(t32, t64);
-    return t32 <= t64 ? 32 : 64;
+    if (!tile_iters(radius, 32)) return 0;
+    const auto regions = [&](int rows) { return (int64_t)nb * tile_units(lh, lw, radius, rows); };
+    const double n32 = (double)regions(32), k64 = (double)((regions(64) + 255) / 256),
+                 k80 = (double)((regions(80) + 255) / 256);
+    const double t32 = radius > 3 ? std::max(3.6, 2.0 + 0.0059 * n32) : std::max(3.0, 1.6 + 0.0052 * n32);
+    const double t64 = radius > 3 ? 1.2 + 3.8 * k64 : 0.9 + 2.9 * k64;
+    const double t80 = 1.2 + 7.6 * k80;
+    us = std::min({t32, t64, t80});
+    return us == t32 ? 32 : us == t64 ? 64 : 80;
 }
 
 // Strip height of the marching wavefronts for nb levels of lh x lw px, and the
 // microseconds per iteration that it predicts; rows 0: level not supported.  A
 // launch takes `rounds` of the device's wavefront slots, each as long as a
 // strip's row steps.  Four columns per lane: 1024 slots (one per SIMD); a step
-// takes 1.36 us while the batch's level (24 B per pixel) fits the last-level
-// cache, 1.85 us from 400 MB (256 x 256 px: 128 pairs at 36 rows 66.7 us for 49
-// steps, 192 at 64 rows 114 / 77, 256 at 64 rows 142 / 77, 1024 at 256 rows 518 /
-// 273).  Two columns: up to three wavefronts per SIMD, 0.9 / 1.5 / 2.6 us
-// (128 x 128 px: 1024 pairs at 64 rows, two per SIMD, 117 us for 77 steps; at 43
-// rows, three, 158 / 56).
+// takes 1.2 us while the batch's level (24 B per pixel) is small against the
+// last-level cache, up to 1.57 from 650 MB.  Two columns: up to three wavefronts
+// per SIMD, 0.93 / 1.25 / 2.2 us at radius 3, one per SIMD 0.77 at 2, 1.2 at 4.
 struct MarchPlan {
     int rows = 0;
     double us = 1e30;
@@ -178,8 +185,8 @@ MarchPlan march_plan(int H, int W, int lh, int lw, int nb, int radius)
     const int c = march_cols(lh, lw, radius);
     if (!c || (c == 4 && (int64_t)H * W % 2)) return best;
     const double mb = 24e-6 * nb * lh * lw;
-    const double step4 = 1.36 + 0.49 * std::min(1.0, std::max(0.0, (mb - 200.0) / 200.0));
-    const double step2[4] = {0.0, 0.9, 1.5, 2.6};
+    const double step4 = 1.2 + 0.37 * std::min(1.0, std::max(0.0, (mb - 350.0) / 300.0));
+    const double step2[4] = {0.0, radius > 3 ? 1.2 : radius == 3 ? 0.93 : 0.77, 1.25, 2.2};
     for (int n = 1; (lh + n - 1) / n >= std::min(lh, 16); n++) {
         const int rows = std::max((lh + n - 1) / n, kMarchMinRows);
         const int64_t units = (int64_t)nb * march_units(lh, lw, radius, rows), per_simd = (units + 1023) / 1024;
@@ -194,14 +201,34 @@ MarchPlan march_plan(int H, int W, int lh, int lw, int nb, int radius)
     return best;
 }
 
-// Microseconds per iteration of the row kernels: 4.5 us per million pixels (rows
-// of up to four wavefronts, two iterations per launch: 128 pairs of 256 x 256
-// 41, 1024 pairs 270) or 5.4 (eight, one iteration: 128 of 512 x 512 178), more
-// by the idle lanes, and at least their chain of row steps.
-double rows_us(int lw, double px)
+// Microseconds per iteration of the row kernels at strip height ty: row steps
+// times the length of a step for `ws` wavefronts per SIMD.  Two iterations per
+// launch (three wavefronts per SIMD at once): 0.98 / 1.09 / 1.2 us, then a
+// microsecond per round of three, and no less than 4.0 us per million pixels (1024
+// pairs of 256 x 256 270 us).  One iteration: 0.57 + 0.09 ws up to four, then
+// 0.27 ws; short strips, in which the fill weighs more, 1.2 to 1.5 times that.
+double rows_us(int lh, int lw, int nb, int radius, int ty, bool two)
 {
-    const int lanes = 64 * rows_cpl(lw) * rows_segs(lw, rows_cpl(lw));
-    return std::max(12.5, (rows_cpl(lw) > 4 ? 5.4e-6 : 4.5e-6) * px * lanes / lw);
+    const int cpl = rows_cpl(lw);
+    const double ws = (double)nb * demons_units(lh, lw, ty) * cpl / 1024.0;
+    if (two) {
+        const double n = std::ceil(ws);
+        const double t = 0.5 * (ty + 4 * radius + 1) * (n <= 3 ? 0.87 + 0.11 * n : std::ceil(n / 3));
+        return std::max(t, 4.0e-6 * nb * lh * lw);
+    }
+    const double step = ws <= 4 ? 0.57 + 0.09 * ws : std::max(1.3, 0.27 * ws);
+    return (std::min(ty, lh) + 2 * radius + 1) * step * (ty >= 64 ? 1.0 : radius > 3 ? 1.5 : 1.2) * (cpl > 4 ? 1.1 : 1.0);
+}
+
+// What `per_launch` iterations per launch cost a pair that stops by the tolerance: it
+// computes on to the end of its launch, (per_launch - 1) / 2 iterations on average,
+// after about 0.5 px / tolerance iterations (257 pairs of 519 x 519 at 0.1 px, where
+// both kernels take 385 us per iteration: the full-resolution level 1.2 ms with two
+// per launch, 2.9 ms with four).
+double late_stop(float tol, int cap, int per_launch)
+{
+    if (!(tol > 0.0f)) return 1.0;
+    return 1.0 + 0.5 * (per_launch - 1) / std::max(1.0, std::min((double)cap, 0.5 / tol));
 }
 
 // A level size the caller set runs as set.  Otherwise, unless ebsd_set_resident
@@ -216,16 +243,20 @@ LevelPlan level_plan(const ebsd_handle* h, int H, int W, int lh, int lw, int nb,
     if (rule) {
         if (h->radius == 0 && h->p.tol_px == 0.0f) return {LevelPlan::Points, 0, std::max(cap, 1), 0};
         const MarchPlan m = march_plan(H, W, lh, lw, nb, h->radius);
-        const double rows = rows_us(lw, (double)nb * lh * lw);
         double tiles = 1e30;
         const int tr = tile_rows_for(lh, lw, nb, h->radius, tiles);
-        if (tiles < std::min(rows, m.us))
-            return {LevelPlan::Tiles, tr, tile_iters(h->radius), tile_units(lh, lw, h->radius, tr)};
-        if (m.us < rows) return {LevelPlan::March, m.rows, 2, march_units(lh, lw, h->radius, m.rows)};
+        const int f = rows_cpl(lw) ? default_fused_ty(lh, lw, nb, h->radius) : 0, ty = strip_ty_for(h, lh, lw, nb);
+        const double rows = rows_us(lh, lw, nb, h->radius, f ? f : ty ? ty : kDefaultStripTY, f > 0);
+        const double tiles_l = tiles * late_stop(h->p.tol_px, cap, tr ? tile_iters(h->radius, tr) : 1);
+        const double march_l = m.us * late_stop(h->p.tol_px, cap, 2);
+        const double rows_l = rows * late_stop(h->p.tol_px, cap, f ? 2 : 1);
+        if (tr && tiles_l < std::min(rows_l, march_l))
+            return {LevelPlan::Tiles, tr, tile_iters(h->radius, tr), tile_units(lh, lw, h->radius, tr)};
+        if (march_l < rows_l) return {LevelPlan::March, m.rows, 2, march_units(lh, lw, h->radius, m.rows)};
     }
     int fty = fused_ty_for(h, lh, lw, nb);
     const bool tuned = h->strip_ty.count(key) && tuned_applies(h->tuned_nb_strip, lh, lw, nb);
-    if (rule && !fty && !tuned && rows_cpl(lw)) fty = default_fused_ty(lh, lw, nb);
+    if (rule && !fty && !tuned && rows_cpl(lw)) fty = default_fused_ty(lh, lw, nb, h->radius);
     if (fty) return {LevelPlan::Rows2, fty, 2, demons_units(lh, lw, fty)};
     const int ty = strip_ty_for(h, lh, lw, nb);
     return {LevelPlan::Rows, ty, 1, demons_units(lh, lw, ty)};

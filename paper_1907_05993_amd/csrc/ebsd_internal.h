@@ -175,12 +175,12 @@ hipError_t launch_demons_iter2(const Bucket* d_bk, const Bucket& hb, int level, 
 bool demons_resident_ok(int h, int w);
 hipError_t launch_demons_resident(const Bucket* d_bk, const Bucket& hb, int level, const float* taps, int radius,
                                   float tol, int cap, hipStream_t s);
-// Launch L of level l runs iterations L K .. L K + K - 1 (K = tile_iters(radius),
-// 0: no tile kernel for this radius) on 2-D tiles cut from regions of 64
-// columns x `rows` (32 or 64) rows; partial sums in slot iteration & 7, one per
+// Launch L of level l runs iterations L K .. L K + K - 1 (K = tile_iters, 0: no
+// tile kernel for this radius) on 2-D tiles cut from regions of 64 columns x
+// `rows` (32 or 64) rows, or of 128 columns x 80 rows (rows = 80); partial sums in slot iteration & 7, one per
 // tile (tile_units).  ceil(cap / K) launches, plus one that only takes the
 // decisions when tol > 0 and the last launch runs more than one iteration.
-int tile_iters(int radius);
+int tile_iters(int radius, int rows);
 int tile_units(int h, int w, int radius, int rows);
 hipError_t launch_demons_tiles(const Bucket* d_bk, const Bucket& hb, int level, int L, const float* taps, int radius,
                                float tol, int cap, int rows, hipStream_t s);

@@ -65,18 +65,6 @@ __device__ __forceinline__ void store_row(__amdgpu_buffer_rsrc_t r, unsigned vof
     else __builtin_amdgcn_raw_buffer_store_b64(t, r, (int)voff, (int)soff, 0);
 }
 
-// src of the previous / next lane; `end` in the first / last lane.
-__device__ __forceinline__ float from_prev(float src, float end)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, end),
-                                                                 __builtin_bit_cast(int, src), 0x138, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float from_next(float src, float end)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, end),
-                                                                 __builtin_bit_cast(int, src), 0x130, 0xf, 0xf, false));
-}
-
 template <int C>
 struct MarchCtx {
     __amdgpu_buffer_rsrc_t R, U, UN;
@@ -146,29 +134,6 @@ __device__ __forceinline__ void march_force(const MarchCtx<C>& k, const MarchSta
             vx[c] = k.virt ? bx : vx[c];
             vy[c] = k.virt ? by : vy[c];
         }
-    }
-}
-
-// Horizontal taps across the lanes, in place.
-template <int C, int RAD>
-__device__ __forceinline__ void march_taps(float (&v)[C], const Taps& tp)
-{
-    float e[C + 2 * RAD];
-#pragma unroll
-    for (int c = 0; c < C; c++) e[RAD + c] = v[c];
-#pragma unroll
-    for (int j = 1; j <= RAD; j++) {
-        // the columns j to the left of the first and j to the right of the last: C columns
-        // further in for each lane passed
-        e[RAD - j] = from_prev(j <= C ? v[j <= C ? C - j : 0] : e[RAD - j + C], v[0]);
-        e[RAD + C - 1 + j] = from_next(j <= C ? v[j <= C ? j - 1 : 0] : e[RAD - 1 + j], v[C - 1]);
-    }
-#pragma unroll
-    for (int c = 0; c < C; c++) {
-        float a = 0.0f;
-#pragma unroll
-        for (int j = 0; j <= 2 * RAD; j++) a = fmaf(tp.w[j], e[c + j], a);
-        v[c] = a;
     }
 }
 
@@ -314,8 +279,8 @@ __device__ __forceinline__ void march_step(const MarchCtx<C>& k, const Taps& tp,
     EBSD_SCHED();
     // taps of row y; past the image the sums are complete
     if (!END || y < k.h) {
-        march_taps<C, RAD>(hx, tp);
-        march_taps<C, RAD>(hy, tp);
+        lane_taps<C, RAD>(hx, tp);
+        lane_taps<C, RAD>(hy, tp);
         march_add<C, RAD, PH, F1>(a, hx, hy, tp);
         if (END && y == k.h - 1) march_bottom<C, RAD, PH>(a, hx, hy, tp);
     }
@@ -357,8 +322,8 @@ __device__ __forceinline__ void march_step(const MarchCtx<C>& k, const Taps& tp,
         k.load_r(j + 2, b.rp);
         EBSD_SCHED();
         if (!END || j < k.h) {
-            march_taps<C, RAD>(hx, tp);
-            march_taps<C, RAD>(hy, tp);
+            lane_taps<C, RAD>(hx, tp);
+            lane_taps<C, RAD>(hy, tp);
             march_add<C, RAD, PH, F2>(b, hx, hy, tp);
             if (END && j == k.h - 1) march_bottom<C, RAD, PH>(b, hx, hy, tp);
         }

@@ -38,6 +38,24 @@ def test_tiles_equal_single_iterations(E, n, H, W, sigma):
     print("  stops (iteration mod 4):", sorted(stops))
 
 
+# batches that the wide regions take without a tolerance (radius 1 the last, 2 and 3
+# the first two, 4 the first and last): one region across with an odd width, several
+# across, a last region of one row or column; with a tolerance the rule goes by it too
+@pytest.mark.parametrize("n,H,W", [(60, 120, 127), (16, 257, 241), (110, 123, 127)])
+@pytest.mark.parametrize("sigma", [0.4, 0.7, 1.0, 1.3])  # radius 1 .. 4
+def test_wide_regions_equal_single_iterations(E, n, H, W, sigma):
+    from paper_1907_05993_amd import synth as S
+    print("case: wide regions", n, H, W, sigma, flush=True)
+    refs, tests, _ = E.gen_pairs([S.make_spec(84, i, H, W, mis_deg=(0.0, 5.0)) for i in range(n)], labels=False)
+    for iters, tol in ((1, 0.0), (9, 0.0), (12, 0.0), (40, 0.1), (7, 0.02), (30, 1e-3)):
+        a, (ia, _) = call(E, refs, tests, False, iters=(iters,), sigma_px=sigma, tol_px=tol)
+        b, (ib, _) = call(E, refs, tests, True, iters=(iters,), sigma_px=sigma, tol_px=tol)
+        for k in ("field", "iters", "q1"):
+            assert torch.equal(a[k], b[k]), (k, iters, tol)
+        if iters > 4 and not tol:
+            assert ib[0] < ia[0]
+
+
 # batches that the marching wavefronts take: two and four columns per lane, lanes
 # past the last column, two and four segments, strips that do not divide the
 # height (the last of a few rows)
