@@ -25,7 +25,9 @@ namespace {
 
 constexpr int kMaxBands = 32;
 constexpr int kGenThreads = 256;
-constexpr int kGenBlocks = 64;  // blocks per pattern
+constexpr int kGenBlocks = 32;  // blocks per pattern
+
+static_assert(kMaxBands <= 32, "band masks of 32 bits");
 
 struct BandTable {
     double n[kMaxBands][3];  // unit plane normals (crystal frame)
@@ -78,62 +80,115 @@ __device__ inline void uniforms2(uint32_t p, uint32_t attempt, uint32_t stream, 
 // cap the rounded mean is returned).
 constexpr int kMaxTries = 64;
 
-__device__ double poisson_sample(double lam, uint32_t p, uint32_t stream, uint32_t k0, uint32_t k1)
+// Constants of PTRS at mean lam >= 10 that its first test needs.
+struct Ptrs {
+    double a, b, vr;
+};
+__device__ inline Ptrs ptrs_of(double lam)
 {
-    if (!(lam > 0.0)) return 0.0;
-    if (lam < 10.0) {
-        double u, v;
-        uniforms2(p, 0u, stream, k0, k1, u, v);
-        double pk = exp(-lam), cdf = pk;
-        int k = 0;
-        while (u > cdf && k < 1000) {
-            k++;
-            pk *= lam / (double)k;
-            cdf += pk;
-        }
-        return (double)k;
+    Ptrs q;
+    q.b = 0.931 + 2.53 * sqrt(lam);
+    q.a = -0.059 + 0.02483 * q.b;
+    q.vr = 0.9277 - 3.6224 / (q.b - 2.0);
+    return q;
+}
+
+// Proposal t of the draw.  Quick: inside the squeeze, which takes no logarithms
+// (86 % of the proposals at mean 100).
+__device__ inline double ptrs_propose(const Ptrs& q, double lam, uint32_t p, uint32_t t, uint32_t stream, uint32_t k0,
+                                      uint32_t k1, double& us, double& v, bool& quick)
+{
+    double u;
+    uniforms2(p, t, stream, k0, k1, u, v);
+    u -= 0.5;
+    us = 0.5 - fabs(u);
+    quick = us >= 0.07 && v <= q.vr;
+    return floor((2.0 * q.a / us + q.b) * u + lam + 0.43);
+}
+
+// log k! of k = 0, 1, ...: the first 16 from a table, then Stirling's series
+// (Abramowitz and Stegun 6.1.41; the term left out is below 1e-16 at k = 16).
+__device__ inline double log_factorial(double k)
+{
+    constexpr double kTab[16] = {0.0,
+                                 0.0,
+                                 0.69314718055994530942,
+                                 1.7917594692280550008,
+                                 3.1780538303479456197,
+                                 4.7874917427820459943,
+                                 6.5792512120101009951,
+                                 8.5251613610654143002,
+                                 10.604602902745250228,
+                                 12.801827480081469611,
+                                 15.104412573075515295,
+                                 17.502307845873885839,
+                                 19.987214495661886150,
+                                 22.552163853123422886,
+                                 25.191221182738681500,
+                                 27.899271383840891566};
+    if (k < 16.0) return kTab[(int)k];
+    const double x = k + 1.0, i = 1.0 / x, i2 = i * i;
+    const double c = i * (1.0 / 12 - i2 * (1.0 / 360 - i2 * (1.0 / 1260 - i2 * (1.0 / 1680 - i2 * (1.0 / 1188 -
+                          i2 * (691.0 / 360360))))));
+    return (x - 0.5) * log(x) - x + 0.91893853320467274178 + c;
+}
+
+// The exact test of a proposal outside the squeeze.
+__device__ inline bool ptrs_accept(const Ptrs& q, double lam, double k, double us, double v)
+{
+    if (k < 0.0 || (us < 0.013 && v > us)) return false;
+    const double invalpha = 1.1239 + 1.1328 / (q.b - 3.4);
+    return log(v) + log(invalpha) - log(q.a / (us * us) + q.b) <= -lam + k * log(lam) - log_factorial(k);
+}
+
+// lam < 10
+__device__ inline double poisson_search(double lam, uint32_t p, uint32_t stream, uint32_t k0, uint32_t k1)
+{
+    double u, v;
+    uniforms2(p, 0u, stream, k0, k1, u, v);
+    double pk = exp(-lam), cdf = pk;
+    int k = 0;
+    while (u > cdf && k < 1000) {
+        k++;
+        pk *= lam / (double)k;
+        cdf += pk;
     }
-    const double slam = sqrt(lam), loglam = log(lam);
-    const double b = 0.931 + 2.53 * slam;
-    const double a = -0.059 + 0.02483 * b;
-    const double invalpha = 1.1239 + 1.1328 / (b - 3.4);
-    const double vr = 0.9277 - 3.6224 / (b - 2.0);
-    for (int t = 0; t < kMaxTries; t++) {
-        double u, v;
-        uniforms2(p, (uint32_t)t, stream, k0, k1, u, v);
-        u -= 0.5;
-        const double us = 0.5 - fabs(u);
-        const double k = floor((2.0 * a / us + b) * u + lam + 0.43);
-        if (us >= 0.07 && v <= vr) return k;
-        if (k < 0.0 || (us < 0.013 && v > us)) continue;
-        if (log(v) + log(invalpha) - log(a / (us * us) + b) <= -lam + k * loglam - lgamma(k + 1.0)) return k;
-    }
-    return floor(lam + 0.5);
+    return (double)k;
 }
 
 // ---- rendering ----------------------------------------------------------------------
 
-__device__ double band_sum(const BandTable& bt, const double* G, double dx, double dy, double dz)
+// Tiles of 16 x 16 px per workgroup, 8 x 8 px per wavefront: a compact wavefront
+// meets few bands.
+constexpr int kGenTile = 16;
+
+// A pattern's bands in the detector frame (LDS).
+struct Bands {
+    double n[kMaxBands][3];
+    double norm[kMaxBands];
+};
+
+__device__ void rotate_bands(const BandTable* __restrict__ bt, const double* G, Bands& s)
 {
-    const double inv = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
-    dx *= inv;
-    dy *= inv;
-    dz *= inv;
-    double acc = 0.0;
-    for (int b = 0; b < bt.count; b++) {
-        const double nx = G[0] * bt.n[b][0] + G[1] * bt.n[b][1] + G[2] * bt.n[b][2];
-        const double ny = G[3] * bt.n[b][0] + G[4] * bt.n[b][1] + G[5] * bt.n[b][2];
-        const double nz = G[6] * bt.n[b][0] + G[7] * bt.n[b][1] + G[8] * bt.n[b][2];
-        const double s = nx * dx + ny * dy + nz * dz;  // sin of the angle to the plane
-        if (fabs(s) <= bt.sin_theta[b]) acc += 0.5 * (1.0 + cos(M_PI * asin(s) / bt.theta[b]));
+    const int b = threadIdx.x;
+    if (b < bt->count) {
+        double q = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            s.n[b][i] = G[3 * i] * bt->n[b][0] + G[3 * i + 1] * bt->n[b][1] + G[3 * i + 2] * bt->n[b][2];
+            q += s.n[b][i] * s.n[b][i];
+        }
+        s.norm[b] = sqrt(q);
     }
-    return acc;
+    __syncthreads();
 }
 
-__device__ double intensity(const BandTable& bt, const GenPair& g, int which, int x, int y, int H, int W,
-                            double xs, double ys, double zs)
+__device__ inline void view_ray(const GenPair& g, int which, double x, double y, double xs, double ys, double zs,
+                                double& rx, double& ry, double& rz)
 {
-    double rx = (double)x - xs, ry = (double)y - ys, rz = zs;
+    rx = x - xs;
+    ry = y - ys;
+    rz = zs;
     if (which) {
         const double tx = g.Finv[0] * rx + g.Finv[1] * ry + g.Finv[2] * rz;
         const double ty = g.Finv[3] * rx + g.Finv[4] * ry + g.Finv[5] * rz;
@@ -142,27 +197,89 @@ __device__ double intensity(const BandTable& bt, const GenPair& g, int which, in
         ry = ty;
         rz = tz;
     }
+}
+
+// The bands (bit mask, uniform over the wavefront) that a pixel of the wavefront's
+// 8 x 8 tile at (x0, y0) can lie in, lane b deciding on band b from the centre ray:
+// over the tile the ray moves by at most d, the unit ray by at most 2 d / |r|, and
+// the sine by that times |n|.  A band is only left out where this is sure.
+__device__ inline uint32_t bands_near(const BandTable* __restrict__ bt, const Bands& s, const GenPair& g, int which,
+                                      int x0, int y0, double xs, double ys, double zs)
+{
+    const int b = threadIdx.x & 63;
+    bool keep = false;
+    if (b < bt->count) {
+        double rx, ry, rz;
+        view_ray(g, which, (double)x0 + 3.5, (double)y0 + 3.5, xs, ys, zs, rx, ry, rz);
+        double d = 3.5 * 1.4143;
+        if (which) {
+            const double c0 = sqrt(g.Finv[0] * g.Finv[0] + g.Finv[3] * g.Finv[3] + g.Finv[6] * g.Finv[6]);
+            const double c1 = sqrt(g.Finv[1] * g.Finv[1] + g.Finv[4] * g.Finv[4] + g.Finv[7] * g.Finv[7]);
+            d = 3.5 * (c0 + c1);
+        }
+        const double r2 = rx * rx + ry * ry + rz * rz, r = sqrt(r2);
+        const double move = 2.0 * d / r;
+        const double sine = (s.n[b][0] * rx + s.n[b][1] * ry + s.n[b][2] * rz) / r;
+        const double margin = s.norm[b] * (move * (1.0 + 1e-9) + 1e-9);
+        // squares far from the limits of the type, here and at every pixel
+        const bool sure = r2 > 1e-100 && r2 < 1e100 && move < 1.0 && s.norm[b] < 1e100;
+        keep = !(sure && fabs(sine) - margin > bt->sin_theta[b]);
+    }
+    return (uint32_t)__ballot(keep);
+}
+
+__device__ double band_sum(const BandTable* __restrict__ bt, const Bands& s, uint32_t near, double dx, double dy,
+                           double dz)
+{
+    const double inv = 1.0 / sqrt(dx * dx + dy * dy + dz * dz);
+    dx *= inv;
+    dy *= inv;
+    dz *= inv;
+    double acc = 0.0;
+    for (; near; near &= near - 1) {
+        const int b = __builtin_ctz(near);
+        const double sine = s.n[b][0] * dx + s.n[b][1] * dy + s.n[b][2] * dz;
+        if (fabs(sine) <= bt->sin_theta[b]) acc += 0.5 * (1.0 + cos(M_PI * asin(sine) / bt->theta[b]));
+    }
+    return acc;
+}
+
+// Intensity of the lane's pixel of tile t (0 outside the pattern); all lanes of the
+// wavefront call it.  p: the pixel's index, -1 outside.
+__device__ inline double tile_intensity(const BandTable* __restrict__ bt, const Bands& s, const GenPair& g, int which,
+                                        int t, int tiles_x, int H, int W, double xs, double ys, double zs, int& p)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ty = t / tiles_x, tx = t - ty * tiles_x;
+    const int x0 = tx * kGenTile + (wave & 1) * 8, y0 = ty * kGenTile + (wave >> 1) * 8;
+    const int x = x0 + (lane & 7), y = y0 + (lane >> 3);
+    p = x < W && y < H ? y * W + x : -1;
+    const uint32_t near = g.bands ? bands_near(bt, s, g, which, x0, y0, xs, ys, zs) : 0u;
+    if (p < 0) return 0.0;
     const double bg =
         1.0 + 0.2 * (g.gx * ((double)x / (double)(W - 1) - 0.5) + g.gy * ((double)y / (double)(H - 1) - 0.5));
-    return g.bands ? bg + 0.5 * band_sum(bt, g.G, rx, ry, rz) : bg;
+    if (!g.bands) return bg;
+    double rx, ry, rz;
+    view_ray(g, which, (double)x, (double)y, xs, ys, zs, rx, ry, rz);
+    return bg + 0.5 * band_sum(bt, s, near, rx, ry, rz);
 }
 
 // Pass 1: per-block partial sums of the unscaled intensity (fixed tree order).
-// blockIdx.y = 2 * pair + (0 reference, 1 test).
+// blockIdx.y = 2 * pair + (0 reference, 1 test).  Bound: FP64 vector ALU.
 __global__ void __launch_bounds__(kGenThreads)
-k_gen_sum(const GenPair* __restrict__ gp, const BandTable* __restrict__ bt_in, int H, int W, double xs, double ys,
-          double zs, double* __restrict__ part)
+k_gen_sum(const GenPair* __restrict__ gp, const BandTable* __restrict__ bt, int H, int W, double xs, double ys,
+          double zs, int tiles_x, int tiles, double* __restrict__ part)
 {
-    __shared__ BandTable bt;
+    __shared__ Bands bands;
     __shared__ double sh[kGenThreads];
-    if (threadIdx.x == 0) bt = *bt_in;
-    __syncthreads();
     const int pat = blockIdx.y;
     const GenPair& g = gp[pat >> 1];
-    const int64_t np = (int64_t)H * W;
+    rotate_bands(bt, g.G, bands);
     double sum = 0.0;
-    for (int64_t p = (int64_t)blockIdx.x * kGenThreads + threadIdx.x; p < np; p += (int64_t)kGenBlocks * kGenThreads)
-        sum += intensity(bt, g, pat & 1, (int)(p % W), (int)(p / W), H, W, xs, ys, zs);
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) {
+        int p;
+        sum += tile_intensity(bt, bands, g, pat & 1, t, tiles_x, H, W, xs, ys, zs, p);
+    }
     sh[threadIdx.x] = sum;
     __syncthreads();
     for (int s = kGenThreads / 2; s > 0; s >>= 1) {
@@ -172,26 +289,104 @@ k_gen_sum(const GenPair* __restrict__ gp, const BandTable* __restrict__ bt_in, i
     if (threadIdx.x == 0) part[(int64_t)pat * kGenBlocks + blockIdx.x] = sh[0];
 }
 
-// Pass 2: scale to the mean count, Poisson noise, fp32 store.
-__global__ void __launch_bounds__(kGenThreads)
-k_gen_write(const GenPair* __restrict__ gp, const BandTable* __restrict__ bt_in, int H, int W, double xs, double ys,
-            double zs, const double* __restrict__ part, float* __restrict__ ref, float* __restrict__ test)
+// Pass 2: scale to the mean count, Poisson noise, fp32 store.  The intensity is
+// computed again (less than the 16 B per pixel that keeping it would move, and no
+// memory for it).  Draws that are not settled by a first quick proposal wait in LDS
+// and are taken 256 at a time, one exact test and one more proposal each, until
+// they are settled: drawn in place, a few lanes held every wavefront for several
+// proposals.  64 pairs of 256 x 256: k_gen_sum 286 -> 115 us (all 25 bands at each
+// pixel before), k_gen_write 746 -> 275 us.
+constexpr int kGenQueue = 2 * kGenThreads;  // at most kGenThreads - 1 wait before a tile
+static_assert(kMaxTries <= 64, "proposal number in the 7 bits above a pixel index of 24");
+__global__ void __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4)))
+k_gen_write(const GenPair* __restrict__ gp, const BandTable* __restrict__ bt, int H, int W, double xs, double ys,
+            double zs, int tiles_x, int tiles, const double* __restrict__ part, float* __restrict__ ref,
+            float* __restrict__ test)
 {
-    __shared__ BandTable bt;
-    if (threadIdx.x == 0) bt = *bt_in;
-    __syncthreads();
+    __shared__ Bands bands;
+    __shared__ double wait_v[kGenQueue];
+    __shared__ uint32_t wait_p[kGenQueue];  // pixel | proposal << 24
+    __shared__ int waiting;
     const int pat = blockIdx.y;
-    const int which = pat & 1;
+    const uint32_t which = pat & 1;
     const GenPair& g = gp[pat >> 1];
+    if (threadIdx.x == 0) waiting = 0;
+    rotate_bands(bt, g.G, bands);
     const int64_t np = (int64_t)H * W;
     double tot = 0.0;
-    for (int b = 0; b < kGenBlocks; b++) tot += part[(int64_t)pat * kGenBlocks + b];
+    for (int b = 0; b < (int)gridDim.x; b++) tot += part[(int64_t)pat * kGenBlocks + b];
     const double scale = g.counts > 0.0 ? g.counts / (tot / (double)np) : 1.0;
     float* dst = (which ? test : ref) + (int64_t)(pat >> 1) * np;
-    for (int64_t p = (int64_t)blockIdx.x * kGenThreads + threadIdx.x; p < np; p += (int64_t)kGenBlocks * kGenThreads) {
-        double v = intensity(bt, g, which, (int)(p % W), (int)(p / W), H, W, xs, ys, zs) * scale;
-        if (g.noise) v = poisson_sample(v, (uint32_t)p, (uint32_t)which, g.key0, g.key1);
-        dst[p] = (float)v;
+    const auto push = [&](bool mine, double v, uint32_t p) {
+        const uint64_t m = __ballot(mine);
+        int at = 0;
+        if ((threadIdx.x & 63) == 0 && m) at = atomicAdd(&waiting, (int)__popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at) + (int)__popcll(m & ((1ull << (threadIdx.x & 63)) - 1));
+        if (mine) {
+            wait_v[at] = v;
+            wait_p[at] = p;
+        }
+    };
+    for (int t = blockIdx.x; t < tiles; t += gridDim.x) {  // uniform over the workgroup
+        int p;
+        double v = tile_intensity(bt, bands, g, (int)which, t, tiles_x, H, W, xs, ys, zs, p) * scale;
+        bool done = true;
+        double k = v;
+        if (g.noise && p >= 0) {
+            k = 0.0;
+            if (v >= 10.0) {
+                double us, r;
+                k = ptrs_propose(ptrs_of(v), v, (uint32_t)p, 0u, which, g.key0, g.key1, us, r, done);
+            } else if (v > 0.0) {
+                done = false;
+            }
+        }
+        if (p >= 0 && done) dst[p] = (float)k;
+        if (!g.noise) continue;
+        push(!done, v, (uint32_t)p);
+        __syncthreads();
+        const bool last = t + (int)gridDim.x >= tiles;
+        for (int n = waiting; n >= kGenThreads || (last && n > 0);) {  // uniform
+            const int i = max(n - kGenThreads, 0) + (int)threadIdx.x;
+            double lam = 0.0;
+            uint32_t e = 0;
+            if (i < n) {
+                lam = wait_v[i];
+                e = wait_p[i];
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) waiting = max(n - kGenThreads, 0);
+            __syncthreads();
+            bool again = false;
+            if (i < n) {
+                const uint32_t q = e & 0xffffffu;
+                double out;
+                if (lam < 10.0) {
+                    out = poisson_search(lam, q, which, g.key0, g.key1);
+                } else {
+                    const Ptrs c = ptrs_of(lam);
+                    uint32_t tr = e >> 24;
+                    double us, r;
+                    bool quick;
+                    out = ptrs_propose(c, lam, q, tr, which, g.key0, g.key1, us, r, quick);
+                    if (!ptrs_accept(c, lam, out, us, r)) {
+                        tr++;
+                        e = q | tr << 24;
+                        if (tr == (uint32_t)kMaxTries) {
+                            out = floor(lam + 0.5);
+                        } else {
+                            out = ptrs_propose(c, lam, q, tr, which, g.key0, g.key1, us, r, quick);
+                            again = !quick;
+                        }
+                    }
+                }
+                if (!again) dst[q] = (float)out;
+            }
+            push(again, lam, e);
+            __syncthreads();
+            n = waiting;
+        }
+        __syncthreads();
     }
 }
 
@@ -286,17 +481,16 @@ extern "C" int ebsd_gen_pairs(const ebsd_gen_spec* specs, int32_t n, int32_t H, 
     if (H < 8 || W < 8 || H > 4096 || W > 4096 || (label && (H % 4 || W % 4))) return EBSD_ESHAPE;
     if (!(pc_z > 0.0) || !std::isfinite(pc_x) || !std::isfinite(pc_y) || !std::isfinite(pc_z)) return EBSD_EINVAL;
     if (n == 0) return EBSD_OK;
-    std::vector<GenPair> hp;
-    BandTable bt;
+    std::vector<char> up;
     try {
-        hp.resize((size_t)n);
-        bt = fcc_bands();
+        up.resize(sizeof(BandTable) + sizeof(GenPair) * (size_t)n);
+        *reinterpret_cast<BandTable*>(up.data()) = fcc_bands();
     } catch (const std::bad_alloc&) {
         return EBSD_ENOMEM;
     }
     for (int i = 0; i < n; i++) {
         const ebsd_gen_spec& s = specs[i];
-        GenPair& g = hp[(size_t)i];
+        GenPair& g = reinterpret_cast<GenPair*>(up.data() + sizeof(BandTable))[i];
         for (int j = 0; j < 9; j++) {
             if (!std::isfinite(s.G[j]) || !std::isfinite(s.F[j])) return EBSD_EINVAL;
             g.G[j] = s.G[j];
@@ -314,27 +508,26 @@ extern "C" int ebsd_gen_pairs(const ebsd_gen_spec* specs, int32_t n, int32_t H, 
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     ebsd::DeviceWideLock lk(ebsd::capture_mutex());  // the buffers' frees wait for the device
-    DevMem dpairs, dbt, dpart;
-    if (hipMalloc(&dpairs.p, sizeof(GenPair) * (size_t)n) != hipSuccess ||
-        hipMalloc(&dbt.p, sizeof(BandTable)) != hipSuccess ||
-        hipMalloc(&dpart.p, sizeof(double) * 2 * (size_t)n * kGenBlocks) != hipSuccess) {
+    // one allocation and one upload: band table, pairs, partial sums
+    const size_t up_bytes = sizeof(BandTable) + sizeof(GenPair) * (size_t)n;
+    DevMem mem;
+    if (hipMalloc(&mem.p, up_bytes + sizeof(double) * 2 * (size_t)n * kGenBlocks) != hipSuccess) {
         (void)hipGetLastError();
         return EBSD_ENOMEM;
     }
-    if (hipMemcpyAsync(dpairs.p, hp.data(), sizeof(GenPair) * (size_t)n, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(dbt.p, &bt, sizeof(BandTable), hipMemcpyHostToDevice, st) != hipSuccess)
-        return EBSD_EDEVICE;
+    if (hipMemcpyAsync(mem.p, up.data(), up_bytes, hipMemcpyHostToDevice, st) != hipSuccess) return EBSD_EDEVICE;
     const double xs = pc_x * W - 0.5, ys = pc_y * H - 0.5, zs = pc_z * W;
-    const GenPair* gp = static_cast<const GenPair*>(dpairs.p);
-    const BandTable* btp = static_cast<const BandTable*>(dbt.p);
-    double* part = static_cast<double*>(dpart.p);
+    const BandTable* btp = static_cast<const BandTable*>(mem.p);
+    const GenPair* gp = reinterpret_cast<const GenPair*>(btp + 1);
+    double* part = reinterpret_cast<double*>(static_cast<char*>(mem.p) + up_bytes);
+    const int tiles_x = (W + kGenTile - 1) / kGenTile, tiles = tiles_x * ((H + kGenTile - 1) / kGenTile);
     for (int c0 = 0; c0 < n; c0 += 16384) {  // 2 patterns per pair on grid.y (<= 65535)
         const int cnt = std::min(16384, n - c0);
-        const dim3 grid(kGenBlocks, 2 * cnt);
+        const dim3 grid(std::min(kGenBlocks, tiles), 2 * cnt);
         hipLaunchKernelGGL(k_gen_sum, grid, dim3(kGenThreads), 0, st, gp + c0, btp, H, W, xs, ys, zs,
-                           part + (size_t)2 * c0 * kGenBlocks);
+                           tiles_x, tiles, part + (size_t)2 * c0 * kGenBlocks);
         hipLaunchKernelGGL(k_gen_write, grid, dim3(kGenThreads), 0, st, gp + c0, btp, H, W, xs, ys, zs,
-                           part + (size_t)2 * c0 * kGenBlocks, ref + (int64_t)c0 * H * W, test + (int64_t)c0 * H * W);
+                           tiles_x, tiles, part + (size_t)2 * c0 * kGenBlocks, ref + (int64_t)c0 * H * W, test + (int64_t)c0 * H * W);
         if (label) {
             const int ng = (H / 4) * (W / 4);
             hipLaunchKernelGGL(k_gen_labels, dim3((ng + 255) / 256, cnt), dim3(256), 0, st, gp + c0, H, W, xs, ys, zs,

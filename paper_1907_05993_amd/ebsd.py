@@ -16,6 +16,7 @@ import ctypes as C
 import os
 from dataclasses import dataclass, field
 
+import numpy as np
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -66,6 +67,9 @@ class CParams(C.Structure):
 class CGenSpec(C.Structure):
     _fields_ = [("G", C.c_double * 9), ("F", C.c_double * 9), ("gx", C.c_double), ("gy", C.c_double),
                 ("counts", C.c_double), ("key", C.c_uint32 * 2), ("noise", C.c_int32), ("bands", C.c_int32)]
+
+
+_GEN_SPEC = np.dtype(CGenSpec)
 
 
 class CPair(C.Structure):
@@ -881,24 +885,23 @@ def gen_pairs(specs, labels=True, device=0):
     if n == 0:
         raise ValueError("no specs")
     H, W, pc = specs[0].H, specs[0].W, tuple(specs[0].pc)
-    arr = (CGenSpec * n)()
-    for i, s in enumerate(specs):
+    for s in specs:
         if (s.H, s.W, tuple(s.pc)) != (H, W, pc) or s.bands != "basic":
             raise ValueError("all specs need the same size, pattern centre and the basic band set")
-        G = [float(v) for v in list(s.G.ravel())]
-        F = [float(v) for v in list(s.F.ravel())]
-        for j in range(9):
-            arr[i].G[j] = G[j]
-            arr[i].F[j] = F[j]
-        arr[i].gx, arr[i].gy = float(s.gxy[0]), float(s.gxy[1])
-        arr[i].counts = float(s.counts)
-        arr[i].key[0], arr[i].key[1] = int(s.seeds[0]) & 0xFFFFFFFF, int(s.seeds[1]) & 0xFFFFFFFF
-        arr[i].noise = int(bool(s.noise))
-        arr[i].bands = 1
+    # filled column by column (64 specs: 80 us, 530 field by field)
+    rec = np.zeros(n, _GEN_SPEC)
+    rec["G"] = np.array([s.G for s in specs], np.float64).reshape(n, 9)
+    rec["F"] = np.array([s.F for s in specs], np.float64).reshape(n, 9)
+    rec["gx"] = [s.gxy[0] for s in specs]
+    rec["gy"] = [s.gxy[1] for s in specs]
+    rec["counts"] = [s.counts for s in specs]
+    rec["key"] = [[int(s.seeds[0]) & 0xFFFFFFFF, int(s.seeds[1]) & 0xFFFFFFFF] for s in specs]
+    rec["noise"] = [bool(s.noise) for s in specs]
+    rec["bands"] = 1
     dev = torch.device("cuda", device)
     ref = torch.empty(n, H, W, dtype=torch.float32, device=dev)
     test = torch.empty(n, H, W, dtype=torch.float32, device=dev)
     label = torch.empty(n, H // 4, W // 4, 2, dtype=torch.float32, device=dev) if labels else None
-    _check(lib().ebsd_gen_pairs(arr, n, H, W, pc[0], pc[1], pc[2], _ptr(ref), _ptr(test), _ptr(label),
+    _check(lib().ebsd_gen_pairs(rec.ctypes.data_as(C.POINTER(CGenSpec)), n, H, W, pc[0], pc[1], pc[2], _ptr(ref), _ptr(test), _ptr(label),
                                 _stream()), "ebsd_gen_pairs")
     return ref, test, label

@@ -147,3 +147,30 @@ def test_generation_speed(E):
     torch.cuda.synchronize()
     dt = time.perf_counter() - t
     print("generated 1024 pairs of 256^2 with labels in %.3f s (%.0f pairs/s)" % (dt, 1024 / dt))
+
+
+# tiles cut by the pattern's edges (one of 16 px at 8 px; bands left out per 8 x 8 px),
+# and more tiles than workgroups of a pattern; bars of the cases above
+@pytest.mark.parametrize("H,W", [(8, 8), (9, 17), (33, 40), (108, 500)])
+def test_ragged_sizes(E, H, W):
+    from paper_1907_05993_amd import synth as S
+    print(f"case: gen ragged {H}x{W}", flush=True)
+    specs = specs_for(3, H, W, cid=52)
+    ref, test, _ = E.gen_pairs(specs, labels=False)
+    for i, s in enumerate(specs):
+        for g, c in zip((ref[i].cpu().numpy(), test[i].cpu().numpy()), S.render_pair(s)):
+            assert (np.abs(g.astype(np.float64) - c) / np.spacing(np.abs(c).astype(np.float32))).max() <= 2.0
+
+
+# every draw waits (mean below 10), most are quick, and a mean between
+@pytest.mark.parametrize("lam", [2.0, 10.5, 150.0])
+def test_draws_over_many_tiles(E, lam):
+    from paper_1907_05993_amd import synth as S
+    print(f"case: gen draws lam={lam}", flush=True)
+    H, W = 100, 300  # 133 tiles of 16 x 16 px
+    s = S.PairSpec(H=H, W=W, G=np.eye(3), F=np.eye(3), gxy=(0.0, 0.0), counts=lam, noise=True, seeds=(13, 7))
+    ref, test = gen_flat(E, [s])
+    at = np.random.default_rng(3).choice(H * W, 4000, replace=False)
+    for img, stream in ((ref, 0), (test, 1)):
+        exp = np.array([P.poisson(lam, int(p), stream, s.seeds) for p in at])
+        assert int((img[0].ravel()[at] != exp).sum()) <= 4  # 1 in 1000, as above
