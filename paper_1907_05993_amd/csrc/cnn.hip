@@ -165,7 +165,7 @@ bool alloc_backward(ebsd_cnn* c)
     const int64_t bp = (int64_t)mask_blocks(n * px(256), 32) * 32;
     c->part2_floats = 1600000 + 128 * n;
     bool ok = dalloc(c, &c->grads, kNumParams) && dalloc(c, &c->adam_m, kNumParams) &&
-              dalloc(c, &c->adam_v, kNumParams) && dalloc(c, &c->gA, g) && dalloc(c, &c->gB, g) &&
+              dalloc(c, &c->adam_v, kNumParams) && dalloc(c, &c->gA, g) && dalloc(c, &c->gB, n * px(64) * 128) &&
               dalloc(c, &c->gC, n * px(64) * 128) && dalloc(c, &c->dz, g) &&
               dalloc(c, &c->part, wgrad_part_floats(c->max_batch)) &&
               dalloc(c, &c->bpart, bp > (int64_t)head_blocks(n * px(64)) * 258 ? bp
@@ -269,11 +269,12 @@ hipError_t forward(ebsd_cnn* c, int n, int H, int W, float* out, hipStream_t s, 
     return e;
 }
 
-// Gradient through layer l given the fp32 gradient g of its output activation
-// act (channel stride act_cs, offset act_co): bias and weight gradients into
+// Gradient through layer l given the source of the fp32 gradient of its output
+// activation act (channel stride act_cs, offset act_co): bias and weight gradients into
 // c->grads and, if gin != NULL, the fp32 gradient of its input.
-hipError_t layer_back(ebsd_cnn* c, int l, int n, int H0, int W0, const float* g, const bf16_t* act,
-                      int act_cs, int act_co, const bf16_t* x, float* gin, hipStream_t s)
+template <class Src>
+hipError_t layer_back(ebsd_cnn* c, int l, int n, int H0, int W0, const Src& g, const bf16_t* act, int act_cs,
+                      int act_co, const bf16_t* x, float* gin, hipStream_t s)
 {
     const LayerDef& d = kLayers[l];
     const int H = H0 >> d.lvl, W = W0 >> d.lvl;
@@ -320,22 +321,23 @@ hipError_t backward(ebsd_cnn* c, int n, int H, int W, const float* gout, hipStre
 {
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
     const int64_t P2 = (int64_t)n * H2 * W2;
-    hipError_t e = launch_head_back(c->a6, gout, P2, kHeadC, c->params + c->off_hw, c->gA, c->bpart, s);
+    hipError_t e = launch_head_back(c->a6, gout, P2, kHeadC, c->bpart, s);
     CK(launch_colsum(c->bpart, head_blocks(P2), 2 * kHeadC + 2, c->grads + c->off_hw, c->part2, c->part2_floats, s));
-    CK(layer_back(c, 9, n, H, W, c->gA, c->a6, 128, 0, c->a5, c->gB, s));         // d2 -> g(a5)
-    CK(layer_back(c, 8, n, H, W, c->gB, c->a5, 128, 0, c->cat, c->gA, s));        // d1 -> g(cat)
-    CK(launch_upsample_back(c->gA, n, H3, W3, 256, kCatC, c->gB, s));             // g(e4)
-    CK(layer_back(c, 7, n, H, W, c->gB, c->e4, 256, 0, c->a4a, c->gC, s));        // c4b -> g(a4a)
-    CK(layer_back(c, 6, n, H, W, c->gC, c->a4a, 256, 0, c->p3, c->gB, s));        // c4a -> g(p3)
-    CK(launch_maxpool_back(c->gB, c->cat, n, H2, W2, 128, kCatC, 256, c->gA, kCatC, 256, c->gC, s));  // g(e3)
-    CK(layer_back(c, 5, n, H, W, c->gC, c->cat, kCatC, 256, c->a3a, c->gA, s));   // c3b -> g(a3a)
-    CK(layer_back(c, 4, n, H, W, c->gA, c->a3a, 128, 0, c->p2, c->gB, s));        // c3a -> g(p2)
-    CK(launch_maxpool_back(c->gB, c->e2, n, H1, W1, 64, 64, 0, nullptr, 0, 0, c->gA, s));  // g(e2)
-    CK(layer_back(c, 3, n, H, W, c->gA, c->e2, 64, 0, c->a2a, c->gB, s));         // c2b -> g(a2a)
-    CK(layer_back(c, 2, n, H, W, c->gB, c->a2a, 64, 0, c->p1, c->gA, s));         // c2a -> g(p1)
-    CK(launch_maxpool_back(c->gA, c->e1, n, H, W, 32, 32, 0, nullptr, 0, 0, c->gB, s));  // g(e1)
-    CK(layer_back(c, 1, n, H, W, c->gB, c->e1, 32, 0, c->a1a, c->gA, s));         // c1b -> g(a1a)
-    CK(layer_back(c, 0, n, H, W, c->gA, c->a1a, 32, 0, c->x0, nullptr, s));       // c1a
+    const HeadGrad head{gout, c->params + c->off_hw};
+    CK(layer_back(c, 9, n, H, W, head, c->a6, 128, 0, c->a5, c->gB, s));                    // d2 -> g(a5)
+    CK(layer_back(c, 8, n, H, W, PlainGrad{c->gB}, c->a5, 128, 0, c->cat, c->gA, s));       // d1 -> g(cat)
+    const UpsampledGrad up{c->gA, H3, W3, kCatC};                                           // g(e4)
+    CK(layer_back(c, 7, n, H, W, up, c->e4, 256, 0, c->a4a, c->gC, s));                     // c4b -> g(a4a)
+    CK(layer_back(c, 6, n, H, W, PlainGrad{c->gC}, c->a4a, 256, 0, c->p3, c->gB, s));       // c4a -> g(p3)
+    const PooledGrad p3{c->gB, c->cat, H2, W2, kCatC, 256, c->gA, kCatC, 256};              // g(e3)
+    CK(layer_back(c, 5, n, H, W, p3, c->cat, kCatC, 256, c->a3a, c->gC, s));                // c3b -> g(a3a)
+    CK(layer_back(c, 4, n, H, W, PlainGrad{c->gC}, c->a3a, 128, 0, c->p2, c->gB, s));       // c3a -> g(p2)
+    const PooledGrad p2{c->gB, c->e2, H1, W1, 64, 0, nullptr, 0, 0};                        // g(e2)
+    CK(layer_back(c, 3, n, H, W, p2, c->e2, 64, 0, c->a2a, c->gA, s));                      // c2b -> g(a2a)
+    CK(layer_back(c, 2, n, H, W, PlainGrad{c->gA}, c->a2a, 64, 0, c->p1, c->gB, s));        // c2a -> g(p1)
+    const PooledGrad p1{c->gB, c->e1, H, W, 32, 0, nullptr, 0, 0};                          // g(e1)
+    CK(layer_back(c, 1, n, H, W, p1, c->e1, 32, 0, c->a1a, c->gA, s));                      // c1b -> g(a1a)
+    CK(layer_back(c, 0, n, H, W, PlainGrad{c->gA}, c->a1a, 32, 0, c->x0, nullptr, s));      // c1a
     return e;
 }
 #undef CK

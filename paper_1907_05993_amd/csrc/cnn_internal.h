@@ -83,22 +83,37 @@ hipError_t launch_pack_input_up2(const float* ref_base, int64_t ref_stride, cons
 // 2x2 max pooling of bf16 [n][H][W][cs] (channels [co, co + C)) -> [n][H/2][W/2][C].
 hipError_t launch_maxpool(const bf16_t* in, int n, int H, int W, int C, int cs, int co, bf16_t* out,
                           hipStream_t s);
-// Gradient through the pooling: g_in[p][c] = (first maximum of p's window ? g[p/2][c] : 0)
-// (+ add[p * add_cs + add_co + c] when add != NULL).  fp32.
-hipError_t launch_maxpool_back(const float* g, const bf16_t* act, int n, int H, int W, int C, int cs,
-                               int co, const float* add, int add_cs, int add_co, float* g_in,
-                               hipStream_t s);
 // Nearest 2x upsampling of bf16 [n][h][w][C] into channels [0, C) of [n][2h][2w][cs].
 hipError_t launch_upsample_into(const bf16_t* in, int n, int h, int w, int C, bf16_t* out, int cs,
                                 hipStream_t s);
-// Gradient of the upsampling: g[n][h][w][c] = sum of the 4 copies in gout[n][2h][2w][cs] channel c.
-hipError_t launch_upsample_back(const float* gout, int n, int h, int w, int C, int cs, float* g,
-                                hipStream_t s);
+// Where the fp32 gradient g[p][c] of an activation [n][H][W][C] comes from.
+struct PlainGrad {
+    const float* g;  // [P][C]
+};
+// Through 2x2 max pooling: g[p/2][c] at the first maximum of p's window, 0 elsewhere
+// (+ add[p * add_cs + add_co + c] when add != NULL); act as launch_mask_round takes it.
+struct PooledGrad {
+    const float* g;
+    const bf16_t* act;
+    int H, W, act_cs, act_co;
+    const float* add;
+    int add_cs, add_co;
+};
+// Through nearest 2x upsampling: the sum of the 4 copies in g[n][2H][2W][cs], channel c.
+struct UpsampledGrad {
+    const float* g;
+    int H, W, cs;
+};
+// Through the head: sum_o gout[p][o] hw[c][o].
+struct HeadGrad {
+    const float *gout, *hw;
+};
 // dz = g * (act > 0) rounded to bf16; per-block partial bias sums of the fp32
 // dz (mask_blocks(P, C) rows of C).  C in {32, 64, 128, 256}.
 int mask_blocks(int64_t P, int C);
-hipError_t launch_mask_round(const float* g, const bf16_t* act, int64_t P, int C, int act_cs,
-                             int act_co, bf16_t* dz, float* bias_part, hipStream_t s);
+template <class Src>
+hipError_t launch_mask_round(const Src& src, const bf16_t* act, int64_t P, int C, int act_cs, int act_co, bf16_t* dz,
+                             float* bias_part, hipStream_t s);
 // 1x1 head: out[p][o] = sum_c act[p][c] * hw[c][o] + hb[o], o < 2, fp32.
 hipError_t launch_head_fwd(const bf16_t* act, int64_t P, int C, const float* hw, const float* hb,
                            float* out, hipStream_t s);
@@ -106,11 +121,10 @@ hipError_t launch_head_fwd(const bf16_t* act, int64_t P, int C, const float* hw,
 int loss_blocks(int64_t P);
 hipError_t launch_loss(const float* out, const float* label, int64_t P, float* gout, float* loss_part,
                        hipStream_t s);
-// Head backward: gact[p][c] = sum_o gout[p][o] hw[c][o]; per-block partials of
-// dhw[c][o] = sum_p act[p][c] gout[p][o] and dhb[o] = sum_p gout[p][o].
+// Head backward: per-block partials of dhw[c][o] = sum_p act[p][c] gout[p][o] and
+// dhb[o] = sum_p gout[p][o].
 int head_blocks(int64_t P);
-hipError_t launch_head_back(const bf16_t* act, const float* gout, int64_t P, int C, const float* hw,
-                            float* gact, float* part, hipStream_t s);
+hipError_t launch_head_back(const bf16_t* act, const float* gout, int64_t P, int C, float* part, hipStream_t s);
 // Weight packing from fp32 HWIO masters [3][3][cin][cout]:
 // fwd[co][t][ci] (ci < cin_pad, zero beyond cin) and, if dgr != NULL, the
 // flipped transpose dgr[ci][t][co] = w[8 - t][ci][co].

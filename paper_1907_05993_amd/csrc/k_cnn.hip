@@ -814,25 +814,49 @@ k_conv_stem(const bf16_t* __restrict__ x0, const bf16_t* __restrict__ w1a, const
 
 // ---- 3x3 weight gradient -------------------------------------------------------
 //
-// Workgroup: 3 waves; wave w owns the three taps of kernel row ky = w for a
-// block of 32 input channels x (32 NT) output channels.  GEMM view per tap:
-// M = input channel, N = output channel, K = pixel.  A k-step takes 16 pixels
-// of one output row (8 per half wave); the three taps of a wave read the input
-// at 10 consecutive halo columns, shared between them.  The workgroup walks a
-// contiguous range of 4 x 32 pixel tiles and writes its fp32 partial sums.
+// Workgroup: 3 NT waves for a block of 32 input channels x (32 NT) output
+// channels; wave 3 j + w owns the three taps of kernel row ky = w for 32 of the
+// output channels.  GEMM view per tap: M = input channel, N = output channel, K =
+// pixel.  A k-step takes 16 pixels of one output row (8 per half wave); the three
+// taps of a wave read the input at 10 consecutive halo columns, shared between
+// them.  The workgroup walks a contiguous range of 4 x 32 pixel tiles and writes
+// its fp32 partial sums.
+//
+// Both operands want 8 pixels of one channel per lane, and the tile holds the
+// channels of a pixel side by side: transposed 8-byte LDS reads give 4 pixels each
+// (5 reads per k-step of 3 MFMA; with reads of 2 bytes 18, and their packing).
+// The next tile is on its way into registers while this one is multiplied, and
+// the blocks of one range of tiles share an XCD's L2.  64 pairs of 256 x 256, all ten
+// layers 2.58 -> 1.0 ms; 384 to 128 channels at 64 x 64 px 658 -> 268 us (863 TFLOP/s).
+// The layers of 32 channels are bound by memory (118 us, 536 MB).
 constexpr int kWgTH = 4, kWgTW = 32, kWgCB = 32, kWgThreads = 192;
 
-template <int NT>
-__global__ void __launch_bounds__(kWgThreads) k_wgrad3x3(WgradArgs a)
+__device__ inline uint2 lds_read_tr16(const bf16_t* p)
 {
-    constexpr int HP = kWgTH + 2, WP = kWgTW + 2;
-    constexpr int BN = 32 * NT;
-    __shared__ __attribute__((aligned(16))) bf16_t sX[HP * WP * kWgCB];
-    __shared__ __attribute__((aligned(16))) bf16_t sD[kWgTH * kWgTW * BN];
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                         (__attribute__((address_space(3))) s16x4*)p));
+}
+__device__ inline bf16x8 frag(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    return __builtin_bit_cast(bf16x8, make_uint4(a, b, c, d));
+}
+
+template <int NT>
+__global__ void __launch_bounds__(NT* kWgThreads) k_wgrad3x3(WgradArgs a)
+{
+    constexpr int HP = kWgTH + 2, WP = kWgTW + 2, T = NT * kWgThreads;
+    constexpr int BN = 32 * NT, NX = (HP * WP * 4 + T - 1) / T, ND = (kWgTH * kWgTW * (BN / 8) + T - 1) / T;
+    // the last two pixels are read past the halo (into the 12-pixel window) and not used
+    __shared__ __attribute__((aligned(16))) bf16_t sX[(HP * WP + 2) * kWgCB];
+    // pixel stride 64 or 192 B: the four pixels of a transposed read on different banks
+    constexpr int DS = NT == 2 ? 96 : 32;
+    __shared__ __attribute__((aligned(16))) bf16_t sD[kWgTH * kWgTW * DS];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int ky = wave % 3, jn = wave / 3;
     const int h = lane >> 5, l32 = lane & 31;
-    int b = blockIdx.x;
+    int b = xcd_logical_block(blockIdx.x, gridDim.x);
     const int ncb = (a.Cin + kWgCB - 1) / kWgCB, nob = a.Cout / BN;
     const int ob = b % nob;
     b /= nob;
@@ -844,65 +868,101 @@ __global__ void __launch_bounds__(kWgThreads) k_wgrad3x3(WgradArgs a)
     const int t_begin = split * a.tiles_per_split;
     const int t_end = min(total, t_begin + a.tiles_per_split);
     const int cvec = min(kWgCB, a.Cin - ci0) / 8;
+    // lane i of 16 reads 4 channels of pixel i / 4 and receives channel i of 4 pixels
+    const int i16 = lane & 15, ch = 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
+    const int tr_x = (i16 >> 2) * kWgCB + ch, tr_d = (i16 >> 2) * DS + ch + 32 * jn;
 
-    f32x16 acc[3][NT];
+    f32x16 acc[3];
+#pragma unroll
     for (int k = 0; k < 3; k++)
-        for (int j = 0; j < NT; j++)
-            for (int i = 0; i < 16; i++) acc[k][j][i] = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; i++) acc[k][i] = 0.0f;
 
-    for (int tile = t_begin; tile < t_end; tile++) {
+    // element offsets of this thread's pieces from the tile's origin, and for each piece of
+    // the halo 5 bits: outside where the tile touches the top, bottom, left, right; never read
+    int ox[NX], od[ND];
+    uint32_t out = 0;
+    static_assert(5 * NX <= 32, "halo bits");
+#pragma unroll
+    for (int k = 0; k < NX; k++) {
+        const int i = tid + k * T, g = i & 3, p = i >> 2, hx = p % WP, hy = p / WP;
+        ox[k] = ((hy - 1) * a.W + hx - 1) * a.Cin + 8 * g;
+        const uint32_t e = (hy == 0 ? 1u : 0u) | (hy == HP - 1 ? 2u : 0u) | (hx == 0 ? 4u : 0u) |
+                           (hx == WP - 1 ? 8u : 0u) | (i < HP * WP * 4 && g < cvec ? 0u : 16u);
+        out |= e << (5 * k);
+    }
+#pragma unroll
+    for (int k = 0; k < ND; k++) {
+        const int i = min(tid + k * T, kWgTH * kWgTW * (BN / 8) - 1), g = i % (BN / 8), p = i / (BN / 8);
+        od[k] = ((p / kWgTW) * a.W + p % kWgTW) * a.Cout + 8 * g;
+    }
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 vx[NX], vd[ND];  // a tile on its way into LDS
+    const auto fetch = [&](int tile) {
         const int img = tile / tpi, rem = tile - tpi * img;
         const int y0 = (rem / txn) * kWgTH, x0 = (rem - txn * (rem / txn)) * kWgTW;
-        const bf16_t* __restrict__ xin = a.x + (int64_t)img * a.H * a.W * a.Cin;
-        const bf16_t* __restrict__ din = a.dz + (int64_t)img * a.H * a.W * a.Cout;
-        for (int i = tid; i < HP * WP * 4; i += kWgThreads) {
-            const int g = i & 3, p = i >> 2;
-            const int hx = p % WP, hy = p / WP;
-            const int yy = y0 + hy - 1, xx = x0 + hx - 1;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (g < cvec && yy >= 0 && yy < a.H && xx >= 0 && xx < a.W)
-                v = *reinterpret_cast<const uint4*>(xin + ((int64_t)yy * a.W + xx) * a.Cin + ci0 + 8 * g);
-            *reinterpret_cast<uint4*>(sX + p * kWgCB + 8 * g) = v;
+        const int64_t px0 = ((int64_t)img * a.H + y0) * a.W + x0;
+        const bf16_t* __restrict__ xin = a.x + px0 * a.Cin + ci0;
+        const bf16_t* __restrict__ din = a.dz + px0 * a.Cout + co0;
+        const uint32_t at = 16u | (y0 == 0 ? 1u : 0u) | (y0 + kWgTH == a.H ? 2u : 0u) | (x0 == 0 ? 4u : 0u) |
+                            (x0 + kWgTW == a.W ? 8u : 0u);
+#pragma unroll
+        for (int k = 0; k < NX; k++) {
+            vx[k] = (u32x4)(0u);
+            if (!((out >> (5 * k)) & at)) vx[k] = *reinterpret_cast<const u32x4*>(xin + ox[k]);
         }
-        for (int i = tid; i < kWgTH * kWgTW * (BN / 8); i += kWgThreads) {
-            const int g = i % (BN / 8), p = i / (BN / 8);
-            const int yy = y0 + p / kWgTW, xx = x0 + p % kWgTW;
-            *reinterpret_cast<uint4*>(sD + p * BN + 8 * g) =
-                *reinterpret_cast<const uint4*>(din + ((int64_t)yy * a.W + xx) * a.Cout + co0 + 8 * g);
+#pragma unroll
+        for (int k = 0; k < ND; k++) vd[k] = *reinterpret_cast<const u32x4*>(din + od[k]);
+    };
+
+    if (t_begin < t_end) fetch(t_begin);
+    for (int tile = t_begin; tile < t_end; tile++) {
+#pragma unroll
+        for (int k = 0; k < NX; k++) {
+            const int i = tid + k * T;
+            if (i < HP * WP * 4) *reinterpret_cast<u32x4*>(sX + (i >> 2) * kWgCB + 8 * (i & 3)) = vx[k];
+        }
+#pragma unroll
+        for (int k = 0; k < ND; k++) {
+            const int i = tid + k * T;
+            if (i < kWgTH * kWgTW * (BN / 8))
+                *reinterpret_cast<u32x4*>(sD + (i / (BN / 8)) * DS + 8 * (i % (BN / 8))) = vd[k];
         }
         __syncthreads();
+        if (tile + 1 < t_end) fetch(tile + 1);
+#pragma unroll
         for (int row = 0; row < kWgTH; row++) {
+#pragma unroll
             for (int xb = 0; xb < kWgTW; xb += 16) {
                 const int px = xb + 8 * h;  // first pixel (tile column) of this half wave
-                uint16_t xv[10];
-                for (int m = 0; m < 10; m++) xv[m] = sX[((row + wave) * WP + px + m) * kWgCB + l32];
-                bf16x8 av[3];
-                for (int kx = 0; kx < 3; kx++) {
-                    u16x8 t;
-                    for (int j = 0; j < 8; j++) t[j] = xv[kx + j];
-                    av[kx] = __builtin_bit_cast(bf16x8, t);
-                }
-                for (int jn = 0; jn < NT; jn++) {
-                    u16x8 t;
-                    for (int j = 0; j < 8; j++) t[j] = sD[(row * kWgTW + px + j) * BN + 32 * jn + l32];
-                    const bf16x8 bv = __builtin_bit_cast(bf16x8, t);
-                    for (int kx = 0; kx < 3; kx++) acc[kx][jn] = mfma16(av[kx], bv, acc[kx][jn]);
-                }
+                const bf16_t* xr = sX + ((row + ky) * WP + px) * kWgCB + tr_x;
+                uint2 w[3];  // 12 pixels of channel ci0 + l32
+#pragma unroll
+                for (int m = 0; m < 3; m++) w[m] = lds_read_tr16(xr + 4 * m * kWgCB);
+                const bf16_t* dr = sD + (row * kWgTW + px) * DS + tr_d;
+                const uint2 d0 = lds_read_tr16(dr), d1 = lds_read_tr16(dr + 4 * DS);
+                const bf16x8 bv = frag(d0.x, d0.y, d1.x, d1.y);
+                const bf16x8 av[3] = {
+                    frag(w[0].x, w[0].y, w[1].x, w[1].y),
+                    frag(__builtin_amdgcn_alignbit(w[0].y, w[0].x, 16), __builtin_amdgcn_alignbit(w[1].x, w[0].y, 16),
+                         __builtin_amdgcn_alignbit(w[1].y, w[1].x, 16), __builtin_amdgcn_alignbit(w[2].x, w[1].y, 16)),
+                    frag(w[0].y, w[1].x, w[1].y, w[2].x)};
+#pragma unroll
+                for (int kx = 0; kx < 3; kx++) acc[kx] = mfma16(av[kx], bv, acc[kx]);
             }
         }
         __syncthreads();
     }
 
     const int keep = a.cin_keep;
+    const int co = co0 + 32 * jn + l32;
+#pragma unroll
     for (int kx = 0; kx < 3; kx++) {
-        const int t = 3 * wave + kx;
-        for (int jn = 0; jn < NT; jn++) {
-            const int co = co0 + 32 * jn + l32;
-            for (int i = 0; i < 16; i++) {
-                const int ci = ci0 + 8 * (i >> 2) + 4 * h + (i & 3);
-                if (ci < keep)
-                    a.part[(((int64_t)split * 9 + t) * keep + ci) * a.Cout + co] = acc[kx][jn][i];
-            }
+        const int t = 3 * ky + kx;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int ci = ci0 + 8 * (i >> 2) + 4 * h + (i & 3);
+            if (ci < keep) a.part[(((int64_t)split * 9 + t) * keep + ci) * a.Cout + co] = acc[kx][i];
         }
     }
 }
@@ -920,8 +980,18 @@ __global__ void __launch_bounds__(256) k_colsum(const float* __restrict__ part, 
     const int64_t c = (int64_t)blockIdx.x * 32 + cl;
     const int64_t b0 = (int64_t)blockIdx.y * chunk, b1 = min(nb, b0 + chunk);
     float s = 0.0f;
-    if (c < ncols)
-        for (int64_t b = b0 + r; b < b1; b += 8) s += part[b * ncols + c];
+    if (c < ncols) {
+        const float* src = part + c;
+        int64_t b = b0 + r;
+        for (; b + 56 < b1; b += 64) {  // 8 loads in flight, added in order
+            float v[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) v[k] = src[(b + 8 * k) * ncols];
+#pragma unroll
+            for (int k = 0; k < 8; k++) s += v[k];
+        }
+        for (; b < b1; b += 8) s += src[b * ncols];
+    }
     sh[r][cl] = s;
     __syncthreads();
     if (r == 0 && c < ncols) {
@@ -1010,42 +1080,6 @@ __global__ void k_maxpool(const bf16_t* __restrict__ in, int n, int H, int W, in
     *reinterpret_cast<u16x8*>(out + q * C + 8 * g) = o;
 }
 
-// One thread per (pooled pixel, channel): route g to the first maximum.
-__global__ void k_maxpool_back(const float* __restrict__ g, const bf16_t* __restrict__ act, int n, int H,
-                               int W, int C, int cs, int co, const float* __restrict__ add, int add_cs,
-                               int add_co, float* __restrict__ gin)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int h2 = H / 2, w2 = W / 2;
-    if (i >= (int64_t)n * h2 * w2 * C) return;
-    const int c = (int)(i % C);
-    const int64_t q = i / C;
-    const int x = (int)(q % w2);
-    const int64_t r = q / w2;
-    const int y = (int)(r % h2);
-    const int64_t img = r / h2;
-    int64_t pix[4];
-    pix[0] = (img * H + 2 * y) * W + 2 * x;
-    pix[1] = pix[0] + 1;
-    pix[2] = pix[0] + W;
-    pix[3] = pix[2] + 1;
-    int k = 0;
-    float m = bf2f(act[pix[0] * cs + co + c]);
-    for (int j = 1; j < 4; j++) {
-        const float v = bf2f(act[pix[j] * cs + co + c]);
-        if (v > m) {
-            m = v;
-            k = j;
-        }
-    }
-    const float gv = g[i];
-    for (int j = 0; j < 4; j++) {
-        float v = j == k ? gv : 0.0f;
-        if (add) v += add[pix[j] * add_cs + add_co + c];
-        gin[pix[j] * C + c] = v;
-    }
-}
-
 __global__ void k_upsample_into(const bf16_t* __restrict__ in, int n, int h, int w, int C,
                                 bf16_t* __restrict__ out, int cs)
 {
@@ -1067,29 +1101,94 @@ __global__ void k_upsample_into(const bf16_t* __restrict__ in, int n, int h, int
     *reinterpret_cast<uint4*>(out + o + (int64_t)W2 * cs + cs) = v;
 }
 
-__global__ void k_upsample_back(const float* __restrict__ gout, int n, int h, int w, int C, int cs,
-                                float* __restrict__ g)
+// Gradient of 8 channels (8 q ..) of the activation at pixel p, from where the
+// layer above left it.
+struct f32x8 {
+    float v[8];
+};
+__device__ inline f32x8 load8(const float* p)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)n * h * w * C) return;
-    const int c = (int)(i % C);
-    const int64_t q = i / C;
-    const int x = (int)(q % w);
-    const int64_t r = q / w;
-    const int y = (int)(r % h);
-    const int64_t img = r / h;
-    const int W2 = 2 * w;
-    const int64_t o = ((img * 2 * h + 2 * y) * W2 + 2 * x) * cs + c;
-    g[i] = ((gout[o] + gout[o + cs]) + gout[o + (int64_t)W2 * cs]) + gout[o + (int64_t)W2 * cs + cs];
+    const float4 a = *reinterpret_cast<const float4*>(p), b = *reinterpret_cast<const float4*>(p + 4);
+    return {{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
+}
+struct PixelXY {
+    uint32_t img, y, x;
+};
+__device__ inline PixelXY pixel_xy(int64_t p, int H, int W)
+{
+    const uint32_t u = (uint32_t)p, r = u / (uint32_t)W;
+    return {r / (uint32_t)H, r % (uint32_t)H, u % (uint32_t)W};
+}
+__device__ inline f32x8 grad8(const PlainGrad& s, int64_t p, int C, int q) { return load8(s.g + p * C + 8 * q); }
+// The pooled gradient goes to the first maximum of each 2 x 2 window.
+__device__ inline f32x8 grad8(const PooledGrad& s, int64_t p, int C, int q)
+{
+    const PixelXY a = pixel_xy(p, s.H, s.W);
+    const int64_t p00 = p - (a.x & 1) - (int64_t)(a.y & 1) * s.W;
+    const bf16_t* act = s.act + p00 * s.act_cs + s.act_co + 8 * q;
+    u16x8 w[4];
+    w[0] = *reinterpret_cast<const u16x8*>(act);
+    w[1] = *reinterpret_cast<const u16x8*>(act + s.act_cs);
+    w[2] = *reinterpret_cast<const u16x8*>(act + (int64_t)s.W * s.act_cs);
+    w[3] = *reinterpret_cast<const u16x8*>(act + (int64_t)(s.W + 1) * s.act_cs);
+    const f32x8 g = load8(s.g + (((int64_t)a.img * (s.H / 2) + a.y / 2) * (s.W / 2) + a.x / 2) * C + 8 * q);
+    f32x8 add{};
+    if (s.add) add = load8(s.add + p * s.add_cs + s.add_co + 8 * q);
+    const int own = (int)(2 * (a.y & 1) + (a.x & 1));
+    f32x8 o;
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        int k = 0;
+        float m = bf2f(w[0][j]);
+#pragma unroll
+        for (int i = 1; i < 4; i++) {
+            const float v = bf2f(w[i][j]);
+            if (v > m) {
+                m = v;
+                k = i;
+            }
+        }
+        o.v[j] = k == own ? g.v[j] : 0.0f;
+        if (s.add) o.v[j] += add.v[j];
+    }
+    return o;
+}
+// The sum over the 2 x 2 pixels that copied this one.
+__device__ inline f32x8 grad8(const UpsampledGrad& s, int64_t p, int C, int q)
+{
+    const PixelXY a = pixel_xy(p, s.H, s.W);
+    const int W2 = 2 * s.W;
+    const float* g = s.g + (((int64_t)a.img * 2 * s.H + 2 * a.y) * W2 + 2 * a.x) * s.cs + 8 * q;
+    const f32x8 g0 = load8(g), g1 = load8(g + s.cs), g2 = load8(g + (int64_t)W2 * s.cs),
+                g3 = load8(g + (int64_t)(W2 + 1) * s.cs);
+    f32x8 o;
+#pragma unroll
+    for (int j = 0; j < 8; j++) o.v[j] = ((g0.v[j] + g1.v[j]) + g2.v[j]) + g3.v[j];
+    return o;
+}
+// The head's two outputs.
+__device__ inline f32x8 grad8(const HeadGrad& s, int64_t p, int, int q)
+{
+    const float2 g = *reinterpret_cast<const float2*>(s.gout + 2 * p);
+    f32x8 o;
+#pragma unroll
+    for (int j = 0; j < 8; j++) {
+        const float2 w = *reinterpret_cast<const float2*>(s.hw + 2 * (8 * q + j));
+        o.v[j] = g.x * w.x + g.y * w.y;
+    }
+    return o;
 }
 
 // One thread per (pixel, 8-channel group): 16-byte loads of the activation,
 // 32-byte loads of the gradient, a 16-byte store of dz.  A block covers
 // 2048 / C pixels; its partial bias sums add the block's pixels in order.
-// C must be 32, 64, 128 or 256.
-__global__ void __launch_bounds__(256) k_mask_round(const float* __restrict__ g, const bf16_t* __restrict__ act,
-                                                    int64_t P, int C, int act_cs, int act_co,
-                                                    bf16_t* __restrict__ dz, float* __restrict__ part)
+// C must be 32, 64, 128 or 256.  Bound: memory.  The gradient behind a pooling, an
+// upsampling or the head is formed here, not written as fp32 and read back (64
+// pairs of 256 x 256, the pooling of 32 channels: 155 + 195 us before, 150 now).
+template <class Src>
+__global__ void __launch_bounds__(256) k_mask_round(Src src, const bf16_t* __restrict__ act, int64_t P, int C,
+                                                    int act_cs, int act_co, bf16_t* __restrict__ dz,
+                                                    float* __restrict__ part)
 {
     __shared__ float sh[256][9];
     const int tid = threadIdx.x;
@@ -1100,12 +1199,10 @@ __global__ void __launch_bounds__(256) k_mask_round(const float* __restrict__ g,
     for (int j = 0; j < 8; j++) v[j] = 0.0f;
     if (p < P) {
         const u16x8 a = *reinterpret_cast<const u16x8*>(act + p * act_cs + act_co + 8 * q);
-        const float4 g0 = *reinterpret_cast<const float4*>(g + p * C + 8 * q);
-        const float4 g1 = *reinterpret_cast<const float4*>(g + p * C + 8 * q + 4);
-        const float gv[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        const f32x8 g = grad8(src, p, C, q);
         u16x8 o;
         for (int j = 0; j < 8; j++) {
-            v[j] = bf2f(a[j]) > 0.0f ? gv[j] : 0.0f;
+            v[j] = bf2f(a[j]) > 0.0f ? g.v[j] : 0.0f;
             o[j] = f2bf(v[j]);
         }
         *reinterpret_cast<u16x8*>(dz + p * C + 8 * q) = o;
@@ -1177,8 +1274,7 @@ constexpr int kHeadPB = 256;
 
 // Columns of the partial sums: dhw[c][o] at 2c + o, dhb[o] at 2C + o.
 __global__ void __launch_bounds__(256) k_head_back(const bf16_t* __restrict__ act, const float* __restrict__ gout,
-                                                   int64_t P, int C, const float* __restrict__ hw,
-                                                   float* __restrict__ gact, float* __restrict__ part)
+                                                   int64_t P, int C, float* __restrict__ part)
 {
     const int tid = threadIdx.x;
     const int64_t p0 = (int64_t)blockIdx.x * kHeadPB;
@@ -1186,19 +1282,26 @@ __global__ void __launch_bounds__(256) k_head_back(const bf16_t* __restrict__ ac
     const int ncol = 2 * C + 2;
     for (int col = tid; col < ncol; col += 256) {
         float s = 0.0f;
+        const int o = col & 1;
+        const float* go = gout + o;
         if (col < 2 * C) {
-            const int c = col >> 1, o = col & 1;
-            for (int64_t p = p0; p < p1; p++) s += bf2f(act[p * C + c]) * gout[2 * p + o];
+            const bf16_t* ac = act + (col >> 1);
+            int64_t p = p0;
+            for (; p + 16 <= p1; p += 16) {  // 16 pixels in flight, added in order
+                float va[16], vg[16];
+#pragma unroll
+                for (int k = 0; k < 16; k++) {
+                    va[k] = bf2f(ac[(p + k) * C]);
+                    vg[k] = go[2 * (p + k)];
+                }
+#pragma unroll
+                for (int k = 0; k < 16; k++) s += va[k] * vg[k];
+            }
+            for (; p < p1; p++) s += bf2f(ac[p * C]) * go[2 * p];
         } else {
-            const int o = col - 2 * C;
-            for (int64_t p = p0; p < p1; p++) s += gout[2 * p + o];
+            for (int64_t p = p0; p < p1; p++) s += go[2 * p];
         }
         part[(int64_t)blockIdx.x * ncol + col] = s;
-    }
-    for (int64_t i = tid; i < (p1 - p0) * C; i += 256) {
-        const int64_t p = p0 + i / C;
-        const int c = (int)(i % C);
-        gact[p * C + c] = gout[2 * p] * hw[2 * c] + gout[2 * p + 1] * hw[2 * c + 1];
     }
 }
 
@@ -1323,7 +1426,7 @@ hipError_t launch_wgrad3x3(const WgradArgs& a, hipStream_t s)
         return hipErrorInvalidValue;
     const int nt = a.Cout % 64 == 0 ? 2 : 1;
     const int ncb = (a.Cin + kWgCB - 1) / kWgCB, nob = a.Cout / (32 * nt);
-    const dim3 grid((unsigned)((int64_t)a.splits * ncb * nob)), block(kWgThreads);
+    const dim3 grid((unsigned)((int64_t)a.splits * ncb * nob)), block(nt * kWgThreads);
     if (nt == 2) hipLaunchKernelGGL(k_wgrad3x3<2>, grid, block, 0, s, a);
     else hipLaunchKernelGGL(k_wgrad3x3<1>, grid, block, 0, s, a);
     return hipGetLastError();
@@ -1372,16 +1475,6 @@ hipError_t launch_maxpool(const bf16_t* in, int n, int H, int W, int C, int cs, 
     return hipGetLastError();
 }
 
-hipError_t launch_maxpool_back(const float* g, const bf16_t* act, int n, int H, int W, int C, int cs,
-                               int co, const float* add, int add_cs, int add_co, float* g_in,
-                               hipStream_t s)
-{
-    const int64_t items = (int64_t)n * (H / 2) * (W / 2) * C;
-    hipLaunchKernelGGL(k_maxpool_back, dim3(blocks_for(items, 256)), dim3(256), 0, s, g, act, n, H, W, C, cs,
-                       co, add, add_cs, add_co, g_in);
-    return hipGetLastError();
-}
-
 hipError_t launch_upsample_into(const bf16_t* in, int n, int h, int w, int C, bf16_t* out, int cs,
                                 hipStream_t s)
 {
@@ -1390,24 +1483,25 @@ hipError_t launch_upsample_into(const bf16_t* in, int n, int h, int w, int C, bf
     return hipGetLastError();
 }
 
-hipError_t launch_upsample_back(const float* gout, int n, int h, int w, int C, int cs, float* g,
-                                hipStream_t s)
-{
-    const int64_t items = (int64_t)n * h * w * C;
-    hipLaunchKernelGGL(k_upsample_back, dim3(blocks_for(items, 256)), dim3(256), 0, s, gout, n, h, w, C, cs, g);
-    return hipGetLastError();
-}
-
 int mask_blocks(int64_t P, int C) { return (int)((P * C / 8 + 255) / 256); }
 
-hipError_t launch_mask_round(const float* g, const bf16_t* act, int64_t P, int C, int act_cs,
-                             int act_co, bf16_t* dz, float* bias_part, hipStream_t s)
+template <class Src>
+hipError_t launch_mask_round(const Src& src, const bf16_t* act, int64_t P, int C, int act_cs, int act_co, bf16_t* dz,
+                             float* bias_part, hipStream_t s)
 {
     if (C != 32 && C != 64 && C != 128 && C != 256) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mask_round, dim3(mask_blocks(P, C)), dim3(256), 0, s, g, act, P, C, act_cs, act_co, dz,
+    hipLaunchKernelGGL(k_mask_round<Src>, dim3(mask_blocks(P, C)), dim3(256), 0, s, src, act, P, C, act_cs, act_co, dz,
                        bias_part);
     return hipGetLastError();
 }
+#define EBSD_MASK_ROUND(Src)                                                                                        \
+    template hipError_t launch_mask_round<Src>(const Src&, const bf16_t*, int64_t, int, int, int, bf16_t*, float*, \
+                                               hipStream_t);
+EBSD_MASK_ROUND(PlainGrad)
+EBSD_MASK_ROUND(PooledGrad)
+EBSD_MASK_ROUND(UpsampledGrad)
+EBSD_MASK_ROUND(HeadGrad)
+#undef EBSD_MASK_ROUND
 
 hipError_t launch_head_fwd(const bf16_t* act, int64_t P, int C, const float* hw, const float* hb,
                            float* out, hipStream_t s)
@@ -1428,10 +1522,9 @@ hipError_t launch_loss(const float* out, const float* label, int64_t P, float* g
 
 int head_blocks(int64_t P) { return (int)((P + kHeadPB - 1) / kHeadPB); }
 
-hipError_t launch_head_back(const bf16_t* act, const float* gout, int64_t P, int C, const float* hw,
-                            float* gact, float* part, hipStream_t s)
+hipError_t launch_head_back(const bf16_t* act, const float* gout, int64_t P, int C, float* part, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_head_back, dim3(head_blocks(P)), dim3(256), 0, s, act, gout, P, C, hw, gact, part);
+    hipLaunchKernelGGL(k_head_back, dim3(head_blocks(P)), dim3(256), 0, s, act, gout, P, C, part);
     return hipGetLastError();
 }
 

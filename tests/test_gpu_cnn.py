@@ -104,6 +104,20 @@ def test_conv_kernels_teacher_forced(E, n, cin, cout, H, W):
         assert np.all(np.abs(gw - ow) <= 1e-5 * sw + 1e-30)
 
 
+# workgroups of several tiles (the next one prefetched), the last range shorter, tiles at
+# every edge, 8 and 32 k input channels, one and two blocks of output channels
+@pytest.mark.parametrize("n,cin,cout,H,W", [(2, 32, 32, 256, 512), (3, 64, 64, 136, 512), (5, 8, 64, 152, 256),
+                                            (1, 96, 32, 264, 288)])
+def test_weight_gradient_over_many_tiles(E, n, cin, cout, H, W):
+    print(f"case: weight gradient n={n} cin={cin} cout={cout} {H}x{W}", flush=True)
+    rng = np.random.default_rng(cin + cout + H)
+    xg, x = bf16_tensor(np.maximum(rng.normal(0.2, 1.0, size=(n, H, W, cin)), 0.0))
+    dzg, dz = bf16_tensor(rng.normal(0.0, 1.0, size=(n, H, W, cout)))
+    gw = E.stage_conv3x3_wgrad(xg, dzg).cpu().numpy().astype(np.float64)
+    # the bar above: 1e-5 of the sum of magnitudes
+    assert np.all(np.abs(gw - cnn.conv3x3_wgrad(x, dz)) <= 1e-5 * cnn.conv3x3_wgrad(np.abs(x), np.abs(dz)) + 1e-30)
+
+
 def random_params(seed):
     p = cnn.init_params(seed)
     rng = np.random.default_rng(seed + 1000)
