@@ -321,12 +321,14 @@ __global__ void __launch_bounds__(1024)
 // gathers fall on different cache lines; from the vector cache (one line per
 // clock) 12 patterns of 1244 x 1024 took 1.91 ms for 25 iterations.  A workgroup
 // therefore keeps the test pattern around its tile's displaced position in LDS
-// (64 columns x 4 PX rows, a margin of 32 px on every side, placed by the
-// tile's mean displacement) and gathers there; lanes whose cell lies outside
-// the window read memory instead (1.16 ms; a margin of 20 px 1.33, of 44 px
-// 1.20).  Bound: vector ALU.  PX = 8 pixels per thread, or 2 where that leaves
-// CUs without work (the levels of one or few patterns).
-constexpr int kPointThreads = 256, kPointTX = 64, kPointMargin = 32;
+// (64 columns x 8 PX rows, a margin of 36 px on every side, placed by the tile's
+// mean displacement) and gathers there; lanes whose cell lies outside the window
+// read memory instead: 1.13 ms.  (Tiles of 4 PX rows and 32 px 1.18, with 24 px
+// 1.23, 16 px 1.33; of 16 PX rows and 48 px 1.23.)  Bound: vector ALU at 45%, and
+// the memory reads of a few far lanes that nearly every wavefront has in nearly
+// every iteration.  PX = 8 pixels per thread, or 2 where that leaves CUs without
+// work (the levels of one or few patterns: 12 of 622 x 512 209 us, 253 with 8).
+constexpr int kPointThreads = 512, kPointTX = 64, kPointMargin = 36;
 
 template <int PX>
 __global__ void __launch_bounds__(kPointThreads)

@@ -163,10 +163,10 @@ __device__ inline int mirror_any(int i, int n)
     return m < n ? m : P - m;
 }
 
-// One line of n samples at stride `st` (elements) from `in` into `out`,
-// outputs a .. a + kCoefB - 1 (those inside the line).
-__device__ inline void bspline_line_block(const float* __restrict__ in, float* __restrict__ out, int n, int64_t st,
-                                          int a)
+// Outputs a .. a + kCoefB - 1 of one line of n samples (a a multiple of kCoefB); at(k)
+// is sample k.
+template <class At>
+__device__ inline void bspline_line_block(At&& at, int n, int a, float (&out)[kCoefB])
 {
     const float z = -0.267949192431122706f;  // sqrt(3) - 2
     float cp = 0.0f, buf[kCoefB + kCoefWarm];
@@ -176,13 +176,13 @@ __device__ inline void bspline_line_block(const float* __restrict__ in, float* _
         for (int j = 0; j < kCoefB + 3 * kCoefWarm; j++) {
             int k = a - kCoefWarm + j;
             k = k < 0 ? -k : (k > n - 1 ? 2 * n - 2 - k : k);
-            cp = in[(int64_t)k * st] + z * cp;
+            cp = at(k) + z * cp;
             if (j >= kCoefWarm) buf[j - kCoefWarm] = cp;
         }
     } else {
 #pragma unroll
         for (int j = 0; j < kCoefB + 3 * kCoefWarm; j++) {
-            cp = in[(int64_t)mirror_any(a - kCoefWarm + j, n) * st] + z * cp;
+            cp = at(mirror_any(a - kCoefWarm + j, n)) + z * cp;
             if (j >= kCoefWarm) buf[j - kCoefWarm] = cp;
         }
     }
@@ -190,41 +190,70 @@ __device__ inline void bspline_line_block(const float* __restrict__ in, float* _
 #pragma unroll
     for (int j = kCoefB + kCoefWarm - 1; j >= 0; j--) {
         cm = z * (cm - buf[j]);
-        if (j < kCoefB && a + j < n) out[(int64_t)(a + j) * st] = 6.0f * cm;
+        if (j < kCoefB) out[j] = 6.0f * cm;
     }
 }
 
-// Row pass: a workgroup stages nr rows of one image in LDS with coalesced
-// loads (row pitch W + 1 words: the lanes of a wavefront, which walk
-// different rows, hit different banks), runs the recursions of every
-// (row, 32-column block) from LDS into a second LDS copy, and stores it
-// coalesced.  grid (ceil(H / nr), images); dynamic LDS 2 nr (W + 1) words.
+// Row pass: a workgroup stages nr rows of one image in LDS with coalesced loads, 8
+// in flight per thread, runs the recursions of every (row, 32-column block) from
+// there, one per thread, puts them in place of the samples and stores them
+// coalesced.  A word of padding after every block, and rows an odd number of words
+// apart, keep the lanes, which walk different rows and blocks, on different banks.
+// grid (ceil(H / nr), images); dynamic LDS nr coef_pitch(W) words, at least as many
+// threads as blocks.  256 patterns of 256 x 256 157 us with a second LDS copy and a
+// load at a time, 65 now; 12 of 1244 x 1024 155 and 38.
 constexpr int kCoefRows = 32;
-constexpr int kCoefLdsWords = 40960;  // 160 KiB
+constexpr int kCoefLdsWords = 17408;  // of a row of 16384 samples
+__host__ __device__ inline int coef_at(int x) { return x + (x >> 5); }
+__host__ __device__ inline int coef_pitch(int W) { return coef_at(W - 1) + 1 | 1; }
+static_assert(kCoefB == 32, "coef_at");
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(512)
     k_bspline_rows(const float* __restrict__ src_all, int64_t src_stride, float* __restrict__ tmp_all, int H, int W,
                    int nr)
 {
     extern __shared__ float lds[];
-    const int P = W + 1;
-    float* sin = lds;
-    float* sout = lds + nr * P;
+    const int P = coef_pitch(W);
+    const int nt = blockDim.x;
     const int y0 = blockIdx.x * nr, img = blockIdx.y;
     const int rows = min(nr, H - y0);
     const float* src = src_all + img * src_stride + (int64_t)y0 * W;
     float* dst = tmp_all + ((int64_t)img * H + y0) * W;
-    for (int r = 0; r < rows; r++)
-        for (int x = threadIdx.x; x < W; x += blockDim.x) sin[r * P + x] = src[(int64_t)r * W + x];
-    __syncthreads();
-    const int nblk = (W + kCoefB - 1) / kCoefB;
-    for (int t = threadIdx.x; t < rows * nblk; t += blockDim.x) {
-        const int r = t % rows, blk = t / rows;
-        bspline_line_block(sin + r * P, sout + r * P, W, 1, blk * kCoefB);
+    // the rows follow each other in memory
+    constexpr int U = 8;
+    const int total = rows * W;
+    {
+        int i = threadIdx.x, r = i / W, x = i - r * W;
+        const auto put = [&](float v) {
+            lds[r * P + coef_at(x)] = v;
+            i += nt;
+            for (x += nt; x >= W; x -= W) r++;
+        };
+        while (i + (U - 1) * nt < total) {
+            float v[U];
+#pragma unroll
+            for (int k = 0; k < U; k++) v[k] = src[i + nt * k];
+#pragma unroll
+            for (int k = 0; k < U; k++) put(v[k]);
+        }
+        while (i < total) put(src[i]);
     }
     __syncthreads();
-    for (int r = 0; r < rows; r++)
-        for (int x = threadIdx.x; x < W; x += blockDim.x) dst[(int64_t)r * W + x] = sout[r * P + x];
+    const int blk = threadIdx.x / rows, a = blk * kCoefB;
+    float* row = lds + (threadIdx.x - blk * rows) * P;
+    float out[kCoefB];
+    if (a < W) bspline_line_block([&](int k) { return row[coef_at(k)]; }, W, a, out);
+    __syncthreads();
+    if (a < W) {
+#pragma unroll
+        for (int j = 0; j < kCoefB; j++)
+            if (a + j < W) row[coef_at(a) + j] = out[j];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x, r = i / W, x = i - r * W; i < total; i += nt) {
+        dst[i] = lds[r * P + coef_at(x)];
+        for (x += nt; x >= W; x -= W) r++;
+    }
 }
 
 // thread = (image, row block, column), columns fastest
@@ -238,7 +267,12 @@ __global__ void __launch_bounds__(256)
     const int64_t r = t / W;
     const int blk = (int)(r % nblk), img = (int)(r / nblk);
     const int64_t o = (int64_t)img * H * W + x;
-    bspline_line_block(tmp_all + o, dst_all + o, H, W, blk * kCoefB);
+    const float* in = tmp_all + o;
+    float out[kCoefB];
+    bspline_line_block([&](int k) { return in[(int64_t)k * W]; }, H, blk * kCoefB, out);
+#pragma unroll
+    for (int j = 0; j < kCoefB; j++)
+        if (blk * kCoefB + j < H) dst_all[o + (int64_t)(blk * kCoefB + j) * W] = out[j];
 }
 
 // Coefficients of n images (image i at src + i src_stride, H x W) into dst
@@ -248,14 +282,14 @@ hipError_t launch_coef_images(const float* src, int64_t src_stride, int n, int H
 {
     if (n <= 0) return hipSuccess;
     const int64_t tc = (int64_t)n * W * ((H + kCoefB - 1) / kCoefB);
-    const int nr = std::max(1, std::min(kCoefRows, kCoefLdsWords / (2 * (W + 1))));
-    if (2 * nr * (W + 1) > kCoefLdsWords) return hipErrorInvalidValue;  // rows longer than 20479 samples
-    const size_t lds = sizeof(float) * 2 * nr * (size_t)(W + 1);
+    const int nblk = (W + kCoefB - 1) / kCoefB, P = coef_pitch(W), nt = nblk > 256 ? 512 : 256;
+    if (nblk > nt) return hipErrorInvalidValue;  // rows longer than 16384 samples
+    const int nr = std::min(kCoefRows, nt / nblk);
+    const size_t lds = sizeof(float) * nr * (size_t)P;  // at most 67 KiB
     static std::atomic<uint64_t> attr_done{0};
-    const hipError_t e =
-        ensure_dynamic_lds((const void*)k_bspline_rows, (int)(sizeof(float) * kCoefLdsWords), attr_done);
+    const hipError_t e = ensure_dynamic_lds((const void*)k_bspline_rows, (int)(sizeof(float) * kCoefLdsWords), attr_done);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_bspline_rows, dim3((unsigned)((H + nr - 1) / nr), (unsigned)n), dim3(256), lds, s, src,
+    hipLaunchKernelGGL(k_bspline_rows, dim3((unsigned)((H + nr - 1) / nr), (unsigned)n), dim3(nt), lds, s, src,
                        src_stride, tmp, H, W, nr);
     hipLaunchKernelGGL(k_bspline_cols, dim3((unsigned)((tc + 255) / 256)), dim3(256), 0, s, tmp, dst, n, H, W);
     return hipGetLastError();

@@ -162,3 +162,19 @@ def test_known_small_rotation_recovered(E, orc):
     d = np.abs(g["F"].cpu().numpy() - o2["F"]).max()
     print("8 passes from the GPU's R_finite: max |dF| vs oracle %.2e" % d)
     assert d <= 1e-6
+
+
+# lines of less than one block, just past one and two, rows that leave a workgroup part of
+# its rows or of its blocks, and those of more than 256 blocks.  Against the exact mirrored
+# filter: a recursion rounds twice per step (gain 1 / (1 - |z|) = 1.37), 17 units of 2^-24
+# max|s| per pass, each pass with gain 3: 102 units, and the dropped start values 2
+@pytest.mark.parametrize("H,W", [(8, 31), (40, 49), (33, 65), (70, 257), (5, 1244), (4, 8192), (4, 8193), (4, 16384)])
+def test_coefficients_at_block_edges(E, H, W):
+    import scipy.ndimage as ndi
+    print(f"case: spline coefficients {H}x{W}", flush=True)
+    img = np.random.default_rng(H * W).uniform(-1.0, 1.0, size=(2, H, W)).astype(np.float32)
+    _, coef = E.stage_remap(torch.from_numpy(img).cuda(), torch.eye(3, dtype=torch.float64).repeat(2, 1, 1),
+                            (W / 2 - 0.5, H / 2 - 0.5, 0.7 * W), interp=3)
+    for i in range(2):
+        exact = ndi.spline_filter(img[i].astype(np.float64), order=3, mode="mirror", output=np.float64)
+        assert np.abs(coef[i].cpu().numpy() - exact).max() <= 104 * 2.0 ** -24
