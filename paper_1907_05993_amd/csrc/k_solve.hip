@@ -12,6 +12,8 @@
 // eigen-solver, the 12 x 13 Lagrange-Newton system) works on matrices in LDS,
 // one column of words per thread, so that no array goes to scratch memory; the
 // small fixed-index algebra stays in registers.
+#include <type_traits>
+
 #include "ebsd_internal.h"
 #include "cnn_internal.h"
 
@@ -1121,13 +1123,37 @@ __global__ void k_scatter_warm(const Bucket* __restrict__ bk)
 // the coarse grid points (full-resolution coordinates 4 i + 1.5) that lie within
 // `radius` of the pattern centre; each thread sums over a strided subset of the
 // points and the sums are combined in a fixed order, so the result does not
-// depend on scheduling.  All threads then run the same small dense algebra.
+// depend on scheduling.  All threads then run the same small dense algebra.  Bound:
+// the chain of one workgroup (about 12 iterations; 200 pairs 168 us before the
+// products with zeros, the LDS shuffles of the sums, the divisions of the solve and
+// the reads of the field from memory were taken out, 112 us now).
 constexpr int kFitThreads = 256;
+constexpr int kFitGrid = 64;  // points a side at most (kept in LDS: every iteration reads them)
 
+// Sum over the wavefront, lane l adding lanes l ^ 32, 16, 8, 4, 2, 1 in turn: across the
+// halves and rows by the swap instructions, then inside the rows of 16 by rotations
+// (after the step of 8 the row repeats after 8 lanes, so that the rotation by 4 fetches
+// the value of l ^ 4, and so on).
 __device__ inline double wave_sum_d(double v)
 {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    const auto add_swapped = [](double v, auto swap) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const auto lo = swap((uint32_t)u), hi = swap((uint32_t)(u >> 32));
+        return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+               __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+    };
+    const auto add_rotated = [](double v, auto ctrl) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, decltype(ctrl)::value, 0xf, 0xf, true);
+        const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        return v + __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    };
+    v = add_swapped(v, [](uint32_t x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+    v = add_swapped(v, [](uint32_t x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    v = add_rotated(v, std::integral_constant<int, 0x128>{});
+    v = add_rotated(v, std::integral_constant<int, 0x124>{});
+    v = add_rotated(v, std::integral_constant<int, 0x122>{});
+    return add_rotated(v, std::integral_constant<int, 0x121>{});
 }
 
 template <int NV>
@@ -1143,6 +1169,36 @@ __device__ void fit_block_sum(double (&v)[NV], double* sh)
 #pragma unroll
     for (int k = 0; k < NV; k++) v[k] = ((sh[k] + sh[NV + k]) + sh[2 * NV + k]) + sh[3 * NV + k];
     __syncthreads();
+}
+
+// Products of the two Jacobian rows of a point, a = (r0, r1, r2, 0, 0, 0, a6, a7) and
+// b = (0, 0, 0, r0, r1, r2, b6, b7), onto t: the 36 of the upper triangle of a a^T + b b^T
+// (those with a zero left out), then a ea + b eb.
+template <int NV>
+__device__ inline void add_rows(double (&t)[NV], const double (&r)[3], double a6, double a7, double b6, double b7,
+                                double ea, double eb)
+{
+    const auto at = [](int i, int j) { return i * 8 - i * (i - 1) / 2 + j - i; };
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+#pragma unroll
+        for (int j = i; j < 3; j++) {
+            const double p = r[i] * r[j];
+            t[at(i, j)] += p;
+            t[at(3 + i, 3 + j)] += p;
+        }
+        t[at(i, 6)] += r[i] * a6;
+        t[at(i, 7)] += r[i] * a7;
+        t[at(3 + i, 6)] += r[i] * b6;
+        t[at(3 + i, 7)] += r[i] * b7;
+        t[36 + i] += r[i] * ea;
+        t[39 + i] += r[i] * eb;
+    }
+    t[at(6, 6)] += a6 * a6 + b6 * b6;
+    t[at(6, 7)] += a6 * a7 + b6 * b7;
+    t[at(7, 7)] += a7 * a7 + b7 * b7;
+    t[42] += a6 * ea + b6 * eb;
+    t[43] += a7 * ea + b7 * eb;
 }
 
 struct GridFit {
@@ -1164,9 +1220,12 @@ k_warm_fit(const float* __restrict__ field, int gh, int gw, double xs, double ys
            float* __restrict__ u_init, float* __restrict__ misfit, uint32_t* __restrict__ flag)
 {
     __shared__ double sh[4 * 45];
+    __shared__ __attribute__((aligned(16))) float qs[2 * kFitGrid * kFitGrid];
     const int b = blockIdx.x;
     GridFit gf;
-    gf.q = field + (int64_t)b * gh * gw * 2;
+    for (int i = threadIdx.x; i < gh * gw * 2; i += kFitThreads) qs[i] = field[(int64_t)b * gh * gw * 2 + i];
+    __syncthreads();
+    gf.q = qs;
     gf.gh = gh;
     gf.gw = gw;
     gf.xs = xs;
@@ -1192,15 +1251,8 @@ k_warm_fit(const float* __restrict__ field, int gh, int gw, double xs, double ys
             const double ax = x - xs, ay = y - ys;
             const double rx = ax * gf.iz, ry = ay * gf.iz;
             const double px = (ax + (double)gf.q[2 * g]) * gf.iz, py = (ay + (double)gf.q[2 * g + 1]) * gf.iz;
-            const double ra[8] = {rx, ry, 1.0, 0.0, 0.0, 0.0, -px * rx, -px * ry};
-            const double rb[8] = {0.0, 0.0, 0.0, rx, ry, 1.0, -py * rx, -py * ry};
-            int k = 0;
-#pragma unroll
-            for (int a = 0; a < 8; a++)
-#pragma unroll
-                for (int c = a; c < 8; c++) t[k++] += ra[a] * ra[c] + rb[a] * rb[c];
-#pragma unroll
-            for (int a = 0; a < 8; a++) t[36 + a] += ra[a] * px + rb[a] * py;
+            const double r[3] = {rx, ry, 1.0};
+            add_rows(t, r, -px * rx, -px * ry, -py * rx, -py * ry, px, py);
             t[44] += 1.0;
         }
         fit_block_sum<45>(t, sh);
@@ -1214,8 +1266,11 @@ k_warm_fit(const float* __restrict__ field, int gh, int gw, double xs, double ys
                 k++;
             }
         for (int a = 0; a < 8; a++) rhs[a] = t[36 + a];
-        if (cholesky_solve8(A, rhs, sol))
+        double Lm[8][8], ip[8];
+        if (cholesky8(A, Lm, ip)) {
+            cholesky8_solve(Lm, ip, rhs, sol);
             for (int a = 0; a < 8; a++) f[a] = sol[a];
+        }
     }
 
     // Gauss-Newton on the 8 free entries (|step| < 1e-12 or 100 steps)
@@ -1235,15 +1290,8 @@ k_warm_fit(const float* __restrict__ field, int gh, int gw, double xs, double ys
             const double id = 1.0 / d;
             const double u = n1 * id, v = n2 * id;
             const double ex = u - pxi, ey = v - pyi;
-            const double ju[8] = {r0 * id, r1 * id, id, 0.0, 0.0, 0.0, -u * r0 * id, -u * r1 * id};
-            const double jv[8] = {0.0, 0.0, 0.0, r0 * id, r1 * id, id, -v * r0 * id, -v * r1 * id};
-            int k = 0;
-#pragma unroll
-            for (int a = 0; a < 8; a++)
-#pragma unroll
-                for (int c = a; c < 8; c++) t[k++] += ju[a] * ju[c] + jv[a] * jv[c];
-#pragma unroll
-            for (int a = 0; a < 8; a++) t[36 + a] += ju[a] * ex + jv[a] * ey;
+            const double r[3] = {r0 * id, r1 * id, id};
+            add_rows(t, r, -u * r0 * id, -u * r1 * id, -v * r0 * id, -v * r1 * id, ex, ey);
         }
         fit_block_sum<44>(t, sh);
         double JtJ[8][8], rhs[8], dlt[8];
@@ -1255,7 +1303,9 @@ k_warm_fit(const float* __restrict__ field, int gh, int gw, double xs, double ys
                 k++;
             }
         for (int a = 0; a < 8; a++) rhs[a] = -t[36 + a];
-        if (!cholesky_solve8(JtJ, rhs, dlt)) break;
+        double Lm[8][8], ip[8];
+        if (!cholesky8(JtJ, Lm, ip)) break;
+        cholesky8_solve(Lm, ip, rhs, dlt);
         double nrm = 0.0;
         for (int a = 0; a < 8; a++) {
             f[a] += dlt[a];
@@ -1415,7 +1465,7 @@ hipError_t launch_warm_fit(const float* field, int n, int net_res, double xs, do
 {
     if (n <= 0) return hipSuccess;
     const int g = net_res / 4, go = N / 4;
-    if (!(go == g || go == 2 * g || 2 * go == g)) return hipErrorInvalidValue;
+    if (g > kFitGrid || !(go == g || go == 2 * g || 2 * go == g)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_warm_fit, dim3(n), dim3(kFitThreads), 0, s, field, g, g, xs, ys, zs, radius, threshold,
                        model_field, go, xsN, ysN, zsN, u_init, misfit, flag);
     return hipGetLastError();
