@@ -103,10 +103,6 @@ def main():
     ap.add_argument("--summarize-pmc", nargs=4, metavar=("COPY_FETCH", "COPY_WRITE", "FETCH", "WRITE"),
                     help="write the HBM traffic record (--traffic-json) from four rocprofv3 --pmc output "
                          "folders (FETCH_SIZE and WRITE_SIZE of --copy-probe, then of a bench run) and exit")
-    ap.add_argument("--strip-rows", type=int, default=64,
-                    help="with --summarize-pmc: the level-0 strip height the profiled run used")
-    ap.add_argument("--two-iteration-rows", type=int, default=128,
-                    help="with --summarize-pmc: the level-0 two-iteration strip height the profiled run used")
     args = ap.parse_args()
 
     if args.summarize_pmc:
@@ -207,6 +203,7 @@ def main():
         torch.cuda.synchronize()
         el = time.perf_counter() - ts
         level_ms, total_ms = reg.timing()
+        launches = reg.launch_counts()[0]
         iters = out["iters"].cpu().numpy().astype(np.int64)
         st = out["status"].cpu().numpy().astype(np.int64)
         err = np.linalg.norm(out["rotvec"].cpu().numpy() - rv_true, axis=1)
@@ -234,7 +231,7 @@ def main():
         out.pop("field", None)
         out_ref = {k: out[k] for k in ("F", "iters", "status", "q2")}
         return dict(out_ref=out_ref, parity=keep, R_finite=out["R_finite"], ssim=ssim, serr=serr, serr1=serr1, elapsed=el, level_ms=level_ms, total_ms=total_ms, iters=iters, status=st, err=err,
-                    tuned=tuned, fused=fused, err_first=err_first, mae_first=out["mae_first"].cpu().numpy(),
+                    tuned=tuned, fused=fused, launches=launches, err_first=err_first, mae_first=out["mae_first"].cpu().numpy(),
                     mae=out["mae"].cpu().numpy(), ph=out["peak_height"].cpu().numpy().mean(axis=1))
 
     warm = timed(make(True, args.cap), "warm start", parity_idx=par_idx)
@@ -346,10 +343,10 @@ def main():
     level_ms = warm["level_ms"]
     demons_bytes = float(BYTES_PER_PX_ITER * px_iters.sum())
     demons_ms = float(level_ms.sum())
-    rows0 = warm["tuned"].get((H, W), 0)
-    frows0 = warm["fused"].get((H, W), 0)
+    # iterations per launch at level 0 (the last launch of a tolerance run may only decide)
     iters0 = int(warm["iters"][:, 0].max())
-    launches0 = (iters0 + 1) // 2 if frows0 else iters0
+    per0 = max(1, round(iters0 / max(int(warm["launches"][0]), 1)))
+    launches0 = -(-iters0 // per0)
     alg_per_launch0 = BYTES_PER_PX_ITER * px_iters[0] / max(launches0, 1)
     launch0_ms = float(level_ms[0]) / max(launches0, 1)
     achieved = alg_per_launch0 / (launch0_ms * 1e-3) / 1e9
@@ -360,7 +357,7 @@ def main():
             tj = json.load(open(args.traffic_json))
             lv = tj.get("levels", {}).get("0", {})
             if (tj.get("workload") == args.workload and tj.get("kernel_source_sha") == kernel_sha()
-                    and lv.get("strip_rows") == rows0 and lv.get("two_iteration_rows", 0) == frows0):
+                    and lv.get("iterations_per_launch") == per0):
                 traffic = lv.get("bytes_per_launch")
         except Exception:
             traffic = None
@@ -411,10 +408,8 @@ def main():
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": (f"k_demons_rows2 (two iterations per launch), level 0 ({H}x{W}), {frows0}-row strips"
-                       if frows0 else
-                       f"k_demons_rows (fused warp + gradient + Eq.1 force + update + Gaussian "
-                       f"smoothing), level 0 ({H}x{W}), {rows0}-row strips"),
+            "kernel": f"k_demons_* (fused warp + gradient + Eq.1 force + update + Gaussian smoothing), level 0 "
+                      f"({H}x{W}), {per0} iteration(s) per launch",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -766,7 +761,7 @@ def summarize_pmc(args):
     fetch = _pmc_rows(args.summarize_pmc[2], "FETCH_SIZE")
     write = _pmc_rows(args.summarize_pmc[3], "WRITE_SIZE")
     out = {}
-    for kn in sorted({k for k, _ in fetch if "k_demons_rows2" in k}):
+    for kn in sorted({k for k, _ in fetch if "k_demons_march" in k or "k_demons_rows2" in k}):
         # median over the dispatches that ran two iterations (the decision-only launch at a
         # level's end moves almost nothing)
         nf = [v * 1024.0 * fetch_factor for k, v in fetch if k == kn]
@@ -777,12 +772,11 @@ def summarize_pmc(args):
         big_w = [v for v in nw if v > 0.1 * max(nw)]
         name = kn.replace("(anonymous namespace)::", "").replace("void ", "").split("(")[0].replace("ebsd::", "")
         out[name] = int(np.median(big_f) + np.median(big_w))
-    level0 = [k for k in out if k.startswith("k_demons_rows2<4, 3, %d," % args.two_iteration_rows)]
+    level0 = [k for k in out if k.startswith("k_demons_march<4, 3")]  # four columns per lane: 256 px
     rec = {"workload": args.workload, "kernel_source_sha": kernel_sha(), "bytes_per_launch": out,
            "calibration": {"fetch_factor": fetch_factor, "write_factor": write_factor}}
     if level0:
-        rec["levels"] = {"0": {"kernel": level0[0], "strip_rows": args.strip_rows,
-                               "two_iteration_rows": args.two_iteration_rows,
+        rec["levels"] = {"0": {"kernel": level0[0], "iterations_per_launch": 2,
                                "bytes_per_launch": out[level0[0]]}}
     with open(args.traffic_json, "w") as fh:
         json.dump(rec, fh, indent=1)
@@ -797,7 +791,8 @@ def kernel_sha():
     import glob
     csrc = os.path.join(ROOT, "paper_1907_05993_amd", "csrc")
     files = sorted(glob.glob(os.path.join(csrc, "k_demons*.hip"))) + [os.path.join(csrc, "demons_rows_impl.h"),
-                                                                         os.path.join(csrc, "dev_util.h")]
+                                                                  os.path.join(csrc, "demons_region.h"),
+                                                                  os.path.join(csrc, "dev_util.h")]
     for f in files:
         h.update(open(f, "rb").read())
     return h.hexdigest()[:16]
