@@ -292,8 +292,9 @@ int ebsd_set_graphs(ebsd_handle* h, int enable);
  * (multi-resolution demons, section 1).  Finer levels whose size was not
  * set by ebsd_set_strip_height / ebsd_set_fused_height also run several
  * iterations per launch by rule: all of them without smoothing and tolerance,
- * four (three at the widest smoothing) on 2-D tiles where the batch is too
- * small to fill the device, two on row strips where the size was not tuned.
+ * else whatever is predicted to be the fastest for the batch, two by wavefronts
+ * that march down strips of the level, four (three at the widest smoothing) on
+ * 2-D regions, or the row strips, as tuned or two where the size was not tuned.
  * enable = 0 turns all of that off: every level runs as tuned or set, one
  * iteration per launch otherwise.  The fields are bit-identical either way;
  * the squared update is summed in another order, so a stop on the tolerance
@@ -319,8 +320,8 @@ int ebsd_set_gating(ebsd_handle* h, int32_t chunk_launches);
 
 /* Demons launches of the last registration call per pyramid level, summed
  * over its size buckets (host arrays of EBSD_MAX_LEVELS, either may be NULL):
- * issued[l] were issued, planned[l] is the full sequence to the cap (one or
- * two iterations per launch).  Levels run level-resident count neither. */
+ * issued[l] were issued, planned[l] is the full sequence to the cap (one, two
+ * or four iterations per launch).  Levels run level-resident count neither. */
 int ebsd_get_launch_counts(const ebsd_handle* h, int32_t* issued, int32_t* planned);
 
 /* Strip height used for a pyramid level of level_h x level_w px (levels
