@@ -243,13 +243,15 @@ hipError_t forward(ebsd_cnn* c, int n, int H, int W, float* out, hipStream_t s, 
     CK(conv_fwd(c, 2, n, H, W, c->p1, c->a2a, 64, 0, s));
     if (infer) {
         CK(conv_fwd(c, 3, n, H, W, c->a2a, c->p2, 64, 0, s, 2));
+    } else if (c->fused) {  // kept for the backward pass, and pooled
+        CK(conv_fwd(c, 3, n, H, W, c->a2a, c->e2, 64, 0, s, 3, c->p2, 64));
     } else {
         CK(conv_fwd(c, 3, n, H, W, c->a2a, c->e2, 64, 0, s));
         CK(launch_maxpool(c->e2, n, H1, W1, 64, 64, 0, c->p2, s));
     }
     CK(conv_fwd(c, 4, n, H, W, c->p2, c->a3a, 128, 0, s));
     const bool fuse = infer && c->fused;
-    if (fuse) {  // e3 into channels 256..383 of cat and, pooled, into p3
+    if (c->fused) {  // e3 into channels 256..383 of cat and, pooled, into p3
         CK(conv_fwd(c, 5, n, H, W, c->a3a, c->cat, kCatC, 256, s, 3, c->p3, 128));
     } else {
         CK(conv_fwd(c, 5, n, H, W, c->a3a, c->cat, kCatC, 256, s));  // e3 = channels 256..383 of cat

@@ -1299,7 +1299,15 @@ __global__ void __launch_bounds__(256) k_head_back(const bf16_t* __restrict__ ac
             }
             for (; p < p1; p++) s += bf2f(ac[p * C]) * go[2 * p];
         } else {
-            for (int64_t p = p0; p < p1; p++) s += go[2 * p];
+            int64_t p = p0;
+            for (; p + 16 <= p1; p += 16) {
+                float vg[16];
+#pragma unroll
+                for (int k = 0; k < 16; k++) vg[k] = go[2 * (p + k)];
+#pragma unroll
+                for (int k = 0; k < 16; k++) s += vg[k];
+            }
+            for (; p < p1; p++) s += go[2 * p];
         }
         part[(int64_t)blockIdx.x * ncol + col] = s;
     }
