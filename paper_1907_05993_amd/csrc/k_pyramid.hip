@@ -271,21 +271,51 @@ __device__ inline float restrict_at(const float* __restrict__ in, int H, int W, 
     return (h[0] + 3.0f * h[1] + 3.0f * h[2] + h[3]) / 8.0f;
 }
 
+// A whole level by the workgroups of grid.x.  A thread takes four pixels of a row: inside
+// the image their 16 samples of a row are 10 consecutive ones, three loads (at 4-byte
+// alignment) instead of 16: 2048 patterns of 256 x 256 326 -> 265 us.
+__device__ inline void restrict_image(const float* __restrict__ in, int H, int W, float* __restrict__ out, int h, int w)
+{
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));
+    const int wg = (w + 3) / 4, n = h * wg;
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+        const int j = t / wg, i = 4 * (t - j * wg);
+        if (i < 1 || 2 * i + 8 >= W || j < 1 || 2 * j + 2 >= H) {
+            float o[4];  // all loads in flight
+#pragma unroll
+            for (int k = 0; k < 4; k++) o[k] = restrict_at(in, H, W, j, min(i + k, w - 1));
+#pragma unroll
+            for (int k = 0; k < 4; k++)
+                if (i + k < w) out[j * w + i + k] = o[k];
+            continue;
+        }
+        float v[4][4];
+        const float* row = in + (2 * j - 1) * W + 2 * i - 1;
+#pragma unroll
+        for (int k = 0; k < 4; k++, row += W) {
+            const f4 p = *reinterpret_cast<const f4*>(row), q = *reinterpret_cast<const f4*>(row + 4);
+            const f2 r = *reinterpret_cast<const f2*>(row + 8);
+            const float x[10] = {p[0], p[1], p[2], p[3], q[0], q[1], q[2], q[3], r[0], r[1]};
+#pragma unroll
+            for (int c = 0; c < 4; c++)
+                v[k][c] = (x[2 * c] + 3.0f * x[2 * c + 1] + 3.0f * x[2 * c + 2] + x[2 * c + 3]) / 8.0f;
+        }
+        f4 o;
+#pragma unroll
+        for (int c = 0; c < 4; c++) o[c] = (v[0][c] + 3.0f * v[1][c] + 3.0f * v[2][c] + v[3][c]) / 8.0f;
+        *reinterpret_cast<f4*>(out + j * w + i) = o;
+    }
+}
+
 __global__ void k_restrict_level(const Bucket* __restrict__ bk, int level)
 {
     const int pat = blockIdx.y;
     float* base = pat < bk->nb ? bk->test_pyr + (int64_t)pat * bk->pyr_elems
                                : bk->ref_pyr + (int64_t)(pat - bk->nb) * bk->pyr_elems;
-    const int Hi = bk->lh[level - 1], Wi = bk->lw[level - 1];
-    const int h = bk->lh[level], w = bk->lw[level];
-    const float* in = base + bk->lvl_off[level - 1];
-    float* out = base + bk->lvl_off[level];
     // per-pattern indices fit in 32 bits (sides of at most 16384 px)
-    const int n = h * w;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
-        const int j = t / w, i = t - j * w;
-        out[t] = restrict_at(in, Hi, Wi, j, i);
-    }
+    restrict_image(base + bk->lvl_off[level - 1], bk->lh[level - 1], bk->lw[level - 1], base + bk->lvl_off[level],
+                   bk->lh[level], bk->lw[level]);
 }
 
 __global__ void k_restrict_plain(const float* __restrict__ in, int H, int W,
@@ -293,42 +323,66 @@ __global__ void k_restrict_plain(const float* __restrict__ in, int H, int W,
 {
     const int pat = blockIdx.y;
     const int h = (H + 1) / 2, w = (W + 1) / 2;
-    const float* src = in + (int64_t)pat * H * W;
-    float* dst = out + (int64_t)pat * h * w;
-    const int n = h * w;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
-        const int j = t / w, i = t - j * w;
-        dst[t] = restrict_at(src, H, W, j, i);
-    }
+    restrict_image(in + (int64_t)pat * H * W, H, W, out + (int64_t)pat * h * w, h, w);
 }
 
 // Prolongation u_{l-1}(x) = 2 bilinear(u_l, (x - 0.5)/2): half-pixel centres;
 // the finer level is H2 x W2 (2h x 2w, or one less where it was odd).
-// Output t of the two channels (t < 2 H2 W2, which fits in 32 bits for sides
-// of at most 16384 px).
-__device__ inline void prolong_one(const float* __restrict__ src, int h, int w, int H2, int W2,
-                                   float* __restrict__ dst, int t)
+// A whole field by the workgroups of grid.x.  Outputs 2 m + 1 and 2 m + 2 lie between the
+// coarser samples m and m + 1, at 1/4 and 3/4: a thread takes the eight outputs 4 g .. 4 g + 3
+// of two such rows from eight samples (2 H2 W2 fits in 32 bits for sides of at most 16384
+// px).  Bound: a short kernel's latency; one pair to 1244 x 1024 14.6 us with an output per
+// thread and step, 8.3 now.
+__device__ inline void prolong_image(const float* __restrict__ src, int h, int w, int H2, int W2,
+                                     float* __restrict__ dst)
 {
-    const int hw2 = H2 * W2;
-    const int c = t >= hw2 ? 1 : 0;
-    const int r = t - c * hw2;
-    const int y = r / W2, x = r - y * W2;
-    float sx = ((float)x - 0.5f) * 0.5f, sy = ((float)y - 0.5f) * 0.5f;
-    dst[t] = 2.0f * bilinear_clamped(src + c * h * w, h, w, sx, sy);
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    const int groups = (W2 + 3) / 4, rows = H2 / 2 + 1, n = 2 * rows * groups, hw2 = H2 * W2;
+    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) {
+        const int q = t / groups, g = t - q * groups, c = q >= rows ? 1 : 0, m = q - c * rows - 1;
+        const int x = 4 * g, y = 2 * m + 1;  // outputs x .. x + 3, y and y + 1
+        if (g < 1 || m < 0 || 2 * g + 2 >= w || m + 1 >= h || x + 3 >= W2 || y + 1 >= H2) {
+            float v[8];  // all loads in flight
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const int xx = min(x + (k & 3), W2 - 1), yy = clampi(y + (k >> 2), 0, H2 - 1);
+                v[k] = 2.0f * bilinear_clamped(src + c * h * w, h, w, ((float)xx - 0.5f) * 0.5f, ((float)yy - 0.5f) * 0.5f);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const int xx = x + (k & 3), yy = y + (k >> 2);
+                if (xx < W2 && yy >= 0 && yy < H2) dst[c * hw2 + yy * W2 + xx] = v[k];
+            }
+            continue;
+        }
+        const float* r0 = src + (c * h + m) * w + 2 * g - 1;
+        const f4 a0 = *reinterpret_cast<const f4*>(r0), a1 = *reinterpret_cast<const f4*>(r0 + w);
+        f4 v0, v1, o0, o1;  // along x, then along y
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            const float f = k & 1 ? 0.25f : 0.75f;
+            const int j = (k + 1) >> 1;
+            v0[k] = (1.0f - f) * a0[j] + f * a0[j + 1];
+            v1[k] = (1.0f - f) * a1[j] + f * a1[j + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            o0[k] = 2.0f * (0.75f * v0[k] + 0.25f * v1[k]);
+            o1[k] = 2.0f * (0.25f * v0[k] + 0.75f * v1[k]);
+        }
+        float* d = dst + c * hw2 + y * W2 + x;
+        *reinterpret_cast<f4*>(d) = o0;
+        *reinterpret_cast<f4*>(d + W2) = o1;
+    }
 }
 
 __global__ void k_prolong_level(const Bucket* __restrict__ bk, int level)
 {
     const int b = blockIdx.y;
-    const int h = bk->lh[level], w = bk->lw[level];
-    const int H2 = bk->lh[level - 1], W2 = bk->lw[level - 1];
     const int cur = bk->state[b].cur;
     const int64_t slot = (int64_t)b * 2 * bk->H * bk->W;
-    const float* src = bk->field[cur] + slot;
-    float* dst = bk->field[cur ^ 1] + slot;
-    const int n = 2 * H2 * W2;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-        prolong_one(src, h, w, H2, W2, dst, t);
+    prolong_image(bk->field[cur] + slot, bk->lh[level], bk->lw[level], bk->lh[level - 1], bk->lw[level - 1],
+                  bk->field[cur ^ 1] + slot);
 }
 
 __global__ void k_rearm(const Bucket* __restrict__ bk)
@@ -344,11 +398,7 @@ __global__ void k_rearm(const Bucket* __restrict__ bk)
 __global__ void k_prolong_plain(const float* __restrict__ u, int h, int w, float* __restrict__ out)
 {
     const int b = blockIdx.y;
-    const float* src = u + (int64_t)b * 2 * h * w;
-    float* dst = out + (int64_t)b * 2 * 4 * h * w;
-    const int n = 2 * 4 * h * w;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
-        prolong_one(src, h, w, 2 * h, 2 * w, dst, t);
+    prolong_image(u + (int64_t)b * 2 * h * w, h, w, 2 * h, 2 * w, out + (int64_t)b * 2 * 4 * h * w);
 }
 
 // Reset demons state; coarsest-level field = u_init / 2^(L-1) or zero.
@@ -685,6 +735,11 @@ inline unsigned grid_for(int64_t n, int per_pattern_max = 1024)
     return (unsigned)g;
 }
 
+// Workgroups per pattern of a pass over n patterns: `many` of a large batch, more of a few
+// large patterns, whose threads would otherwise take several pieces in turn (one pair of
+// 1244 x 1024: 1126 -> 1093 us per call, with the borders of prolong_image).
+inline int per_pattern(int many, int64_t n) { return (int)std::max<int64_t>(many, 4096 / n); }
+
 }  // namespace
 
 int64_t stat_chain_doubles(int npat, int64_t n, bool aligned)
@@ -709,10 +764,10 @@ hipError_t launch_pyramids(const Bucket* d_bk, const Bucket& hb, hipStream_t s)
 {
     const int npat = hb.nb + hb.nref;
     int64_t n0 = (int64_t)hb.H * hb.W;
-    hipLaunchKernelGGL(k_normalize_l0, dim3(grid_for((n0 + 3) / 4, 64), npat), dim3(256), 0, s, d_bk);
+    hipLaunchKernelGGL(k_normalize_l0, dim3(grid_for((n0 + 3) / 4, per_pattern(64, npat)), npat), dim3(256), 0, s, d_bk);
     for (int l = 1; l < hb.L; l++) {
         int64_t n = (int64_t)hb.lh[l] * hb.lw[l];
-        hipLaunchKernelGGL(k_restrict_level, dim3(grid_for(n, 64), npat), dim3(256), 0, s, d_bk, l);
+        hipLaunchKernelGGL(k_restrict_level, dim3(grid_for((n + 3) / 4, per_pattern(64, npat)), npat), dim3(256), 0, s, d_bk, l);
     }
     return hipGetLastError();
 }
@@ -727,7 +782,7 @@ hipError_t launch_demons_init(const Bucket* d_bk, const Bucket& hb, hipStream_t 
 hipError_t launch_prolong_level(const Bucket* d_bk, const Bucket& hb, int level, hipStream_t s)
 {
     int64_t n = (int64_t)2 * hb.lh[level - 1] * hb.lw[level - 1];
-    hipLaunchKernelGGL(k_prolong_level, dim3(grid_for(n, 128), hb.nb), dim3(256), 0, s, d_bk, level);
+    hipLaunchKernelGGL(k_prolong_level, dim3(grid_for((n + 7) / 8, per_pattern(64, hb.nb)), hb.nb), dim3(256), 0, s, d_bk, level);
     hipLaunchKernelGGL(k_rearm, dim3((hb.nb + 255) / 256), dim3(256), 0, s, d_bk);
     return hipGetLastError();
 }
@@ -822,7 +877,7 @@ hipError_t launch_zero_iters(const Bucket* d_bk, const Bucket& hb, hipStream_t s
 hipError_t launch_copy_field(const Bucket* d_bk, const Bucket& hb, hipStream_t s)
 {
     int64_t n = (int64_t)2 * hb.H * hb.W / 4;
-    hipLaunchKernelGGL(k_copy_field, dim3(grid_for(n, 64), hb.nb), dim3(256), 0, s, d_bk);
+    hipLaunchKernelGGL(k_copy_field, dim3(grid_for(n / 4, per_pattern(64, hb.nb)), hb.nb), dim3(256), 0, s, d_bk);
     return hipGetLastError();
 }
 

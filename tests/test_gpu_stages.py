@@ -306,3 +306,19 @@ def test_teacher_forced_full_depth(E, orc):
             assert d <= 1e-4, (k, d)
         u = un
     print("teacher-forced worst per-step |du| difference: %.2e px" % worst)
+
+
+# four outputs per thread: sizes around one and two groups, no interior group, a last group
+# of one to three; tolerances of the cases above
+@pytest.mark.parametrize("H,W", [(2, 2), (3, 9), (7, 10), (9, 16), (10, 17), (33, 19), (64, 35), (40, 131)])
+def test_restrict_and_prolong_group_edges(E, orc, H, W):
+    print(f"case: restriction and prolongation {H}x{W}", flush=True)
+    x = rng(31).normal(size=(3, H, W)).astype(np.float32)
+    out = E.stage_restrict(cuda(x)).cpu().numpy()
+    for i in range(3):
+        np.testing.assert_allclose(out[i], orc.restrict(x[i].astype(np.float64)), atol=1e-6)
+    for h, w in ((H, W), (1, W), (H, 1)):
+        u = rng(32).normal(size=(2, 2, h, w)).astype(np.float32)
+        out = E.stage_prolong(cuda(u)).cpu().numpy()
+        for i in range(2):
+            np.testing.assert_allclose(out[i], orc.prolong(u[i].astype(np.float64)), atol=2e-6)
