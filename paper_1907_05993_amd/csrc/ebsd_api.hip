@@ -889,41 +889,57 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         }
         return EBSD_OK;
     };
-    auto run_range = [&](int l, int a, int e) -> int {
-        if (h->graphs && e > a) {
-            std::ostringstream key;
-            key << H << ' ' << W << ' ' << nb << ' ' << nref << ' ' << l << ' ' << p.max_iters[l]
-                << ' ' << p.tol_px << ' ' << h->radius << ' ' << (int)plan[l].kind << ' ' << plan[l].rows << ' ' << a
-                << ' ' << e
-                << ' ' << (void*)base;
-            auto it = h->graph_cache.find(key.str());
-            hipGraphExec_t exec = nullptr;
-            if (it != h->graph_cache.end()) {
-                exec = it->second;
-            } else {
-                if (!h->cap_stream &&
-                    hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
-                    h->cap_stream = nullptr;
-                hipGraph_t graph = nullptr;
-                std::shared_lock<std::shared_mutex> cap_lk(capture_mutex());
-                if (h->cap_stream &&
-                    hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
-                    const int e2 = launch_range(l, a, e, h->cap_stream);
-                    const hipError_t ec = hipStreamEndCapture(h->cap_stream, &graph);
-                    if (e2 == EBSD_OK && ec == hipSuccess && graph &&
-                        hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess)
-                        exec = nullptr;
-                    if (graph) (void)hipGraphDestroy(graph);
-                }
-                (void)hipGetLastError();
-                h->graph_cache[key.str()] = exec;  // nullptr: this configuration runs eagerly
-            }
-            if (exec) {
-                EBSD_TRY(hipGraphLaunch(exec, s));
-                return EBSD_OK;
-            }
+    // Issues fn's launches on s: the first time one by one, and captured for the next time while
+    // the device works on them; then as a graph (nullptr in the cache: not capturable).
+    auto run_graph = [&](const std::string& key, auto&& fn) -> int {
+        const auto it = h->graphs ? h->graph_cache.find(key) : h->graph_cache.end();
+        if (it != h->graph_cache.end() && it->second) {
+            EBSD_TRY(hipGraphLaunch(it->second, s));
+            return EBSD_OK;
         }
-        return launch_range(l, a, e, s);
+        const int r = fn(s);
+        if (r || !h->graphs || it != h->graph_cache.end()) return r;
+        if (!h->cap_stream && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
+            h->cap_stream = nullptr;
+        hipGraph_t graph = nullptr;
+        hipGraphExec_t exec = nullptr;
+        std::shared_lock<std::shared_mutex> cap_lk(capture_mutex());
+        if (h->cap_stream && hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
+            const int e2 = fn(h->cap_stream);
+            const hipError_t ec = hipStreamEndCapture(h->cap_stream, &graph);
+            if (e2 == EBSD_OK && ec == hipSuccess && graph &&
+                hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess)
+                exec = nullptr;
+            if (graph) (void)hipGraphDestroy(graph);
+        }
+        (void)hipGetLastError();
+        h->graph_cache[key] = exec;
+        return EBSD_OK;
+    };
+    auto level_key = [&](int l, int a, int e) {
+        std::ostringstream key;
+        key << H << ' ' << W << ' ' << nb << ' ' << nref << ' ' << l << ' ' << p.max_iters[l]
+            << ' ' << p.tol_px << ' ' << h->radius << ' ' << (int)plan[l].kind << ' ' << plan[l].rows << ' ' << a
+            << ' ' << e
+            << ' ' << (void*)base;
+        return key.str();
+    };
+    auto run_range = [&](int l, int a, int e) -> int {
+        if (e <= a) return EBSD_OK;
+        return run_graph(level_key(l, a, e), [&](hipStream_t st) { return launch_range(l, a, e, st); });
+    };
+    auto resident = [&](int l) {
+        // one workgroup per pair and CU, at any batch size: 64 x 64 px take 2.1 us per
+        // iteration and round of 256 pairs (8.5 us for 1024 pairs), the row kernels
+        // 16 us for one pair and 27 us for 1024 (two iterations per launch)
+        return h->resident && demons_resident_ok(b.lh[l], b.lw[l]);
+    };
+    // what follows a level's iterations: its end and the next finer level's field
+    auto finish_level = [&](int l, hipStream_t st) -> int {
+        if (!resident(l))
+            EBSD_TRY(launch_level_end(d_bk, b, l, p.max_iters[l], p.tol_px, plan[l].units, plan[l].per_launch, st));
+        if (l > 0) EBSD_TRY(launch_prolong_level(d_bk, b, l, st));
+        return EBSD_OK;
     };
     // gating needs a stream the host may wait on: not while the caller captures it
     bool gate = p.tol_px > 0.0f && h->gate_chunk > 0 && mode == Mode::Full;
@@ -1002,22 +1018,47 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         EBSD_TRY(launch_solve_first(d_bk, b, 0.0f, s));
     } else if (mode == Mode::Full) {
         EBSD_TRY(launch_demons_init(d_bk, b, s));
-        for (int l = L - 1; l >= 0; l--) {
-            // one workgroup per pair and CU, at any batch size: 64 x 64 px take 2.1 us per
-            // iteration and round of 256 pairs (8.5 us for 1024 pairs), the row kernels
-            // 16 us for one pair and 27 us for 1024 (two iterations per launch)
-            const bool res = h->resident && demons_resident_ok(b.lh[l], b.lw[l]);
+        // Levels of which every launch is issued, in one graph with what lies between them
+        // (each graph and each launch beside one costs 7 to 9 us of idle device: one pair of
+        // 1244 x 1024 1085 us with a graph per level, 1047 with one); with timing events, or
+        // where the host gates a level's launches, level by level.
+        bool whole = !tm;
+        for (int l = 0; l < L; l++)
+            whole = whole && (resident(l) || !gate || n_launches(l) <= h->gate_chunk);
+        if (whole) {
+            std::string key = "levels";
+            for (int l = L - 1; l >= 0; l--) {
+                const int nl = resident(l) ? 0 : n_launches(l);
+                key += " / " + level_key(l, resident(l) ? -1 : 0, nl);
+                h->launches_planned[l] += nl;
+                h->launches_issued[l] += nl;
+            }
+            const int e = run_graph(key, [&](hipStream_t st) -> int {
+                for (int l = L - 1; l >= 0; l--) {
+                    if (resident(l)) {
+                        EBSD_TRY(launch_demons_resident(d_bk, b, l, h->taps, h->radius, p.tol_px, p.max_iters[l], st));
+                    } else {
+                        const int r = launch_range(l, 0, n_launches(l), st);
+                        if (r) return r;
+                    }
+                    const int r = finish_level(l, st);
+                    if (r) return r;
+                }
+                return EBSD_OK;
+            });
+            if (e) return e;
+        }
+        for (int l = L - 1; l >= 0 && !whole; l--) {
             if (tm) EBSD_TRY(hipEventRecord(h->ev[2 + 2 * l], s));
-            if (res) {
+            if (resident(l)) {
                 EBSD_TRY(launch_demons_resident(d_bk, b, l, h->taps, h->radius, p.tol_px, p.max_iters[l], s));
             } else {
                 const int e = run_level(l);
                 if (e) return e;
             }
             if (tm) EBSD_TRY(hipEventRecord(h->ev[3 + 2 * l], s));
-            if (!res)
-                EBSD_TRY(launch_level_end(d_bk, b, l, p.max_iters[l], p.tol_px, plan[l].units, plan[l].per_launch, s));
-            if (l > 0) EBSD_TRY(launch_prolong_level(d_bk, b, l, s));
+            const int e = finish_level(l, s);
+            if (e) return e;
         }
         EBSD_TRY(launch_sample_q1(d_bk, b, s));
         if (want_ssim) EBSD_TRY(launch_ssim(d_bk, b, s));

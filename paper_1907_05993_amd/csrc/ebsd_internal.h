@@ -225,11 +225,11 @@ __host__ __device__ inline void march_seg(int seg, int nsegs, int w, int c, int 
 // be pinned host memory mapped into the device's address space).
 hipError_t launch_count_active(const Bucket* d_bk, int32_t* out, hipStream_t s);
 // Close level l: iteration counts, convergence of the last iteration, final
-// buffer.  per_launch: iterations per launch the level ran with; units: partial
+// buffer, and the state for the next level.  per_launch: iterations per launch the level ran with; units: partial
 // sums per pair and iteration.
 hipError_t launch_level_end(const Bucket* d_bk, const Bucket& hb, int level, int cap, float tol,
                             int units, int per_launch, hipStream_t s);
-// Prolong the field of every pair from level l to level l-1 and re-arm the pairs.
+// Prolong the field of every pair from level l to level l-1.
 hipError_t launch_prolong_level(const Bucket* d_bk, const Bucket& hb, int level, hipStream_t s);
 // Sample the finest field at the ROI centres -> q1.
 hipError_t launch_sample_q1(const Bucket* d_bk, const Bucket& hb, hipStream_t s);

@@ -211,6 +211,7 @@ __global__ void k_level_end(const Bucket* __restrict__ bk, int level, int cap, f
     }
     bk->iters[(int64_t)b * bk->L + level] = n;
     st.cur = (st.base + (n + per_launch - 1) / per_launch) & 1;
+    st.base = st.cur ^ 1;  // where the next level's field is prolonged to
     st.stop = -1;
     bk->state[b] = st;
 }

@@ -114,6 +114,7 @@ __global__ void __launch_bounds__(kResThreads)
     if (threadIdx.x == 0) {
         bk->iters[(int64_t)b * bk->L + level] = k;
         st.cur = (st.base + k) & 1;
+        st.base = st.cur ^ 1;  // where the next level's field is prolonged to
         st.stop = -1;
         if (conv) st.convmask |= 1u << level;
         bk->state[b] = st;

@@ -385,16 +385,6 @@ __global__ void k_prolong_level(const Bucket* __restrict__ bk, int level)
                   bk->field[cur ^ 1] + slot);
 }
 
-__global__ void k_rearm(const Bucket* __restrict__ bk)
-{
-    int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= bk->nb) return;
-    PairState st = bk->state[b];
-    st.base = st.cur ^ 1;  // the prolonged field was written to the other buffer
-    st.stop = -1;
-    bk->state[b] = st;
-}
-
 __global__ void k_prolong_plain(const float* __restrict__ u, int h, int w, float* __restrict__ out)
 {
     const int b = blockIdx.y;
@@ -783,7 +773,6 @@ hipError_t launch_prolong_level(const Bucket* d_bk, const Bucket& hb, int level,
 {
     int64_t n = (int64_t)2 * hb.lh[level - 1] * hb.lw[level - 1];
     hipLaunchKernelGGL(k_prolong_level, dim3(grid_for((n + 7) / 8, per_pattern(64, hb.nb)), hb.nb), dim3(256), 0, s, d_bk, level);
-    hipLaunchKernelGGL(k_rearm, dim3((hb.nb + 255) / 256), dim3(256), 0, s, d_bk);
     return hipGetLastError();
 }
 
