@@ -458,7 +458,8 @@ __device__ void wave_gn_terms(const double (&f)[9], int n, WaveSolveLds& L)
 __device__ void wave_gather(const WaveTask& w, int n, WaveSolveLds& L, double (&A)[8][8], double (&r)[8])
 {
     double acc = 0.0;
-#pragma unroll 4
+    // 64 reads in flight: 101 ROIs of one pair 69 -> 63 us per solve (16 in flight before)
+#pragma unroll 16
     for (int i = 0; i < n; i++) acc += L.tab[w.au][i] * L.tab[w.bu][i] + L.tab[w.av][i] * L.tab[w.bv][i];
     if (threadIdx.x < 36) {
         L.M[w.a][w.c] = acc;
