@@ -178,14 +178,25 @@ bool alloc_backward(ebsd_cnn* c)
     return ok;
 }
 
+PackArgs one_layer(const float* w, int cin, int cout, bf16_t* fwd, bf16_t* dgr)
+{
+    PackArgs a;
+    a.n = 1;
+    a.layer[0] = {w, fwd, dgr, cin, cin, cout};
+    return a;
+}
+
 hipError_t pack_weights(ebsd_cnn* c, hipStream_t s)
 {
     if (c->packed) return hipSuccess;
+    PackArgs a;
+    a.n = 10;
     for (int l = 0; l < 10; l++) {
         const LayerDef& d = kLayers[l];
-        hipError_t e = launch_pack_weights(c->params + c->off_w[l], d.cin, d.cinp, d.cout, c->wf[l], c->wd[l], s);
-        if (e != hipSuccess) return e;
+        a.layer[l] = {c->params + c->off_w[l], c->wf[l], c->wd[l], d.cin, d.cinp, d.cout};
     }
+    const hipError_t e = launch_pack_weights(a, s);
+    if (e != hipSuccess) return e;
     c->packed = true;
     return hipSuccess;
 }
@@ -355,8 +366,7 @@ int normalize_pack(ebsd_cnn* c, const float* ref, const float* test, int n, int 
     const int64_t hw = (int64_t)H * W;
     float* nr = c->norm;
     float* nt = c->norm + (int64_t)c->max_batch * kPixPerPair;
-    if (launch_stage_normalize(ref, n, hw, nr, nullptr, s) != hipSuccess) return EBSD_EDEVICE;
-    if (launch_stage_normalize(test, n, hw, nt, nullptr, s) != hipSuccess) return EBSD_EDEVICE;
+    if (launch_normalize_pairs(ref, test, n, hw, nr, nt, s) != hipSuccess) return EBSD_EDEVICE;
     if (launch_pack_input(nr, hw, nullptr, nt, hw, n, H, W, c->x0, s) != hipSuccess) return EBSD_EDEVICE;
     return EBSD_OK;
 }
@@ -663,7 +673,7 @@ int ebsd_stage_conv3x3(const uint16_t* x, int32_t n, int32_t H, int32_t W, int32
     DeviceWideLock lk(capture_mutex());
     TempBuf wf;
     if (hipMalloc(&wf.p, sizeof(bf16_t) * 9 * Cin * Cout) != hipSuccess) return EBSD_ENOMEM;
-    if (launch_pack_weights(w, Cin, Cin, Cout, static_cast<bf16_t*>(wf.p), nullptr, s) != hipSuccess)
+    if (launch_pack_weights(one_layer(w, Cin, Cout, static_cast<bf16_t*>(wf.p), nullptr), s) != hipSuccess)
         return EBSD_EDEVICE;
     ConvArgs a;
     a.x = x;
@@ -693,7 +703,7 @@ int ebsd_stage_conv3x3_dgrad(const uint16_t* dz, int32_t n, int32_t H, int32_t W
     if (hipMalloc(&wf.p, sizeof(bf16_t) * 9 * Cin * Cout) != hipSuccess ||
         hipMalloc(&wd.p, sizeof(bf16_t) * 9 * Cin * Cout) != hipSuccess)
         return EBSD_ENOMEM;
-    if (launch_pack_weights(w, Cin, Cin, Cout, static_cast<bf16_t*>(wf.p), static_cast<bf16_t*>(wd.p), s) !=
+    if (launch_pack_weights(one_layer(w, Cin, Cout, static_cast<bf16_t*>(wf.p), static_cast<bf16_t*>(wd.p)), s) !=
         hipSuccess)
         return EBSD_EDEVICE;
     ConvArgs a;

@@ -127,9 +127,19 @@ int head_blocks(int64_t P);
 hipError_t launch_head_back(const bf16_t* act, const float* gout, int64_t P, int C, float* part, hipStream_t s);
 // Weight packing from fp32 HWIO masters [3][3][cin][cout]:
 // fwd[co][t][ci] (ci < cin_pad, zero beyond cin) and, if dgr != NULL, the
-// flipped transpose dgr[ci][t][co] = w[8 - t][ci][co].
-hipError_t launch_pack_weights(const float* w, int cin, int cin_pad, int cout, bf16_t* fwd,
-                               bf16_t* dgr, hipStream_t s);
+// flipped transpose dgr[ci][t][co] = w[8 - t][ci][co].  All layers in one launch (ten
+// launches of 3 to 7 us, which a training step issues after every update, took 110 us with
+// their gaps, this one 15).
+struct PackLayer {
+    const float* w;
+    bf16_t *fwd, *dgr;
+    int32_t cin, cin_pad, cout;
+};
+struct PackArgs {
+    int32_t n;
+    PackLayer layer[10];
+};
+hipError_t launch_pack_weights(const PackArgs& a, hipStream_t s);
 // Adam (fp32): m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2; p -= lr mhat / (sqrt(vhat) + eps).
 hipError_t launch_adam(float* p, const float* g, float* m, float* v, int64_t n, float lr, float b1,
                        float b2, float eps, float bc1, float bc2, hipStream_t s);

@@ -304,6 +304,10 @@ hipError_t launch_solve_second(const Bucket* d_bk, const Bucket& hb, int second_
 // ---- stage launchers -----------------------------------------------------------
 hipError_t launch_stage_normalize(const float* in, int n, int64_t elems, float* out,
                                   uint32_t* flags, hipStream_t s);
+// The same of two sets of n patterns in one launch (one set of up to 256 patterns leaves CUs idle:
+// two of 64 patterns of 256 x 256 33 + 28 us, 33 together).
+hipError_t launch_normalize_pairs(const float* a, const float* b, int n, int64_t elems, float* out_a, float* out_b,
+                                  hipStream_t s);
 hipError_t launch_stage_restrict(const float* in, int n, int H, int W, float* out, hipStream_t s);
 hipError_t launch_stage_demons_iter(const float* R, const float* T, int n, int H, int W,
                                     const float* u_in, const float* taps, int radius,

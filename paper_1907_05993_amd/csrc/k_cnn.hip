@@ -6,6 +6,8 @@
 // supplies row l % 32 of A with the 8 consecutive k values 8 (l / 32) .. +7,
 // and column l % 32 of B with the same 8 k values; it receives the 16
 // accumulator values C[8 (i / 4) + 4 (l / 32) + i % 4][l % 32], i = 0..15.
+#include <algorithm>
+
 #include "cnn_internal.h"
 #include "dev_util.h"
 
@@ -1313,9 +1315,13 @@ __global__ void __launch_bounds__(256) k_head_back(const bf16_t* __restrict__ ac
     }
 }
 
-__global__ void k_pack_weights(const float* __restrict__ w, int cin, int cin_pad, int cout,
-                               bf16_t* __restrict__ fwd, bf16_t* __restrict__ dgr)
+__global__ void k_pack_weights(PackArgs a)
 {
+    const PackLayer& l = a.layer[blockIdx.y];
+    const float* __restrict__ w = l.w;
+    bf16_t* __restrict__ fwd = l.fwd;
+    bf16_t* __restrict__ dgr = l.dgr;
+    const int cin = l.cin, cin_pad = l.cin_pad, cout = l.cout;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nf = (int64_t)cout * 9 * cin_pad;
     if (i < nf) {
@@ -1536,12 +1542,13 @@ hipError_t launch_head_back(const bf16_t* act, const float* gout, int64_t P, int
     return hipGetLastError();
 }
 
-hipError_t launch_pack_weights(const float* w, int cin, int cin_pad, int cout, bf16_t* fwd,
-                               bf16_t* dgr, hipStream_t s)
+hipError_t launch_pack_weights(const PackArgs& a, hipStream_t s)
 {
-    const int64_t nf = (int64_t)cout * 9 * cin_pad, nd = (int64_t)cin * 9 * cout;
-    const int64_t n = nf > nd ? nf : nd;
-    hipLaunchKernelGGL(k_pack_weights, dim3(blocks_for(n, 256)), dim3(256), 0, s, w, cin, cin_pad, cout, fwd, dgr);
+    if (a.n < 1 || a.n > 10) return hipErrorInvalidValue;
+    int64_t n = 0;
+    for (int l = 0; l < a.n; l++)
+        n = std::max({n, (int64_t)a.layer[l].cout * 9 * a.layer[l].cin_pad, (int64_t)a.layer[l].cin * 9 * a.layer[l].cout});
+    hipLaunchKernelGGL(k_pack_weights, dim3(blocks_for(n, 256), a.n), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

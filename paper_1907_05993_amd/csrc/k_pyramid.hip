@@ -688,14 +688,14 @@ __global__ void k_copy_field(const Bucket* __restrict__ bk)
 // Stand-alone normalisation: one block per pattern computes the statistics
 // and writes the normalised pattern.
 __global__ void __launch_bounds__(kStatThreads)
-    k_stage_norm(const float* __restrict__ in, int64_t elems, float* __restrict__ out,
-                 uint32_t* __restrict__ flags)
+    k_stage_norm(const float* __restrict__ in, const float* __restrict__ in2, int64_t elems, float* __restrict__ out,
+                 float* __restrict__ out2, uint32_t* __restrict__ flags)
 {
     __shared__ double sh[kStatThreads];
     __shared__ PatStat st;
     const int p = blockIdx.x;
-    const float* src = in + (int64_t)p * elems;
-    float* dst = out + (int64_t)p * elems;
+    const float* src = (blockIdx.y ? in2 : in) + (int64_t)p * elems;
+    float* dst = (blockIdx.y ? out2 : out) + (int64_t)p * elems;
     pattern_stats(src, elems, &st, sh);
     __syncthreads();
     const PatStat s = st;
@@ -873,7 +873,14 @@ hipError_t launch_copy_field(const Bucket* d_bk, const Bucket& hb, hipStream_t s
 hipError_t launch_stage_normalize(const float* in, int n, int64_t elems, float* out,
                                   uint32_t* flags, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_stage_norm, dim3(n), dim3(kStatThreads), 0, s, in, elems, out, flags);
+    hipLaunchKernelGGL(k_stage_norm, dim3(n), dim3(kStatThreads), 0, s, in, nullptr, elems, out, nullptr, flags);
+    return hipGetLastError();
+}
+
+hipError_t launch_normalize_pairs(const float* a, const float* b, int n, int64_t elems, float* out_a, float* out_b,
+                                  hipStream_t s)
+{
+    hipLaunchKernelGGL(k_stage_norm, dim3(n, 2), dim3(kStatThreads), 0, s, a, b, elems, out_a, out_b, nullptr);
     return hipGetLastError();
 }
 
