@@ -110,7 +110,7 @@ __device__ inline void taps_h(float2* rows, unsigned rb, const Taps& tp, float& 
 // other R rows and the u rows of the last 2r + 1 steps stay in registers.
 // Row offsets are uniform (scalar offset operands of the buffer accesses).
 // Returns the workgroup's sum of |u_new - u|^2 (all threads) when want_ss.
-template <int NW, int RAD, int TY, bool ONE = false>
+template <int NW, int RAD, int TY, bool LARGE, bool ONE = false>
 __device__ float demons_strip(const float* __restrict__ Rg, const float* __restrict__ Tg,
                               const float* __restrict__ ug, float* __restrict__ ung, int h, int w,
                               int y0, int sx0, int ws, int we, const Taps& tp, bool want_ss)
@@ -130,7 +130,7 @@ __device__ float demons_strip(const float* __restrict__ Rg, const float* __restr
     const int x = clampi(gx, 0, w - 1);
     const int xm = max(x - 1, 0), xp = min(x + 1, w - 1);
     const float sx = (xp - xm == 2) ? 0.5f : 1.0f;
-    const BilGeom gg = bil_geom(h, w);
+    const BilGeomOf<LARGE> gg = bil_geom<LARGE>(h, w);
     const unsigned uw4 = 4u * (unsigned)w;
     const unsigned x4 = 4u * (unsigned)x;
     // byte offset of channel 1 of the field
@@ -280,11 +280,11 @@ __device__ __forceinline__ void static_for(F&& f)
 }
 
 // Loop-invariant context of demons_strip2.
-template <int NW, int RAD>
+template <int NW, int RAD, bool LARGE>
 struct Strip2Ctx {
     __amdgpu_buffer_rsrc_t R, U, UN;
     GatherBase T;
-    BilGeom gg;
+    BilGeomOf<LARGE> gg;
     unsigned uw4, x4, ch1;
     int c, gx, x, h, w, y0;
     bool in, want_ss;
@@ -321,8 +321,9 @@ struct Strip2State {
 // compile-time in every phase of the march, so the ring slots are fixed
 // registers and no state is merged across branches.  The prefetches of a
 // stage's last step are issued anyway (clamped rows, always inside the image).
-template <int NW, int RAD, int TY, int SL1, int SL2, bool DO1, bool DO2, bool OUT1, bool OUT2, bool INIT2>
-__device__ __forceinline__ void strip2_step(const Strip2Ctx<NW, RAD>& k, const Taps& tp, Strip2State<RAD>& st,
+template <int NW, int RAD, int TY, int SL1, int SL2, bool DO1, bool DO2, bool OUT1, bool OUT2, bool INIT2,
+          bool LARGE>
+__device__ __forceinline__ void strip2_step(const Strip2Ctx<NW, RAD, LARGE>& k, const Taps& tp, Strip2State<RAD>& st,
                                             int S)
 {
     constexpr int NR = 2 * RAD + 1;
@@ -473,7 +474,7 @@ __device__ __forceinline__ void strip2_step(const Strip2Ctx<NW, RAD>& k, const T
     st.oth2 = t;
 }
 
-template <int NW, int RAD, int TY>
+template <int NW, int RAD, int TY, bool LARGE>
 __device__ float2 demons_strip2(const float* __restrict__ Rg, const float* __restrict__ Tg,
                                 const float* __restrict__ ug, float* __restrict__ ung, int h, int w,
                                 int y0, int sx0, int ws, int we, const Taps& tp, bool want_ss)
@@ -494,7 +495,7 @@ __device__ float2 demons_strip2(const float* __restrict__ Rg, const float* __res
     __shared__ StripRows<NW, RAD> L1, L2;
     __shared__ float2 hist[NH][RW];
     __shared__ float red[2][NW];
-    Strip2Ctx<NW, RAD> k;
+    Strip2Ctx<NW, RAD, LARGE> k;
     const unsigned img_bytes = 4u * (unsigned)h * (unsigned)w;
     k.R = make_rsrc(Rg, img_bytes);
     k.T = gather_base(Tg, h, w);
@@ -510,7 +511,7 @@ __device__ float2 demons_strip2(const float* __restrict__ Rg, const float* __res
     k.want_ss = want_ss;
     const int xm = max(k.x - 1, 0), xp = min(k.x + 1, w - 1);
     k.sx = (xp - xm == 2) ? 0.5f : 1.0f;
-    k.gg = bil_geom(h, w);
+    k.gg = bil_geom<LARGE>(h, w);
     k.uw4 = 4u * (unsigned)w;
     k.x4 = 4u * (unsigned)k.x;
     k.ch1 = img_bytes;
@@ -605,7 +606,8 @@ __device__ float2 demons_strip2(const float* __restrict__ Rg, const float* __res
 }
 
 // SEG: the level is cut into column segments (levels wider than 64 NW px);
-// without it nsegs is 1 and every lane's column is its index.
+// without it nsegs is 1 and every lane's column is its index.  Only such levels
+// can have more than kMaxFp32Pixels pixels.
 template <int NW, int RAD, int TY, bool SEG>
 __global__ void __launch_bounds__(64 * NW)
     k_demons_rows(const Bucket* __restrict__ bk, int level, int k, Taps tp, float tol, int nstrips, int nsegs_arg)
@@ -642,7 +644,7 @@ __global__ void __launch_bounds__(64 * NW)
     float* un = bk->field[(st.base + k + 1) & 1] + slot;
     int sx0 = 0, ws = 0, we = w;
     if constexpr (SEG) rows_seg_cols(seg, nsegs, w, NW, sx0, ws, we);
-    const float ss = demons_strip<NW, RAD, TY>(R, T, u, un, h, w, strip * TY, sx0, ws, we, tp, tol > 0.0f);
+    const float ss = demons_strip<NW, RAD, TY, SEG>(R, T, u, un, h, w, strip * TY, sx0, ws, we, tp, tol > 0.0f);
     if (tol > 0.0f && threadIdx.x == 0)
         bk->partial[(k & 1) * npart + (int64_t)b * bk->max_tiles + unit] = ss;
 }
@@ -714,18 +716,18 @@ __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(3)
             bk->state[b].stop = k - 1;
             bk->state[b].convmask = st.convmask | (1u << level);
         }
-        demons_strip<NW, RAD, TY>(R, T, fb, fa, h, w, strip * TY, sx0, ws, we, tp, false);
+        demons_strip<NW, RAD, TY, SEG>(R, T, fb, fa, h, w, strip * TY, sx0, ws, we, tp, false);
         return;
     }
     if (k >= cap) return;
     if (k + 1 < cap) {
-        const float2 ss = demons_strip2<NW, RAD, TY>(R, T, fa, fb, h, w, strip * TY, sx0, ws, we, tp, tol > 0.0f);
+        const float2 ss = demons_strip2<NW, RAD, TY, SEG>(R, T, fa, fb, h, w, strip * TY, sx0, ws, we, tp, tol > 0.0f);
         if (tol > 0.0f && threadIdx.x == 0) {
             bk->partial[(k & 3) * npart + pofs + unit] = ss.x;
             bk->partial[((k + 1) & 3) * npart + pofs + unit] = ss.y;
         }
     } else {
-        const float ss = demons_strip<NW, RAD, TY>(R, T, fa, fb, h, w, strip * TY, sx0, ws, we, tp, tol > 0.0f);
+        const float ss = demons_strip<NW, RAD, TY, SEG>(R, T, fa, fb, h, w, strip * TY, sx0, ws, we, tp, tol > 0.0f);
         if (tol > 0.0f && threadIdx.x == 0) bk->partial[(k & 3) * npart + pofs + unit] = ss;
     }
 }
@@ -741,7 +743,7 @@ __global__ void __launch_bounds__(64 * NW)
     const int64_t hw = (int64_t)h * w;
     double acc = 0.0;
     for (int y0 = 0; y0 < h; y0 += TY)
-        acc += (double)demons_strip<NW, RAD, TY, ONE>(R + b * hw, T + b * hw, u + 2 * b * hw,
+        acc += (double)demons_strip<NW, RAD, TY, false, ONE>(R + b * hw, T + b * hw, u + 2 * b * hw,
                                                        un + 2 * b * hw, h, w, y0, 0, 0, w, tp, true);
     if (rms && threadIdx.x == 0) rms[b] = sqrt(acc / (double)hw);
 }

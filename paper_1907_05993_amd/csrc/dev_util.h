@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cell_index.h"
 #include "ebsd_internal.h"
 
 namespace ebsd {
@@ -120,20 +121,29 @@ __device__ inline Bilin bilinear_issue(__amdgpu_buffer_rsrc_t img, int h, int w,
     b.v11 = bload(img, o + dy + dx);
     return b;
 }
-// Per-level constants of the bilinear gather below.
-struct BilGeom {
+// Per-level constants of the bilinear gather below.  LARGE: the level may have
+// more than kMaxFp32Pixels pixels, so that a pixel index needs whole numbers
+// (cell_index.h): one instruction more per gather (1024 warm pairs of 256 x 256
+// 68.4 -> 69.5 ms, 192 pairs of 400 x 400 37.7 -> 38.3 ms with it), which the
+// kernels of levels up to that size do without.
+template <bool LARGE>
+struct BilGeomOf {
     float wm1, hm1;   // last column / row
     float wm2, hm2;   // largest left / top corner: max(w - 2, 0), max(h - 2, 0)
     float wf;         // row length
+    unsigned w4;      // row bytes
 };
-__device__ inline BilGeom bil_geom(int h, int w)
+typedef BilGeomOf<false> BilGeom;
+template <bool LARGE = false>
+__device__ inline BilGeomOf<LARGE> bil_geom(int h, int w)
 {
-    BilGeom g;
+    BilGeomOf<LARGE> g;
     g.wm1 = (float)(w - 1);
     g.hm1 = (float)(h - 1);
     g.wm2 = (float)max(w - 2, 0);
     g.hm2 = (float)max(h - 2, 0);
     g.wf = (float)w;
+    g.w4 = 4u * (unsigned)w;
     return g;
 }
 // Gather half of a bilinear sample whose 2 x 2 cell always lies inside the
@@ -141,12 +151,11 @@ __device__ inline BilGeom bil_geom(int h, int w)
 // [0, w-2] x [0, h-2], so a sample on the last column or row takes weight 1
 // on the far corner instead of weight 0 on a neighbour outside; blended with
 // lerp_ends (exact at both weights 0 and 1), it returns that pixel exactly.
-// One vector offset (y0 w + x0 < 2^24 is exact in the fma); the two pixels of
-// a cell's row are one 8-byte load at 4-byte alignment, which halves the
-// gather instructions of a pixel (the vector memory unit's address rate is
-// part of what a row step of the demons kernels waits on: 1024 warm-started
-// pairs of 256 x 256, 3 x 150 iterations, 81.5 -> 75.9 ms with the 8-byte
-// loads; 192 pairs of 400 x 400 52.0 -> 48.8 ms).
+// One vector offset (up to kMaxFp32Pixels y0 w + x0 is exact in the fma); the two
+// pixels of a cell's row are one 8-byte load at 4-byte alignment, which halves the gather instructions of a pixel (the vector
+// memory unit's address rate is part of what a row step of the demons kernels
+// waits on: 1024 warm-started pairs of 256 x 256, 3 x 150 iterations, 81.5 ->
+// 75.9 ms with the 8-byte loads; 192 pairs of 400 x 400 52.0 -> 48.8 ms).
 // `img` and `below` (img plus a row; img itself for one row) are uniform.
 // ONE: the image is one pixel wide, both pixels of a row are the same one.
 typedef float f32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
@@ -162,8 +171,8 @@ __device__ inline GatherBase gather_base(const float* img, int h, int w)
     b.below = (const EBSD_GLOBAL char*)(h > 1 ? p + w : p);
     return b;
 }
-template <bool ONE = false>
-__device__ inline Bilin bilinear_issue_g(const GatherBase& img, const BilGeom& g, float x, float y)
+template <bool ONE = false, bool LARGE>
+__device__ inline Bilin bilinear_issue_g(const GatherBase& img, const BilGeomOf<LARGE>& g, float x, float y)
 {
     Bilin b;
     const float xc = fminf(fmaxf(x, 0.0f), g.wm1);
@@ -171,7 +180,7 @@ __device__ inline Bilin bilinear_issue_g(const GatherBase& img, const BilGeom& g
     const float xf = fminf(floorf(xc), g.wm2), yf = fminf(floorf(yc), g.hm2);
     b.fx = xc - xf;
     b.fy = yc - yf;
-    const unsigned o = 4u * (unsigned)fmaf(yf, g.wf, xf);
+    const unsigned o = LARGE ? cell_offset(xf, yf, g.w4) : 4u * (unsigned)fmaf(yf, g.wf, xf);
     if (ONE) {
         b.v00 = b.v01 = *(const EBSD_GLOBAL float*)(img.img + o);
         b.v10 = b.v11 = *(const EBSD_GLOBAL float*)(img.below + o);

@@ -151,13 +151,13 @@ int default_fused_ty(int lh, int lw, int nb, int radius)
 // 0.5 % more than the fastest one on average and 38 % at worst.
 
 // Region rows (32, 64 or 80) of the tile kernels for nb levels of lh x lw px (0: no
-// tile kernel at this radius).  Regions of 64 and 80 rows (these twice as wide) run
+// tile kernel at this radius or level size).  Regions of 64 and 80 rows (these twice as wide) run
 // in rounds of one per compute unit: at radius 3 64 rows 4.0 us up to 256 regions,
 // 7.1 up to 512, 13 for 1024, 29 for 2560; 80 rows 9.0, 16.6, 31, 78.  Those of 32
 // rows overlap: 256 regions 3.1, 1024 6.9, 4096 22.
 int tile_rows_for(int lh, int lw, int nb, int radius, double& us)
 {
-    if (!tile_iters(radius, 32)) return 0;
+    if (!tile_iters(radius, 32) || (int64_t)lh * lw > kMaxFp32Pixels) return 0;
     const auto regions = [&](int rows) { return (int64_t)nb * tile_units(lh, lw, radius, rows); };
     const double n32 = (double)regions(32), k64 = (double)((regions(64) + 255) / 256),
                  k80 = (double)((regions(80) + 255) / 256);

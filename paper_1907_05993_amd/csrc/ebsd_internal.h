@@ -175,6 +175,11 @@ hipError_t launch_demons_iter2(const Bucket* d_bk, const Bucket& hb, int level, 
 bool demons_resident_ok(int h, int w);
 hipError_t launch_demons_resident(const Bucket* d_bk, const Bucket& hb, int level, const float* taps, int radius,
                                   float tol, int cap, hipStream_t s);
+// Largest level whose pixel indices FP32 holds exactly.  The kernels of larger
+// levels (above 4096 x 4096 px; all wider than 512 px) are the row kernels in
+// column segments, the 2-D tile kernel of one iteration and
+// launch_demons_points, which form them in whole numbers.
+constexpr int64_t kMaxFp32Pixels = int64_t(1) << 24;
 // Launch L of level l runs iterations L K .. L K + K - 1 (K = tile_iters, 0: no
 // tile kernel for this radius) on 2-D tiles cut from regions of 64 columns x
 // `rows` (32 or 64) rows, or of 128 columns x 80 rows (rows = 80); partial sums in slot iteration & 7, one per

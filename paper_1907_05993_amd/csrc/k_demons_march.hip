@@ -581,7 +581,7 @@ hipError_t launch_c(const Bucket* d_bk, const Bucket& hb, int level, int L, cons
 // together with an even pattern size.
 int march_cols(int h, int w, int radius)
 {
-    if (radius < 1 || radius > kMaxRadius || h < 2 || w < 4) return 0;
+    if (radius < 1 || radius > kMaxRadius || h < 2 || w < 4 || (int64_t)h * w > kMaxFp32Pixels) return 0;
     if (w <= 128) return w % 2 == 0 ? 2 : 0;
     return w % 4 == 0 && radius < 4 ? 4 : 0;
 }

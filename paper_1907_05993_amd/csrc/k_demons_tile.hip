@@ -351,7 +351,7 @@ __global__ void __launch_bounds__(kPointThreads)
     const GatherBase T = gather_base(Tg, h, w);
     const EBSD_GLOBAL float* __restrict__ u = gptr(bk->field[base & 1] + slot);
     EBSD_GLOBAL float* __restrict__ un = gptr(bk->field[(base + 1) & 1] + slot);
-    const BilGeom g = bil_geom(h, w);
+    const BilGeomOf<true> g = bil_geom<true>(h, w);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int x = min(tx0 + lane, w - 1);
     float ux[kPointPx], uy[kPointPx];
@@ -494,7 +494,8 @@ hipError_t launch_demons_tiles(const Bucket* d_bk, const Bucket& hb, int level, 
 {
     Taps tp;
     for (int i = 0; i < 2 * kMaxRadius + 1; i++) tp.w[i] = i <= 2 * radius ? taps[i] : 0.0f;
-    if (hb.nb <= 0 || hb.lh[level] < 2 || hb.lw[level] < 2 || (rows != 32 && rows != 64 && rows != kWideRows))
+    if (hb.nb <= 0 || hb.lh[level] < 2 || hb.lw[level] < 2 || (rows != 32 && rows != 64 && rows != kWideRows) ||
+        (int64_t)hb.lh[level] * hb.lw[level] > kMaxFp32Pixels)
         return hipErrorInvalidValue;
     switch (1000 * radius + rows) {
     case 1032: return launch_tiles<1, 4, 8>(d_bk, hb, level, L, tp, tol, cap, s);
