@@ -478,8 +478,10 @@ __device__ void wave_gather(const WaveTask& w, int n, WaveSolveLds& L, double (&
 }
 
 // a / b from b's correctly rounded reciprocal ib: one Newton correction of the
-// product, which is the correctly rounded quotient (Markstein 1990), in three
-// operations instead of a division's fifteen.
+// product (Markstein 1990), in three operations instead of a division's fifteen.  The
+// correctly rounded quotient but, perhaps, where a / b lies within about 2^-51 units in
+// the last place of the middle between two numbers: a ib can be off by 1.5 units, half
+// a unit more than the theorem takes.
 __device__ inline double div_by(double a, double b, double ib)
 {
     const double q = a * ib;

@@ -81,6 +81,17 @@ __device__ inline int mirror1(int i, int n)
 #define EBSD_XG __attribute__((address_space(1)))
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
+// a / b from ib = 1 / b, correctly rounded: one Newton correction of a ib (Markstein
+// 1990).  a ib can be off by 1.5 units in the last place, half a unit more than the
+// theorem takes, so the result may be the other neighbour where a / b lies within
+// about 2^-51 units of the middle between two numbers.  b = 0 (a ray parallel to the
+// detector) gives the infinity or NaN of a division, which a correction would lose.
+__device__ inline double quotient(double a, double b, double ib)
+{
+    const double q = a * ib, c = fma(fma(-q, b, a), ib, q);
+    return isfinite(q) ? c : q;
+}
+
 // Cubic B-spline interpolant with coefficients c (h x w, whole-sample mirror
 // extension) at double-precision coordinates clamped to the image: weights
 // beta3(t + 1), beta3(t), beta3(t - 1), beta3(t - 2) on the four nodes
@@ -1005,11 +1016,9 @@ struct RoiLoader {
         const double v0 = r00 * p0 + r10 * p1 + r20 * p2;
         const double v1 = r01 * p0 + r11 * p1 + r21 * p2;
         const double v2 = r02 * p0 + r12 * p1 + r22 * p2;
-        // both quotients from one reciprocal: a correction step gives the correctly
-        // rounded quotient (Markstein 1990)
-        const double iv = 1.0 / v2, n0 = zs * v0, n1 = zs * v1;
-        const double q0 = n0 * iv, q1 = n1 * iv;
-        const double sx = xs + fma(fma(-q0, v2, n0), iv, q0), sy = ys + fma(fma(-q1, v2, n1), iv, q1);
+        // both quotients from one reciprocal
+        const double iv = 1.0 / v2;
+        const double sx = xs + quotient(zs * v0, v2, iv), sy = ys + quotient(zs * v1, v2, iv);
         const float a = INTERP == 3 ? bspline_d(Cf, H, W, sx, sy) : bilinear_d(Rn, H, W, sx, sy);
         return make_float2(a, Tn[(int64_t)Y * W + X]);
     }
