@@ -214,12 +214,12 @@ __device__ inline void bspline_line_block(At&& at, int n, int a, float (&out)[kC
 // threads as blocks.  256 patterns of 256 x 256 157 us with a second LDS copy and a
 // load at a time, 65 now; 12 of 1244 x 1024 155 and 38.
 constexpr int kCoefRows = 32;
-constexpr int kCoefLdsWords = 17408;  // of a row of 16384 samples
-__host__ __device__ inline int coef_at(int x) { return x + (x >> 5); }
-__host__ __device__ inline int coef_pitch(int W) { return coef_at(W - 1) + 1 | 1; }
+constexpr int kCoefMaxW = 20479;  // longest row: 640 blocks
+__host__ __device__ constexpr int coef_at(int x) { return x + (x >> 5); }
+__host__ __device__ constexpr int coef_pitch(int W) { return coef_at(W - 1) + 1 | 1; }
 static_assert(kCoefB == 32, "coef_at");
 
-__global__ void __launch_bounds__(512)
+__global__ void __launch_bounds__(1024)
     k_bspline_rows(const float* __restrict__ src_all, int64_t src_stride, float* __restrict__ tmp_all, int H, int W,
                    int nr)
 {
@@ -293,12 +293,13 @@ hipError_t launch_coef_images(const float* src, int64_t src_stride, int n, int H
 {
     if (n <= 0) return hipSuccess;
     const int64_t tc = (int64_t)n * W * ((H + kCoefB - 1) / kCoefB);
-    const int nblk = (W + kCoefB - 1) / kCoefB, P = coef_pitch(W), nt = nblk > 256 ? 512 : 256;
-    if (nblk > nt) return hipErrorInvalidValue;  // rows longer than 16384 samples
+    if (W > kCoefMaxW) return hipErrorInvalidValue;
+    const int nblk = (W + kCoefB - 1) / kCoefB, nt = nblk > 512 ? 1024 : (nblk > 256 ? 512 : 256);
     const int nr = std::min(kCoefRows, nt / nblk);
-    const size_t lds = sizeof(float) * nr * (size_t)P;  // at most 67 KiB
+    const size_t lds = sizeof(float) * nr * (size_t)coef_pitch(W);  // at most 83 KiB
     static std::atomic<uint64_t> attr_done{0};
-    const hipError_t e = ensure_dynamic_lds((const void*)k_bspline_rows, (int)(sizeof(float) * kCoefLdsWords), attr_done);
+    const hipError_t e =
+        ensure_dynamic_lds((const void*)k_bspline_rows, (int)(sizeof(float) * coef_pitch(kCoefMaxW)), attr_done);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_bspline_rows, dim3((unsigned)((H + nr - 1) / nr), (unsigned)n), dim3(nt), lds, s, src,
                        src_stride, tmp, H, W, nr);

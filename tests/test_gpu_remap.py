@@ -178,3 +178,17 @@ def test_coefficients_at_block_edges(E, H, W):
     for i in range(2):
         exact = ndi.spline_filter(img[i].astype(np.float64), order=3, mode="mirror", output=np.float64)
         assert np.abs(coef[i].cpu().numpy() - exact).max() <= 104 * 2.0 ** -24
+
+
+# rows of more than 512 blocks, up to the longest that the coefficients' row pass takes
+@pytest.mark.parametrize("W", [16385, 18000, 20479])
+def test_coefficients_of_rows_past_16384(E, W):
+    test_coefficients_at_block_edges(E, 3, W)
+
+
+def test_coefficient_rows_past_the_limit_are_refused(E):
+    print("case: spline coefficients 3x20480", flush=True)
+    img = torch.zeros(1, 3, 20480, device="cuda")
+    with pytest.raises(E.EbsdError) as ei:
+        E.stage_remap(img, torch.eye(3, dtype=torch.float64)[None], (10239.5, 1.0, 14336.0), interp=3)
+    assert ei.value.code == -5
