@@ -610,9 +610,6 @@ __device__ uint32_t solve_F_wave(const RoiSet& rs, double* F, WaveSolveLds& L)
     } else {
         st |= EBSD_SOLVE_ILLCOND;
     }
-    // Gauss-Newton to a step below 1e-14, or until a step below 1e-13 no longer
-    // halves: those are rounding (they never fall below 1e-14 for some shift sets)
-    double before = INFINITY;
     for (int it = 0; it < 100; it++) {
         wave_gn_terms(f, n, L);
         wave_gather(w, n, L, M, rhs);
@@ -631,8 +628,7 @@ __device__ uint32_t solve_F_wave(const RoiSet& rs, double* F, WaveSolveLds& L)
             st |= EBSD_SOLVE_ILLCOND;
             break;
         }
-        if (nrm < 1e-28 || (nrm < 1e-26 && nrm > 0.25 * before)) break;
-        before = nrm;
+        if (sqrt(nrm) < 1e-14) break;
     }
     // conditioning of J^T J at the solution: flagged above 1e12.  A bound from its
     // Cholesky factor clears the usual case (a decade under the limit, so that
