@@ -261,28 +261,39 @@ int ebsd_pipeline_destroy(ebsd_pipeline* pl);
 int ebsd_second_pass_batch(ebsd_handle* h, const ebsd_pair* pairs, int32_t n,
                            const double* R_finite, const ebsd_outputs* out, void* stream);
 
-/* Autotuner for the demons kernel: on this batch (same validation as
- * ebsd_register_batch), times every supported strip height (rows per
- * workgroup: 16, 32, 64, 128) of the row-marching demons kernel for each
- * pyramid level (wider than 512 px: column segments, and also the 2-D tile
- * kernel as strip height 0), and keeps the fastest per level size for
- * later calls of this handle whose size bucket holds at least a quarter as
- * many pairs as the tuned batch (smaller batches use the default rule of
- * ebsd_get_strip_height).  If the environment variable EBSD_TUNE_CACHE
- * named a file when the handle was created, the table is read from it then
- * and written back here (lines "gfx950 <h> <w> <rows> <two-iteration rows>",
- * through a temporary file renamed over the cache, so a reader never sees a
- * partial table).  Synchronises
- * `stream`.  Demons results are unaffected (the strip height only changes the
- * work decomposition). */
+/* Autotuner for the demons kernels: on this batch (same validation as
+ * ebsd_register_batch), times for each pyramid level every supported strip
+ * height (rows per workgroup: 16, 32, 64, 128) of the row-marching demons
+ * kernel (wider than 512 px: column segments, and also the 2-D tile kernel as
+ * strip height 0), every strip height of its two-iteration form, and, for
+ * levels of more than 64 x 64 px, the kernels of several iterations that the
+ * rule of ebsd_set_resident chooses from.  It keeps the fastest strip heights
+ * per level size for later calls of this handle whose size bucket holds at
+ * least a quarter as many pairs as the tuned batch (smaller batches use the
+ * default rule of ebsd_get_strip_height), and the fastest kernel for those that
+ * hold a quarter to four times as many (others choose by prediction; the rule's
+ * own choice is kept unless another kernel is faster by more than 3%).  A
+ * tolerance enters as the iterations that a launch of several runs past a
+ * pair's stop; the timings themselves are of full iterations.  Without
+ * smoothing and tolerance a level's iterations are one launch whatever was
+ * timed.  If the environment variable EBSD_TUNE_CACHE named a file when the
+ * handle was created, the table is read from it then and written back here
+ * (lines "gfx950 <h> <w> <rows> <two-iteration rows>", the last with
+ * ",<kind>,<pairs>" behind it where the kernel was measured, kind as in
+ * ebsd_set_level_plan; through a temporary file renamed over the cache, so a
+ * reader never sees a partial table).  Synchronises `stream`.  Demons results
+ * are unaffected (the choice only changes the work decomposition). */
 int ebsd_autotune(ebsd_handle* h, const ebsd_pair* pairs, int32_t n, void* stream);
 
-/* Graph replay (default on): the demons iterations of each pyramid level
- * (one launch per iteration) form a static sequence for a given batch
- * configuration (pair size, batch size, distinct references, parameters,
- * strip height); it is captured once into a HIP graph and replayed on later
- * calls, the per-call pointers travelling in a descriptor copied before the
- * replay.  enable = 0 makes later calls launch every kernel directly.
+/* Graph replay (default on): the demons launches of a call, with what lies
+ * between the levels, form a static sequence for a given batch configuration
+ * (pair size, batch size, parameters, plan of each level).  The first call of
+ * a configuration issues them one by one and captures them into a HIP graph
+ * behind that; later calls replay it, the per-call pointers travelling in a
+ * descriptor copied before the replay.  Where the host decides between
+ * launches (ebsd_set_gating with levels of more launches than a chunk) or
+ * times the levels (ebsd_set_timing), each chunk or level is a graph of its
+ * own.  enable = 0 makes later calls launch every kernel directly.
  * Results are identical either way. */
 int ebsd_set_graphs(ebsd_handle* h, int enable);
 
@@ -292,7 +303,8 @@ int ebsd_set_graphs(ebsd_handle* h, int enable);
  * (multi-resolution demons, section 1).  Finer levels whose size was not
  * set by ebsd_set_strip_height / ebsd_set_fused_height also run several
  * iterations per launch by rule: all of them without smoothing and tolerance,
- * else whatever is predicted to be the fastest for the batch, two by wavefronts
+ * else whatever ebsd_autotune measured, or without it is predicted, to be the
+ * fastest for the batch (ebsd_get_level_plan), two by wavefronts
  * that march down strips of the level, four (three at the widest smoothing) on
  * 2-D regions, or the row strips, as tuned or two where the size was not tuned.
  * enable = 0 turns all of that off: every level runs as tuned or set, one
@@ -353,6 +365,30 @@ int ebsd_set_strip_height(ebsd_handle* h, int32_t level_h, int32_t level_w, int3
  * 128, or 8 for levels at most 128 px wide; EBSD_EINVAL otherwise). */
 int ebsd_get_fused_height(const ebsd_handle* h, int32_t level_h, int32_t level_w);
 int ebsd_set_fused_height(ebsd_handle* h, int32_t level_h, int32_t level_w, int32_t rows);
+
+/* The kernel that runs a level's demons iterations. */
+enum {
+    EBSD_PLAN_BY_RULE = -1,
+    EBSD_PLAN_ROWS = 0,    /* row strips, one iteration per launch */
+    EBSD_PLAN_ROWS2 = 1,   /* row strips, two */
+    EBSD_PLAN_MARCH = 2,   /* wavefronts marching down strips, two */
+    EBSD_PLAN_REGIONS = 3, /* 2-D regions, four, or three (regions of 32 and 64 rows at radius 4) */
+    EBSD_PLAN_POINTS = 4,  /* a pixel per thread, all (without smoothing and tolerance) */
+    EBSD_PLAN_RESIDENT = 5 /* a workgroup per pair, all (levels of at most 64 x 64 px) */
+};
+/* Which one runs level `level` of H x W patterns in a size bucket of `pairs`
+ * pairs, and its strip height or region rows in *rows (0: none); either may be
+ * NULL.  Errors as ebsd_register_batch for the size. */
+int ebsd_get_level_plan(const ebsd_handle* h, int32_t H, int32_t W, int32_t level, int32_t pairs, int32_t* kind,
+                        int32_t* rows);
+/* Force it for a level size (a level that runs resident does so all the
+ * same unless ebsd_set_resident turned that off); the last of this call,
+ * ebsd_set_strip_height and ebsd_set_fused_height counts.  rows: as those two take
+ * them for EBSD_PLAN_ROWS and _ROWS2, 9 to 16384 for _MARCH, 32, 64 or 80 for
+ * _REGIONS, 0 for _POINTS; EBSD_PLAN_BY_RULE undoes it.  EBSD_EINVAL where the kind
+ * does not support the level or the handle's smoothing.  Fields, counts and
+ * status are those of every other kind. */
+int ebsd_set_level_plan(ebsd_handle* h, int32_t level_h, int32_t level_w, int32_t kind, int32_t rows);
 
 /* Timing of the demons iterations, for measurement tools.  enable != 0 makes
  * later calls record HIP events on their stream around each pyramid level's

@@ -62,6 +62,17 @@ struct ebsd_handle {
     // level sizes whose strip height or two-iteration strip height the caller set
     // (ebsd_set_strip_height, ebsd_set_fused_height): they run as set
     std::set<std::pair<int, int>> forced;
+    // the kind of kernel (LevelPlan::Kind) that ebsd_autotune measured as the fastest
+    // per level size, and the batch size it measured
+    struct TunedKind {
+        int kind, pairs;
+    };
+    std::map<std::pair<int, int>, TunedKind> tuned_kind;
+    // level sizes whose kernel kind and rows the caller set (ebsd_set_level_plan)
+    struct SetPlan {
+        int kind, rows;
+    };
+    std::map<std::pair<int, int>, SetPlan> set_plan;
     std::string tune_cache;  // EBSD_TUNE_CACHE at create time (may be empty)
     // captured launch sequences per bucket configuration (replayed with
     // hipGraphLaunch); the capture itself runs on a private stream
@@ -121,7 +132,13 @@ int fused_ty_for(const ebsd_handle* h, int lh, int lw, int nb = 1 << 20)
 
 // How a level's iterations are launched.
 struct LevelPlan {
-    enum Kind { Rows, Rows2, March, Tiles, Points } kind;
+    enum Kind {
+        Rows = EBSD_PLAN_ROWS,
+        Rows2 = EBSD_PLAN_ROWS2,
+        March = EBSD_PLAN_MARCH,
+        Tiles = EBSD_PLAN_REGIONS,
+        Points = EBSD_PLAN_POINTS
+    } kind;
     int rows;        // strip height (0: the 2-D tile kernel of one iteration), or region rows of Tiles
     int per_launch;  // iterations per launch
     int units;       // partial sums per pair and iteration
@@ -231,39 +248,101 @@ double late_stop(float tol, int cap, int per_launch)
     return 1.0 + 0.5 * (per_launch - 1) / std::max(1.0, std::min((double)cap, 0.5 / tol));
 }
 
+// The kernel kind measured for this level size, for batches of a quarter to four times
+// as many pairs as it was measured on (a small batch starves a large one's kernel of
+// workgroups and the other way round); -1: none.
+int tuned_kind_for(const ebsd_handle* h, int lh, int lw, int nb)
+{
+    const auto it = h->tuned_kind.find(std::make_pair(lh, lw));
+    if (it == h->tuned_kind.end()) return -1;
+    const int64_t n = nb, q = it->second.pairs;
+    return 4 * n >= q && n <= 4 * q ? it->second.kind : -1;
+}
+
+// Whether a level of lh x lw px can run on a kernel kind with these rows.
+bool plan_supported(const ebsd_handle* h, int lh, int lw, int kind, int rows)
+{
+    switch (kind) {
+    case LevelPlan::Rows: return strip_ty_ok(lw, rows);
+    case LevelPlan::Rows2: return rows2_ty_ok(lw, rows);
+    case LevelPlan::March: return march_cols(lh, lw, h->radius) && rows >= kMarchMinRows && rows <= 16384;
+    case LevelPlan::Tiles:
+        return tile_iters(h->radius, 32) && (rows == 32 || rows == 64 || rows == 80) && lh >= 2 && lw >= 2 &&
+               (int64_t)lh * lw <= kMaxFp32Pixels;
+    case LevelPlan::Points: return h->radius == 0 && h->p.tol_px == 0.0f && rows == 0;
+    }
+    return false;
+}
+
 // A level size the caller set runs as set.  Otherwise, unless ebsd_set_resident
 // turned off running several iterations per launch by rule: without smoothing
-// and tolerance all iterations in one launch; else the tile kernel, the marching
-// wavefronts or the row kernels, whichever is predicted to be the fastest, the
-// row kernels as tuned, or untuned two iterations per launch.
+// and tolerance all iterations in one launch; else the kernel that ebsd_autotune
+// measured as the fastest; else the tile kernel, the marching wavefronts or the row
+// kernels, whichever is predicted to be the fastest.  Strips and regions of the
+// marching and tile kernels are as predicted for the batch, row strips as tuned, or
+// untuned two iterations per launch.
 LevelPlan level_plan(const ebsd_handle* h, int H, int W, int lh, int lw, int nb, int cap)
 {
     const auto key = std::make_pair(lh, lw);
+    const auto set = h->set_plan.find(key);
+    if (set != h->set_plan.end()) {
+        const int rows = set->second.rows;
+        switch (set->second.kind) {
+        case LevelPlan::Rows: return {LevelPlan::Rows, rows, 1, demons_units(lh, lw, rows)};
+        case LevelPlan::Rows2: return {LevelPlan::Rows2, rows, 2, demons_units(lh, lw, rows)};
+        case LevelPlan::March:
+            if (march_cols(lh, lw, h->radius) == 4 && (int64_t)H * W % 2) break;  // see march_cols
+            return {LevelPlan::March, rows, 2, march_units(lh, lw, h->radius, rows)};
+        case LevelPlan::Tiles:
+            return {LevelPlan::Tiles, rows, tile_iters(h->radius, rows), tile_units(lh, lw, h->radius, rows)};
+        case LevelPlan::Points: return {LevelPlan::Points, 0, std::max(cap, 1), 0};
+        }
+    }
     const bool rule = h->resident && !h->forced.count(key);
+    int fty = fused_ty_for(h, lh, lw, nb);
+    const int ty = strip_ty_for(h, lh, lw, nb);
+    const bool tuned = h->strip_ty.count(key) && tuned_applies(h->tuned_nb_strip, lh, lw, nb);
+    if (rule && !fty && !tuned && rows_cpl(lw)) fty = default_fused_ty(lh, lw, nb, h->radius);
     if (rule) {
         if (h->radius == 0 && h->p.tol_px == 0.0f) return {LevelPlan::Points, 0, std::max(cap, 1), 0};
         const MarchPlan m = march_plan(H, W, lh, lw, nb, h->radius);
         double tiles = 1e30;
         const int tr = tile_rows_for(lh, lw, nb, h->radius, tiles);
-        const int f = rows_cpl(lw) ? default_fused_ty(lh, lw, nb, h->radius) : 0, ty = strip_ty_for(h, lh, lw, nb);
-        const double rows = rows_us(lh, lw, nb, h->radius, f ? f : ty ? ty : kDefaultStripTY, f > 0);
-        const double tiles_l = tiles * late_stop(h->p.tol_px, cap, tr ? tile_iters(h->radius, tr) : 1);
-        const double march_l = m.us * late_stop(h->p.tol_px, cap, 2);
-        const double rows_l = rows * late_stop(h->p.tol_px, cap, f ? 2 : 1);
-        if (tr && tiles_l < std::min(rows_l, march_l))
+        int kind = tuned_kind_for(h, lh, lw, nb);
+        if (kind < 0) {
+            const double rows = rows_us(lh, lw, nb, h->radius, fty ? fty : ty ? ty : kDefaultStripTY, fty > 0);
+            const double tiles_l = tiles * late_stop(h->p.tol_px, cap, tr ? tile_iters(h->radius, tr) : 1);
+            const double march_l = m.us * late_stop(h->p.tol_px, cap, 2);
+            const double rows_l = rows * late_stop(h->p.tol_px, cap, fty ? 2 : 1);
+            if (tr && tiles_l < std::min(rows_l, march_l)) kind = LevelPlan::Tiles;
+            else if (march_l < rows_l) kind = LevelPlan::March;
+        }
+        if (kind == LevelPlan::Tiles && tr)
             return {LevelPlan::Tiles, tr, tile_iters(h->radius, tr), tile_units(lh, lw, h->radius, tr)};
-        if (march_l < rows_l) return {LevelPlan::March, m.rows, 2, march_units(lh, lw, h->radius, m.rows)};
+        if (kind == LevelPlan::March && m.rows) return {LevelPlan::March, m.rows, 2, march_units(lh, lw, h->radius, m.rows)};
     }
-    int fty = fused_ty_for(h, lh, lw, nb);
-    const bool tuned = h->strip_ty.count(key) && tuned_applies(h->tuned_nb_strip, lh, lw, nb);
-    if (rule && !fty && !tuned && rows_cpl(lw)) fty = default_fused_ty(lh, lw, nb, h->radius);
     if (fty) return {LevelPlan::Rows2, fty, 2, demons_units(lh, lw, fty)};
-    const int ty = strip_ty_for(h, lh, lw, nb);
     return {LevelPlan::Rows, ty, 1, demons_units(lh, lw, ty)};
 }
 
+// Launch k of a level that runs by plan q (Points: its only launch, q.per_launch
+// iterations).
+hipError_t launch_plan(const ebsd_handle* h, const Bucket* d_bk, const Bucket& b, const LevelPlan& q, int l, int k,
+                       float tol, int cap, hipStream_t s)
+{
+    switch (q.kind) {
+    case LevelPlan::Rows: return launch_demons_iter(d_bk, b, l, k, h->taps, h->radius, tol, q.rows, s);
+    case LevelPlan::Rows2: return launch_demons_iter2(d_bk, b, l, k, h->taps, h->radius, tol, cap, q.rows, s);
+    case LevelPlan::March: return launch_demons_march(d_bk, b, l, k, h->taps, h->radius, tol, cap, q.rows, s);
+    case LevelPlan::Tiles: return launch_demons_tiles(d_bk, b, l, k, h->taps, h->radius, tol, cap, q.rows, s);
+    case LevelPlan::Points: return launch_demons_points(d_bk, b, l, h->taps, q.per_launch, s);
+    }
+    return hipErrorInvalidValue;
+}
+
 // Tuning cache: one line "gfx950 <level h> <level w> <strip height> <fused strip height>"
-// per level size (fused strip height 0: one iteration per launch).
+// per level size (fused strip height 0: one iteration per launch), the last with
+// ",<kind>,<pairs>" behind it where the kernel kind was measured.
 void load_tune_cache(ebsd_handle* h)
 {
     if (h->tune_cache.empty()) return;
@@ -279,6 +358,12 @@ void load_tune_cache(ebsd_handle* h)
         if (strip_ty_ok(lw, ty)) h->strip_ty[key] = ty;
         if (rows2_ty_ok(lw, fty)) h->fused_ty[key] = fty;
         else h->fused_ty.erase(key);
+        char c1 = 0, c2 = 0;
+        int kind = -1, pairs = 0;
+        if (is >> c1 >> kind >> c2 >> pairs && c1 == ',' && c2 == ',' && kind >= LevelPlan::Rows &&
+            kind <= LevelPlan::Tiles && pairs > 0)
+            h->tuned_kind[key] = {kind, pairs};
+        else h->tuned_kind.erase(key);
     }
 }
 
@@ -295,9 +380,13 @@ void save_tune_cache(const ebsd_handle* h)
     tmp << h->tune_cache << ".tmp." << (unsigned long)getpid();
     {
         std::ofstream f(tmp.str(), std::ios::trunc);
-        for (auto& kv : h->strip_ty)
+        for (auto& kv : h->strip_ty) {
             f << "gfx950 " << kv.first.first << " " << kv.first.second << " " << kv.second << " "
-              << fused_ty_for(h, kv.first.first, kv.first.second) << "\n";
+              << fused_ty_for(h, kv.first.first, kv.first.second);
+            const auto it = h->tuned_kind.find(kv.first);
+            if (it != h->tuned_kind.end()) f << "," << it->second.kind << "," << it->second.pairs;
+            f << "\n";
+        }
         f.flush();
         if (!f) {
             f.close();
@@ -803,54 +892,93 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     EBSD_TRY(launch_stats(d_bk, nb, nref, chain_doubles ? reinterpret_cast<double*>(base + o_chain) : nullptr, s));
     EBSD_TRY(launch_pyramids(d_bk, b, s));
     if (tune_only) {
-        // time each supported strip height for every row-marching level
+        // time every supported strip height of the row kernels for each level, then the
+        // marching wavefronts and the regions that the rule would take
         EBSD_TRY(launch_demons_init(d_bk, b, s));
         hipEvent_t e0, e1;
         EBSD_TRY(hipEventCreate(&e0));
         EBSD_TRY(hipEventCreate(&e1));
+        // us per iteration of at least `iters` iterations behind a first launch
+        const auto time_plan = [&](const LevelPlan& q, int l, int iters, float& us) -> int {
+            const int K = q.per_launch, cap = 1 << 20, n = (iters + K - 1) / K;
+            EBSD_TRY(launch_plan(h, d_bk, b, q, l, 0, 0.0f, cap, s));
+            EBSD_TRY(hipEventRecord(e0, s));
+            for (int k = 1; k <= n; k++) EBSD_TRY(launch_plan(h, d_bk, b, q, l, k, 0.0f, cap, s));
+            EBSD_TRY(hipEventRecord(e1, s));
+            EBSD_TRY(hipEventSynchronize(e1));
+            float ms = 0.0f;
+            EBSD_TRY(hipEventElapsedTime(&ms, e0, e1));
+            us = 1e3f * ms / (float)(n * K);
+            return EBSD_OK;
+        };
         for (int l = L - 1; l >= 0; l--) {
             const int lh = b.lh[l], lw = b.lw[l];
             if (!rows_cpl(lw)) continue;
-            float best = 1e30f;
+            const auto key = std::make_pair(lh, lw);
+            float best = 1e30f, us = 0.0f;
             int best_ty = kDefaultStripTY;
             for (int ty : {0, 16, 32, 64, 128}) {
                 if (!strip_ty_ok(lw, ty)) continue;  // 0: the 2-D tile kernel, levels wider than 512 px
-                for (int it = 0; it < 2; it++)
-                    EBSD_TRY(launch_demons_iter(d_bk, b, l, it, h->taps, h->radius, 0.0f, ty, s));
-                EBSD_TRY(hipEventRecord(e0, s));
-                for (int it = 0; it < 6; it++)
-                    EBSD_TRY(launch_demons_iter(d_bk, b, l, it, h->taps, h->radius, 0.0f, ty, s));
-                EBSD_TRY(hipEventRecord(e1, s));
-                EBSD_TRY(hipEventSynchronize(e1));
-                float ms = 0.0f;
-                EBSD_TRY(hipEventElapsedTime(&ms, e0, e1));
-                if (ms < best) {
-                    best = ms;
+                const int r = time_plan({LevelPlan::Rows, ty, 1, 0}, l, 6, us);
+                if (r) return r;
+                if (us < best) {
+                    best = us;
                     best_ty = ty;
                 }
             }
-            h->strip_ty[std::make_pair(lh, lw)] = best_ty;
-            h->tuned_nb_strip[std::make_pair(lh, lw)] = nb;
-            // two iterations per launch: 3 launches (6 iterations) against the best 6 single launches
             int best_fty = 0;
             for (int fty : {8, 16, 32, 64, 128}) {
                 if (!rows2_ty_ok(lw, fty)) continue;
-                EBSD_TRY(launch_demons_iter2(d_bk, b, l, 0, h->taps, h->radius, 0.0f, 1 << 20, fty, s));
-                EBSD_TRY(hipEventRecord(e0, s));
-                for (int L2 = 1; L2 <= 3; L2++)
-                    EBSD_TRY(launch_demons_iter2(d_bk, b, l, L2, h->taps, h->radius, 0.0f, 1 << 20, fty, s));
-                EBSD_TRY(hipEventRecord(e1, s));
-                EBSD_TRY(hipEventSynchronize(e1));
-                float ms = 0.0f;
-                EBSD_TRY(hipEventElapsedTime(&ms, e0, e1));
-                if (ms < best) {
-                    best = ms;
+                const int r = time_plan({LevelPlan::Rows2, fty, 2, 0}, l, 6, us);
+                if (r) return r;
+                if (us < best) {
+                    best = us;
                     best_fty = fty;
                 }
             }
-            if (best_fty) h->fused_ty[std::make_pair(lh, lw)] = best_fty;
-            else h->fused_ty.erase(std::make_pair(lh, lw));
-            h->tuned_nb_fused[std::make_pair(lh, lw)] = nb;
+            h->strip_ty[key] = best_ty;
+            h->tuned_nb_strip[key] = nb;
+            if (best_fty) h->fused_ty[key] = best_fty;
+            else h->fused_ty.erase(key);
+            h->tuned_nb_fused[key] = nb;
+            h->tuned_kind.erase(key);
+            // levels that run in one launch whatever was measured
+            if (demons_resident_ok(lh, lw) || (h->radius == 0 && p.tol_px == 0.0f)) continue;
+            // the other kinds, but those predicted at more than twice the best row kernel;
+            // what the rule takes stays unless another is faster by more than 3 % in a
+            // second, longer timing of the two (short ones differ by more among themselves)
+            const int cap = p.max_iters[l];
+            const LevelPlan by_rule = level_plan(h, H, W, lh, lw, nb, cap);
+            LevelPlan kinds[3] = {{best_fty ? LevelPlan::Rows2 : LevelPlan::Rows, best_fty ? best_fty : best_ty,
+                                   best_fty ? 2 : 1, 0}};
+            float cost[3] = {best};
+            int n = 1;
+            double tiles = 1e30;
+            const int tr = tile_rows_for(lh, lw, nb, h->radius, tiles);
+            const MarchPlan m = march_plan(H, W, lh, lw, nb, h->radius);
+            if (tr && (tiles < 2.0 * best || by_rule.kind == LevelPlan::Tiles))
+                kinds[n++] = {LevelPlan::Tiles, tr, tile_iters(h->radius, tr), 0};
+            if (m.rows && (m.us < 2.0 * best || by_rule.kind == LevelPlan::March))
+                kinds[n++] = {LevelPlan::March, m.rows, 2, 0};
+            int fast = 0, rule = 0;
+            for (int i = 0; i < n; i++) {
+                if (i > 0) {
+                    const int r = time_plan(kinds[i], l, 6, cost[i]);
+                    if (r) return r;
+                }
+                cost[i] *= (float)late_stop(p.tol_px, cap, kinds[i].per_launch);
+                if (cost[i] < cost[fast]) fast = i;
+                if (kinds[i].kind == by_rule.kind) rule = i;
+            }
+            if (fast != rule) {
+                for (int i : {rule, fast}) {
+                    const int r = time_plan(kinds[i], l, 24, cost[i]);
+                    if (r) return r;
+                    cost[i] *= (float)late_stop(p.tol_px, cap, kinds[i].per_launch);
+                }
+                if (!(cost[fast] < 0.97f * cost[rule])) fast = rule;
+            }
+            h->tuned_kind[key] = {kinds[fast].kind, nb};
         }
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
@@ -867,26 +995,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         return (cap + K - 1) / K + ((p.tol_px > 0.0f && cap > 0 && (cap - 1) % K != 0) ? 1 : 0);
     };
     auto launch_range = [&](int l, int a, int e, hipStream_t st) -> int {
-        const int rows = plan[l].rows, cap = p.max_iters[l];
-        for (int k = a; k < e; k++) {
-            switch (plan[l].kind) {
-            case LevelPlan::Rows:
-                EBSD_TRY(launch_demons_iter(d_bk, b, l, k, h->taps, h->radius, p.tol_px, rows, st));
-                break;
-            case LevelPlan::Rows2:
-                EBSD_TRY(launch_demons_iter2(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));
-                break;
-            case LevelPlan::March:
-                EBSD_TRY(launch_demons_march(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));
-                break;
-            case LevelPlan::Tiles:
-                EBSD_TRY(launch_demons_tiles(d_bk, b, l, k, h->taps, h->radius, p.tol_px, cap, rows, st));
-                break;
-            case LevelPlan::Points:
-                EBSD_TRY(launch_demons_points(d_bk, b, l, h->taps, cap, st));
-                break;
-            }
-        }
+        for (int k = a; k < e; k++) EBSD_TRY(launch_plan(h, d_bk, b, plan[l], l, k, p.tol_px, p.max_iters[l], st));
         return EBSD_OK;
     };
     // Issues fn's launches on s: the first time one by one, and captured for the next time while
@@ -1311,6 +1420,7 @@ int ebsd_set_strip_height(ebsd_handle* h, int32_t level_h, int32_t level_w, int3
     try {
         h->strip_ty[std::make_pair((int)level_h, (int)level_w)] = ty;
         h->forced.insert(std::make_pair((int)level_h, (int)level_w));
+        h->set_plan.erase(std::make_pair((int)level_h, (int)level_w));
     } catch (const std::bad_alloc&) {
         return EBSD_ENOMEM;
     }
@@ -1333,10 +1443,46 @@ int ebsd_set_fused_height(ebsd_handle* h, int32_t level_h, int32_t level_w, int3
         if (rows) h->fused_ty[key] = rows;
         else h->fused_ty.erase(key);
         h->forced.insert(key);
+        h->set_plan.erase(key);
     } catch (const std::bad_alloc&) {
         return EBSD_ENOMEM;
     }
     h->tuned_nb_fused.erase(key);  // forced: applies to every batch
+    return EBSD_OK;
+}
+
+int ebsd_set_level_plan(ebsd_handle* h, int32_t level_h, int32_t level_w, int32_t kind, int32_t rows)
+{
+    if (!h || level_h <= 0 || level_w <= 0 || level_h > 16384 || level_w > 16384) return EBSD_EINVAL;
+    const auto key = std::make_pair((int)level_h, (int)level_w);
+    if (kind == EBSD_PLAN_BY_RULE) {
+        h->set_plan.erase(key);
+        return EBSD_OK;
+    }
+    if (!plan_supported(h, level_h, level_w, kind, rows)) return EBSD_EINVAL;
+    try {
+        h->set_plan[key] = {kind, rows};
+    } catch (const std::bad_alloc&) {
+        return EBSD_ENOMEM;
+    }
+    return EBSD_OK;
+}
+
+int ebsd_get_level_plan(const ebsd_handle* h, int32_t H, int32_t W, int32_t level, int32_t pairs, int32_t* kind,
+                        int32_t* rows)
+{
+    if (!h || level < 0 || level >= h->p.levels || pairs < 1) return EBSD_EINVAL;
+    const int e = check_shape(h->p, H, W);
+    if (e) return e;
+    int lh = H, lw = W;
+    for (int l = 0; l < level; l++) {
+        lh = (lh + 1) / 2;
+        lw = (lw + 1) / 2;
+    }
+    const bool res = h->resident && demons_resident_ok(lh, lw);
+    const LevelPlan q = level_plan(h, H, W, lh, lw, pairs, h->p.max_iters[level]);
+    if (kind) *kind = res ? EBSD_PLAN_RESIDENT : q.kind;
+    if (rows) *rows = res ? 0 : q.rows;
     return EBSD_OK;
 }
 

@@ -102,6 +102,8 @@ class COutputs(C.Structure):
 
 _lib = None
 
+PLAN_KINDS = ("rows", "rows2", "march", "regions", "points", "resident")
+
 EXPORTED = ["ebsd_version", "ebsd_params_default", "ebsd_strerror", "ebsd_create", "ebsd_destroy",
             "ebsd_get_params", "ebsd_roi_layout", "ebsd_register_batch",
             "ebsd_register_batch_init", "ebsd_second_pass_batch", "ebsd_stage_normalize",
@@ -115,6 +117,7 @@ EXPORTED = ["ebsd_version", "ebsd_params_default", "ebsd_strerror", "ebsd_create
             "ebsd_cnn_forward", "ebsd_cnn_train_step", "ebsd_cnn_reset_optimizer",
             "ebsd_load_model", "ebsd_set_model", "ebsd_stage_conv3x3", "ebsd_stage_conv3x3_dgrad",
             "ebsd_stage_conv3x3_wgrad", "ebsd_gen_pairs", "ebsd_get_fused_height", "ebsd_set_fused_height",
+            "ebsd_get_level_plan", "ebsd_set_level_plan",
             "ebsd_set_gating", "ebsd_get_launch_counts", "ebsd_tilt_rotation", "ebsd_cnn_get_optimizer",
             "ebsd_cnn_set_optimizer", "ebsd_stage_bandpass_static", "ebsd_cnn_set_fusion",
             "ebsd_pipeline_create", "ebsd_pipeline_handle", "ebsd_pipeline_submit", "ebsd_pipeline_wait",
@@ -153,6 +156,8 @@ def lib():
         L.ebsd_set_strip_height.argtypes = [vp, i32, i32, i32]
         L.ebsd_get_fused_height.argtypes = [vp, i32, i32]
         L.ebsd_set_fused_height.argtypes = [vp, i32, i32, i32]
+        L.ebsd_get_level_plan.argtypes = [vp, i32, i32, i32, i32, vp, vp]
+        L.ebsd_set_level_plan.argtypes = [vp, i32, i32, i32, i32]
         L.ebsd_set_gating.argtypes = [vp, i32]
         L.ebsd_tilt_rotation.argtypes = [C.c_double, C.POINTER(C.c_double)]
         L.ebsd_get_launch_counts.argtypes = [vp, vp, vp]
@@ -456,8 +461,9 @@ class Registrar:
         _check(lib().ebsd_set_model(self._h, net._h), "ebsd_set_model")
 
     def autotune(self, refs, tests, ref_ids=None):
-        """Time the demons strip heights on this batch and keep the fastest per
-        level; returns {(h, w): rows}."""
+        """Time the demons kernels and strip heights on this batch and keep the
+        fastest per level (level_plan); returns {(h, w): rows}, the strip heights of
+        one iteration per launch."""
         arr, n, shapes, keep = self._pairs(refs, tests, ref_ids)
         _check(lib().ebsd_autotune(self._h, arr, n, _stream()), "ebsd_autotune")
         out = {}
@@ -502,6 +508,19 @@ class Registrar:
         """{(h, w): fused strip height or 0} for the levels of an H x W pattern."""
         sizes = [level_size(H, W, l) for l in range(self.params.levels)]
         return {(h, w): lib().ebsd_get_fused_height(self._h, h, w) for h, w in sizes}
+
+    def level_plan(self, H, W, level, pairs):
+        """(kind, rows) of the kernel that runs this level of H x W patterns in a
+        size bucket of `pairs` pairs; kind is a name of PLAN_KINDS."""
+        kind, rows = C.c_int32(), C.c_int32()
+        _check(lib().ebsd_get_level_plan(self._h, H, W, level, pairs, C.byref(kind), C.byref(rows)),
+               "ebsd_get_level_plan")
+        return PLAN_KINDS[kind.value], rows.value
+
+    def set_level_plan(self, level_h, level_w, kind, rows=0):
+        """Force the kernel of a level size (kind None: by rule again)."""
+        k = -1 if kind is None else PLAN_KINDS.index(kind)
+        _check(lib().ebsd_set_level_plan(self._h, level_h, level_w, k, rows), "ebsd_set_level_plan")
 
     def set_timing(self, on=True):
         _check(lib().ebsd_set_timing(self._h, int(bool(on))), "ebsd_set_timing")
