@@ -19,7 +19,7 @@ def call(E, refs, tests, multi, **kw):
 
 
 # one column / row past a tile, a last tile of one row or column, several tiles
-# across, one region only; 20 pairs of 150 px take the regions of 64 rows
+# across, one region only; 20 pairs of 150 px take the regions of 64 rows (radius 3 and 4)
 @pytest.mark.parametrize("n,H,W", [(1, 65, 66), (2, 72, 41), (1, 41, 129), (1, 97, 640), (2, 300, 70), (20, 150, 150)])
 @pytest.mark.parametrize("sigma", [0.4, 0.7, 1.0, 1.3])  # radius 1 .. 4
 def test_tiles_equal_single_iterations(E, n, H, W, sigma):
@@ -57,7 +57,7 @@ def test_wide_regions_equal_single_iterations(E, n, H, W, sigma):
 
 
 # batches that the marching wavefronts take: two and four columns per lane, lanes
-# past the last column, two and four segments, strips that do not divide the
+# past the last column, two and three segments, strips that do not divide the
 # height (the last of a few rows)
 @pytest.mark.parametrize("n,H,W", [(1024, 90, 126), (1000, 66, 128), (200, 110, 132), (128, 128, 256), (160, 100, 260),
                                    (64, 140, 700)])
