@@ -79,7 +79,15 @@ struct ebsd_handle {
     bool graphs = true;
     bool resident = true;  // levels of at most 64 x 64 px iterate in one launch
     hipStream_t cap_stream = nullptr;
-    std::map<std::string, hipGraphExec_t> graph_cache;
+    struct CachedGraph {
+        hipGraphExec_t exec;  // nullptr: not capturable
+        int launches;         // its size
+        uint64_t call;        // the last call that used it
+    };
+    std::map<std::string, CachedGraph> graph_cache;
+    int64_t graph_launches = 0;  // of all cached graphs
+    uint64_t call = 0;           // registration calls so far
+    bool in_flight = false;      // a call failed: its launches may still be running
     // With a tolerance, a level's launches go out in chunks of gate_chunk; after
     // each chunk a kernel writes the number of pairs still iterating into
     // pinned host memory, and the host stops issuing chunks once a chunk has
@@ -541,8 +549,37 @@ int map_err(hipError_t e)
 void clear_graphs(ebsd_handle* h)
 {
     for (auto& kv : h->graph_cache)
-        if (kv.second) (void)hipGraphExecDestroy(kv.second);
+        if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
     h->graph_cache.clear();
+    h->graph_launches = 0;
+}
+
+// Launches that the cached graphs of a handle may hold together (a call of 3 x 150
+// iterations has about 300: some hundred batch configurations).  Graphs that the
+// running call used are kept beyond it.
+constexpr int64_t kMaxGraphLaunches = 1 << 15;
+
+// Make room for a graph: drops the least recently used ones.  No earlier call's graph is
+// running any more: a call begins by waiting for the end of the previous one
+// (ensure_pin), unless that one failed.
+void trim_graphs(ebsd_handle* h, int launches)
+{
+    if (h->graph_launches + launches <= kMaxGraphLaunches) return;
+    std::vector<std::pair<uint64_t, const std::string*>> old;
+    for (auto& kv : h->graph_cache)
+        if (kv.second.call != h->call) old.push_back({kv.second.call, &kv.first});
+    if (old.empty()) return;
+    std::sort(old.begin(), old.end());
+    DeviceWideLock lk(capture_mutex());
+    if (h->in_flight && hipDeviceSynchronize() != hipSuccess) return;
+    h->in_flight = false;
+    for (auto& o : old) {
+        if (h->graph_launches + launches <= kMaxGraphLaunches) break;
+        const auto it = h->graph_cache.find(*o.second);
+        if (it->second.exec) (void)hipGraphExecDestroy(it->second.exec);
+        h->graph_launches -= it->second.launches;
+        h->graph_cache.erase(it);
+    }
 }
 
 int ensure_ws(ebsd_handle* h, size_t bytes)
@@ -1000,16 +1037,18 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     };
     // Issues fn's launches on s: the first time one by one, and captured for the next time while
     // the device works on them; then as a graph (nullptr in the cache: not capturable).
-    auto run_graph = [&](const std::string& key, auto&& fn) -> int {
+    auto run_graph = [&](const std::string& key, int launches, auto&& fn) -> int {
         const auto it = h->graphs ? h->graph_cache.find(key) : h->graph_cache.end();
-        if (it != h->graph_cache.end() && it->second) {
-            EBSD_TRY(hipGraphLaunch(it->second, s));
+        if (it != h->graph_cache.end()) it->second.call = h->call;
+        if (it != h->graph_cache.end() && it->second.exec) {
+            EBSD_TRY(hipGraphLaunch(it->second.exec, s));
             return EBSD_OK;
         }
         const int r = fn(s);
         if (r || !h->graphs || it != h->graph_cache.end()) return r;
         if (!h->cap_stream && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
             h->cap_stream = nullptr;
+        trim_graphs(h, launches);
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
         std::shared_lock<std::shared_mutex> cap_lk(capture_mutex());
@@ -1022,12 +1061,13 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
             if (graph) (void)hipGraphDestroy(graph);
         }
         (void)hipGetLastError();
-        h->graph_cache[key] = exec;
+        h->graph_cache[key] = {exec, launches, h->call};
+        h->graph_launches += launches;
         return EBSD_OK;
     };
     auto level_key = [&](int l, int a, int e) {
         std::ostringstream key;
-        key << H << ' ' << W << ' ' << nb << ' ' << nref << ' ' << l << ' ' << p.max_iters[l]
+        key << H << ' ' << W << ' ' << nb << ' ' << l << ' ' << p.max_iters[l]
             << ' ' << p.tol_px << ' ' << h->radius << ' ' << (int)plan[l].kind << ' ' << plan[l].rows << ' ' << a
             << ' ' << e
             << ' ' << (void*)base;
@@ -1035,7 +1075,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
     };
     auto run_range = [&](int l, int a, int e) -> int {
         if (e <= a) return EBSD_OK;
-        return run_graph(level_key(l, a, e), [&](hipStream_t st) { return launch_range(l, a, e, st); });
+        return run_graph(level_key(l, a, e), e - a, [&](hipStream_t st) { return launch_range(l, a, e, st); });
     };
     auto resident = [&](int l) {
         // one workgroup per pair and CU, at any batch size: 64 x 64 px take 2.1 us per
@@ -1136,13 +1176,15 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
             whole = whole && (resident(l) || !gate || n_launches(l) <= h->gate_chunk);
         if (whole) {
             std::string key = "levels";
+            int launches = 0;
             for (int l = L - 1; l >= 0; l--) {
                 const int nl = resident(l) ? 0 : n_launches(l);
+                launches += nl + 2;
                 key += " / " + level_key(l, resident(l) ? -1 : 0, nl);
                 h->launches_planned[l] += nl;
                 h->launches_issued[l] += nl;
             }
-            const int e = run_graph(key, [&](hipStream_t st) -> int {
+            const int e = run_graph(key, launches, [&](hipStream_t st) -> int {
                 for (int l = L - 1; l >= 0; l--) {
                     if (resident(l)) {
                         EBSD_TRY(launch_demons_resident(d_bk, b, l, h->taps, h->radius, p.tol_px, p.max_iters[l], st));
@@ -1234,13 +1276,20 @@ int run_body(ebsd_handle* h, const ebsd_pair* pairs, int n, Mode mode, const flo
     e = ensure_pin(h, need);
     if (e) return e;
     size_t off = 0;
+    h->call++;
     for (auto& hb : buckets) {
         size_t used = 0;
         e = run_bucket(h, hb, mode, u_init, rfin_in, out, s, off, &used, tune_only);
-        if (e) return e;
+        if (e) {
+            h->in_flight = true;
+            return e;
+        }
         off = align_up(off + used, 256);
     }
-    if (hipEventRecord(h->pin_free, s) != hipSuccess) return EBSD_EDEVICE;
+    if (hipEventRecord(h->pin_free, s) != hipSuccess) {
+        h->in_flight = true;
+        return EBSD_EDEVICE;
+    }
     h->pin_pending = true;
     if (tune_only) save_tune_cache(h);
     return EBSD_OK;
@@ -1254,6 +1303,7 @@ int run(ebsd_handle* h, const ebsd_pair* pairs, int n, Mode mode, const float* u
     try {
         return run_body(h, pairs, n, mode, u_init, rfin_in, out, stream, tune_only);
     } catch (const std::bad_alloc&) {
+        h->in_flight = true;
         return EBSD_ENOMEM;
     }
 }

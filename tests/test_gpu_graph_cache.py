@@ -1,0 +1,84 @@
+"""The captured graphs of a handle are bounded: a stream of ever other batch sizes
+does not hold more and more memory, and sizes that come back after their graph was
+dropped, or while others are captured, give the same results.  Needs an MI355X."""
+import os
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    from paper_1907_05993_amd import ebsd
+    ebsd.lib()
+    return ebsd
+
+
+def resident_bytes():
+    with open("/proc/self/statm") as f:
+        return int(f.read().split()[1]) * os.sysconf("SC_PAGE_SIZE")
+
+
+def setup(E, n, **kw):
+    from paper_1907_05993_amd import synth as S
+    refs, tests, _ = E.gen_pairs([S.make_spec(87, i, 64, 64, mis_deg=(0.0, 4.0)) for i in range(n)], labels=False)
+    reg = E.Registrar(E.Params(levels=2, sigma_px=1.0, roi_size=32, n_roi=5, roi_radius_frac=0.05, second_pass=0, **kw))
+    reg.set_resident(False)
+    return refs, tests, reg
+
+
+def test_memory_of_many_batch_sizes(E):
+    """Graphs of 2000 launches, one per batch size: 16 of them fit the bound."""
+    refs, tests, reg = setup(E, 72, iters=(1000, 1000))
+    for level in (64, 32):
+        reg.set_strip_height(level, level, 16)
+    used = []
+    for n in range(72, 0, -1):  # the largest first: the workspace does not grow
+        reg.register(refs[:n], tests[:n], want_field=False)
+        torch.cuda.synchronize()
+        used.append(resident_bytes())
+    print("  MB after 24, 48, 72 sizes:", [round((used[k] - used[0]) / 1e6, 1) for k in (23, 47, 71)], flush=True)
+    # the first 24 sizes fill the bound; the other 48 hold no more, which would be twice
+    # as much as those
+    assert used[71] - used[23] <= 0.5 * (used[23] - used[0])
+    reg.close()
+
+
+@pytest.mark.parametrize("gating,tol", [(0, 0.0), (2, 0.05)])
+def test_results_while_graphs_come_and_go(E, gating, tol):
+    refs, tests, reg = setup(E, 40, iters=(900, 900), tol_px=tol)
+    reg.set_gating(gating)
+    plain = setup(E, 1, iters=(900, 900), tol_px=tol)[2]
+    plain.set_graphs(False)
+    want = {}
+    order = list(range(40, 0, -1)) + [40, 3, 40, 39, 1, 17, 17, 40] + list(range(1, 41, 3))
+    for n in order:
+        if n not in want:
+            want[n] = plain.register(refs[:n], tests[:n])
+        got = reg.register(refs[:n], tests[:n])
+        torch.cuda.synchronize()
+        for k in ("field", "iters", "F", "status"):
+            assert torch.equal(got[k], want[n][k]), (n, k)
+    reg.close()
+    plain.close()
+
+
+def test_number_of_references_shares_a_graph(E):
+    """Batches of one size with other numbers of distinct references (their slots travel in
+    the descriptor) in turn, against single launches."""
+    refs, tests, reg = setup(E, 12, iters=(20, 20))
+    plain = setup(E, 1, iters=(20, 20))[2]
+    plain.set_graphs(False)
+    for k in (12, 1, 5, 12, 2, 1):
+        ids = [i % k for i in range(12)]
+        r = [r[i % k] for i in range(12)]
+        a = reg.register(r, list(tests), ref_ids=ids)
+        b = plain.register(r, list(tests), ref_ids=ids)
+        torch.cuda.synchronize()
+        assert torch.equal(a["F"], b["F"]) and torch.equal(a["iters"], b["iters"])
+        for x, y in zip(a["field"], b["field"]):
+            assert torch.equal(x, y)
+    reg.close()
+    plain.close()
