@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(1024)
 // work (the levels of one or few patterns: 12 of 622 x 512 209 us, 253 with 8).
 constexpr int kPointThreads = 512, kPointTX = 64, kPointMargin = 36;
 
-template <int PX>
+template <int PX, bool LARGE>
 __global__ void __launch_bounds__(kPointThreads)
     k_demons_points(const Bucket* __restrict__ bk, int level, float w0, int ntx, int ntiles, int cap)
 {
@@ -351,7 +351,7 @@ __global__ void __launch_bounds__(kPointThreads)
     const GatherBase T = gather_base(Tg, h, w);
     const EBSD_GLOBAL float* __restrict__ u = gptr(bk->field[base & 1] + slot);
     EBSD_GLOBAL float* __restrict__ un = gptr(bk->field[(base + 1) & 1] + slot);
-    const BilGeomOf<true> g = bil_geom<true>(h, w);
+    const BilGeomOf<LARGE> g = bil_geom<LARGE>(h, w);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int x = min(tx0 + lane, w - 1);
     float ux[kPointPx], uy[kPointPx];
@@ -521,12 +521,13 @@ hipError_t launch_demons_points(const Bucket* d_bk, const Bucket& hb, int level,
     const int ntx = (hb.lw[level] + kPointTX - 1) / kPointTX;
     const auto tiles = [&](int ty) { return ntx * ((hb.lh[level] + ty - 1) / ty); };
     constexpr int rows = kPointThreads / kPointTX;  // of one pixel per thread
-    if ((int64_t)hb.nb * tiles(8 * rows) >= 1024)
-        hipLaunchKernelGGL(k_demons_points<8>, dim3((unsigned)((int64_t)hb.nb * tiles(8 * rows))), dim3(kPointThreads),
-                           0, s, d_bk, level, taps[0], ntx, tiles(8 * rows), cap);
-    else
-        hipLaunchKernelGGL(k_demons_points<2>, dim3((unsigned)((int64_t)hb.nb * tiles(2 * rows))), dim3(kPointThreads),
-                           0, s, d_bk, level, taps[0], ntx, tiles(2 * rows), cap);
+    const auto launch = [&](auto kernel, int px) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((int64_t)hb.nb * tiles(px * rows))), dim3(kPointThreads), 0, s, d_bk,
+                           level, taps[0], ntx, tiles(px * rows), cap);
+    };
+    if ((int64_t)hb.lh[level] * hb.lw[level] > kMaxFp32Pixels) launch(k_demons_points<8, true>, 8);
+    else if ((int64_t)hb.nb * tiles(8 * rows) >= 1024) launch(k_demons_points<8, false>, 8);
+    else launch(k_demons_points<2, false>, 2);
     return hipGetLastError();
 }
 
