@@ -171,9 +171,13 @@ int default_fused_ty(int lh, int lw, int nb, int radius)
 }
 
 // The microseconds per iteration below are fitted to the times of all kernels on
-// levels of 66 x 78 to 1244 x 1024 px in batches of 1 to 1000 at radius 1 to 4
-// (976 points).  Over radius 2 to 4 the kernel predicted to be the fastest takes
-// 0.5 % more than the fastest one on average and 38 % at worst.
+// levels of 66 to 1300 px a side, 5e4 to 8e7 pixels per batch, radius 1 to 4: finest
+// of three levels, cold start, patterns up to 8 degrees apart (880 sizes of batches,
+// 3520 points without a tolerance, 2120 with one of 0.02 to 0.3 px).  On 417 other
+// batches what the rule picks takes 2.0 % more than the fastest kernel on average (40 %
+// at worst) and 0.53 times as long as one iteration per launch (1.13 at worst) without
+// a tolerance, and 5.9 % (76 %) and 0.72 times (1.65; above 1.05 in 23 of 998) with one.
+// Smooth fields (a warm start) gather faster than these by up to a third.
 
 // Region rows (32, 64 or 80) of the tile kernels for nb levels of lh x lw px (0: no
 // tile kernel at this radius or level size).  Regions of 64 and 80 rows (these twice as wide) run
@@ -187,8 +191,8 @@ int tile_rows_for(int lh, int lw, int nb, int radius, double& us)
     const double n32 = (double)regions(32), k64 = (double)((regions(64) + 255) / 256),
                  k80 = (double)((regions(80) + 255) / 256);
     const double t32 = radius > 3 ? std::max(3.6, 2.0 + 0.0059 * n32) : std::max(3.0, 1.6 + 0.0052 * n32);
-    const double t64 = radius > 3 ? 1.2 + 3.8 * k64 : 0.9 + 2.9 * k64;
-    const double t80 = 1.2 + 7.6 * k80;
+    const double t64 = radius > 3 ? 1.2 + 3.8 * k64 : 0.9 + 2.8 * k64;
+    const double t80 = 1.2 + (radius > 3 ? 8.2 : 7.8) * k80;
     us = std::min({t32, t64, t80});
     return us == t32 ? 32 : us == t64 ? 64 : 80;
 }
@@ -199,7 +203,9 @@ int tile_rows_for(int lh, int lw, int nb, int radius, double& us)
 // strip's row steps.  Four columns per lane: 1024 slots (one per SIMD); a step
 // takes 1.2 us while the batch's level (24 B per pixel) is small against the
 // last-level cache, up to 1.57 from 650 MB.  Two columns: up to three wavefronts
-// per SIMD, 0.93 / 1.25 / 2.2 us at radius 3, one per SIMD 0.77 at 2, 1.2 at 4.
+// per SIMD, 0.93 / 1.25 / 2.2 us at radius 3, one per SIMD 0.77 at 2, 1.2 at 4.  And
+// no less than 5.5 / 5.5 / 3.9 / 4.2 us per million pixels at radius 1 to 4: the less
+// smooth the field, the more lines of the test pattern a row's gathers touch.
 struct MarchPlan {
     int rows = 0;
     double us = 1e30;
@@ -223,37 +229,63 @@ MarchPlan march_plan(int H, int W, int lh, int lw, int nb, int radius)
         }
         if (rows == kMarchMinRows) break;
     }
+    constexpr double floor_us[kMaxRadius + 1] = {0.0, 5.5, 5.5, 3.9, 4.2};
+    best.us = std::max(best.us, floor_us[radius] * 1e-6 * nb * lh * lw);
     return best;
 }
 
 // Microseconds per iteration of the row kernels at strip height ty: row steps
 // times the length of a step for `ws` wavefronts per SIMD.  Two iterations per
 // launch (three wavefronts per SIMD at once): 0.98 / 1.09 / 1.2 us, then a
-// microsecond per round of three, and no less than 4.0 us per million pixels (1024
-// pairs of 256 x 256 270 us).  One iteration: 0.57 + 0.09 ws up to four, then
-// 0.27 ws; short strips, in which the fill weighs more, 1.2 to 1.5 times that.
+// microsecond per round of three, and no less than 5.3 / 6.0 / 4.0 us per million
+// pixels at radius 1 to 3 (1024 pairs of 256 x 256 270 us at radius 3).  One
+// iteration: 0.57 + 0.09 ws up to four, then 0.22 ws, 8 us per million pixels at
+// radius 1 and 7 above; short strips, in which the fill weighs more, 1.2 to 1.5 times
+// that.
 double rows_us(int lh, int lw, int nb, int radius, int ty, bool two)
 {
     const int cpl = rows_cpl(lw);
-    const double ws = (double)nb * demons_units(lh, lw, ty) * cpl / 1024.0;
+    const double ws = (double)nb * demons_units(lh, lw, ty) * cpl / 1024.0, mpx = 1e-6 * nb * lh * lw;
     if (two) {
         const double n = std::ceil(ws);
         const double t = 0.5 * (ty + 4 * radius + 1) * (n <= 3 ? 0.87 + 0.11 * n : std::ceil(n / 3));
-        return std::max(t, 4.0e-6 * nb * lh * lw);
+        return std::max(t, (radius == 1 ? 5.3 : radius == 2 ? 6.0 : 4.0) * mpx);
     }
-    const double step = ws <= 4 ? 0.57 + 0.09 * ws : std::max(1.3, 0.27 * ws);
-    return (std::min(ty, lh) + 2 * radius + 1) * step * (ty >= 64 ? 1.0 : radius > 3 ? 1.5 : 1.2) * (cpl > 4 ? 1.1 : 1.0);
+    const double step = ws <= 4 ? 0.57 + 0.09 * ws : std::max(1.1, 0.22 * ws);
+    const double t = (std::min(ty, lh) + 2 * radius + 1) * step * (ty >= 64 ? 1.0 : radius > 3 ? 1.5 : 1.2) *
+                     (cpl > 4 ? 1.15 : 1.0);
+    return std::max(t, (radius > 1 ? 7.0 : 8.0) * mpx);
 }
 
-// What `per_launch` iterations per launch cost a pair that stops by the tolerance: it
-// computes on to the end of its launch, (per_launch - 1) / 2 iterations on average,
-// after about 0.5 px / tolerance iterations (257 pairs of 519 x 519 at 0.1 px, where
-// both kernels take 385 us per iteration: the full-resolution level 1.2 ms with two
-// per launch, 2.9 ms with four).
-double late_stop(float tol, int cap, int per_launch)
+// Iterations after which a level's pairs stop on the tolerance: 1 + (c / t)^2 at a
+// tolerance of t px of the level, c = 0.105, 0.076 and 0.066 at radius 2, 3 and 4 (tenth
+// of a pixel 2, 0.05 3 to 5, 0.02 11 to 54); at radius 1 the field settles late and the
+// tolerances lie close together (0.3 px 1, 0.1 12, 0.07 112).  Medians over batches of
+// patterns up to 8 degrees apart, started from the next coarser level; the coarsest one
+// takes a dozen more (0.075 px of the level: 14, where a finer level takes 3).
+double expected_stop(float tol, int cap, int level, bool coarsest, int radius)
 {
-    if (!(tol > 0.0f)) return 1.0;
-    return 1.0 + 0.5 * (per_launch - 1) / std::max(1.0, std::min((double)cap, 0.5 / tol));
+    if (!(tol > 0.0f)) return cap;
+    constexpr double c[kMaxRadius + 1] = {0.145, 0.145, 0.105, 0.076, 0.066};
+    const double x = c[radius] * (double)(1 << level) / (double)tol;
+    return std::min((double)cap, (coarsest ? 13.0 : 1.0) + std::pow(x, radius > 1 ? 2.0 : 6.5));
+}
+
+// Microseconds that a level takes at `us` per iteration and K iterations per launch.  A
+// pair that stops by the tolerance after s iterations computes on to the end of its
+// launch and, if it stopped inside one, the iterations up to there once more: K more, or
+// on average K - 1 where s is spread over more than a launch.  The launches behind that
+// cost a microsecond each (fewer are issued where the host ends the issue, see
+// ebsd_set_gating).  10 % in favour of one iteration per launch, which an early stop
+// costs least.
+double level_us(const ebsd_handle* h, double us, int K, int cap, int level)
+{
+    const double s = expected_stop(h->p.tol_px, cap, level, level == h->p.levels - 1, h->radius);
+    if (s >= cap) return us * cap;
+    const double work = K == 1 ? s : s + K * (s < K ? 1.0 : (K - 1.0) / K);
+    double launches = std::ceil((double)cap / K);
+    if (h->gate_chunk > 0) launches = std::min(launches, std::ceil(4.0 * s / K) + 3.0 * h->gate_chunk);
+    return (us * work + std::max(0.0, launches - work / K)) * (K > 1 ? 1.1 : 1.0);
 }
 
 // The kernel kind measured for this level size, for batches of a quarter to four times
@@ -289,7 +321,7 @@ bool plan_supported(const ebsd_handle* h, int lh, int lw, int kind, int rows)
 // kernels, whichever is predicted to be the fastest.  Strips and regions of the
 // marching and tile kernels are as predicted for the batch, row strips as tuned, or
 // untuned two iterations per launch.
-LevelPlan level_plan(const ebsd_handle* h, int H, int W, int lh, int lw, int nb, int cap)
+LevelPlan level_plan(const ebsd_handle* h, int H, int W, int level, int lh, int lw, int nb, int cap)
 {
     const auto key = std::make_pair(lh, lw);
     const auto set = h->set_plan.find(key);
@@ -308,26 +340,34 @@ LevelPlan level_plan(const ebsd_handle* h, int H, int W, int lh, int lw, int nb,
     }
     const bool rule = h->resident && !h->forced.count(key);
     int fty = fused_ty_for(h, lh, lw, nb);
-    const int ty = strip_ty_for(h, lh, lw, nb);
+    const int ty = strip_ty_for(h, lh, lw, nb), rty = ty ? ty : kDefaultStripTY;
     const bool tuned = h->strip_ty.count(key) && tuned_applies(h->tuned_nb_strip, lh, lw, nb);
-    if (rule && !fty && !tuned && rows_cpl(lw)) fty = default_fused_ty(lh, lw, nb, h->radius);
     if (rule) {
         if (h->radius == 0 && h->p.tol_px == 0.0f) return {LevelPlan::Points, 0, std::max(cap, 1), 0};
+        // row strips: as tuned, else one or two iterations per launch
+        const auto rows = [&](int strip, bool two) {
+            return level_us(h, rows_us(lh, lw, nb, h->radius, strip, two), two ? 2 : 1, cap, level);
+        };
+        double rows_l = rows(fty ? fty : rty, fty > 0);
+        const int dty = !fty && !tuned && rows_cpl(lw) ? default_fused_ty(lh, lw, nb, h->radius) : 0;
+        if (dty && rows(dty, true) < rows_l) {
+            rows_l = rows(dty, true);
+            fty = dty;
+        }
         const MarchPlan m = march_plan(H, W, lh, lw, nb, h->radius);
         double tiles = 1e30;
         const int tr = tile_rows_for(lh, lw, nb, h->radius, tiles);
         int kind = tuned_kind_for(h, lh, lw, nb);
         if (kind < 0) {
-            const double rows = rows_us(lh, lw, nb, h->radius, fty ? fty : ty ? ty : kDefaultStripTY, fty > 0);
-            const double tiles_l = tiles * late_stop(h->p.tol_px, cap, tr ? tile_iters(h->radius, tr) : 1);
-            const double march_l = m.us * late_stop(h->p.tol_px, cap, 2);
-            const double rows_l = rows * late_stop(h->p.tol_px, cap, fty ? 2 : 1);
+            const double tiles_l = tr ? level_us(h, tiles, tile_iters(h->radius, tr), cap, level) : 1e30;
+            const double march_l = m.rows ? level_us(h, m.us, 2, cap, level) : 1e30;
             if (tr && tiles_l < std::min(rows_l, march_l)) kind = LevelPlan::Tiles;
             else if (march_l < rows_l) kind = LevelPlan::March;
         }
         if (kind == LevelPlan::Tiles && tr)
             return {LevelPlan::Tiles, tr, tile_iters(h->radius, tr), tile_units(lh, lw, h->radius, tr)};
         if (kind == LevelPlan::March && m.rows) return {LevelPlan::March, m.rows, 2, march_units(lh, lw, h->radius, m.rows)};
+        if (kind == LevelPlan::Rows) fty = 0;
     }
     if (fty) return {LevelPlan::Rows2, fty, 2, demons_units(lh, lw, fty)};
     return {LevelPlan::Rows, ty, 1, demons_units(lh, lw, ty)};
@@ -712,7 +752,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
         pe = (pe + 63) / 64 * 64;  // every level 256 B aligned
         max_units = std::max(max_units, demons_units(b.lh[l], b.lw[l], kMinStripTY2));
         if (b.lw[l] > 512) max_units = std::max(max_units, demons_tiles(b.lh[l], b.lw[l]));
-        plan[l] = level_plan(h, H, W, b.lh[l], b.lw[l], nb, p.max_iters[l]);
+        plan[l] = level_plan(h, H, W, l, b.lh[l], b.lw[l], nb, p.max_iters[l]);
         max_units = std::max(max_units, plan[l].units);
     }
     b.pyr_elems = pe;
@@ -963,6 +1003,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
                     best_ty = ty;
                 }
             }
+            const float best_one = best;
             int best_fty = 0;
             for (int fty : {8, 16, 32, 64, 128}) {
                 if (!rows2_ty_ok(lw, fty)) continue;
@@ -985,11 +1026,11 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
             // what the rule takes stays unless another is faster by more than 3 % in a
             // second, longer timing of the two (short ones differ by more among themselves)
             const int cap = p.max_iters[l];
-            const LevelPlan by_rule = level_plan(h, H, W, lh, lw, nb, cap);
-            LevelPlan kinds[3] = {{best_fty ? LevelPlan::Rows2 : LevelPlan::Rows, best_fty ? best_fty : best_ty,
-                                   best_fty ? 2 : 1, 0}};
-            float cost[3] = {best};
-            int n = 1;
+            const LevelPlan by_rule = level_plan(h, H, W, l, lh, lw, nb, cap);
+            LevelPlan kinds[4] = {{LevelPlan::Rows, best_ty, 1, 0}, {LevelPlan::Rows2, best_fty, 2, 0}};
+            float cost[4] = {best_one, best};
+            const int timed = best_fty ? 2 : 1;
+            int n = timed;
             double tiles = 1e30;
             const int tr = tile_rows_for(lh, lw, nb, h->radius, tiles);
             const MarchPlan m = march_plan(H, W, lh, lw, nb, h->radius);
@@ -999,11 +1040,11 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
                 kinds[n++] = {LevelPlan::March, m.rows, 2, 0};
             int fast = 0, rule = 0;
             for (int i = 0; i < n; i++) {
-                if (i > 0) {
+                if (i >= timed) {
                     const int r = time_plan(kinds[i], l, 6, cost[i]);
                     if (r) return r;
                 }
-                cost[i] *= (float)late_stop(p.tol_px, cap, kinds[i].per_launch);
+                cost[i] = (float)level_us(h, cost[i], kinds[i].per_launch, cap, l);
                 if (cost[i] < cost[fast]) fast = i;
                 if (kinds[i].kind == by_rule.kind) rule = i;
             }
@@ -1011,7 +1052,7 @@ int run_bucket(ebsd_handle* h, const HostBucket& hbk, Mode mode, const float* u_
                 for (int i : {rule, fast}) {
                     const int r = time_plan(kinds[i], l, 24, cost[i]);
                     if (r) return r;
-                    cost[i] *= (float)late_stop(p.tol_px, cap, kinds[i].per_launch);
+                    cost[i] = (float)level_us(h, cost[i], kinds[i].per_launch, cap, l);
                 }
                 if (!(cost[fast] < 0.97f * cost[rule])) fast = rule;
             }
@@ -1530,7 +1571,7 @@ int ebsd_get_level_plan(const ebsd_handle* h, int32_t H, int32_t W, int32_t leve
         lw = (lw + 1) / 2;
     }
     const bool res = h->resident && demons_resident_ok(lh, lw);
-    const LevelPlan q = level_plan(h, H, W, lh, lw, pairs, h->p.max_iters[level]);
+    const LevelPlan q = level_plan(h, H, W, level, lh, lw, pairs, h->p.max_iters[level]);
     if (kind) *kind = res ? EBSD_PLAN_RESIDENT : q.kind;
     if (rows) *rows = res ? 0 : q.rows;
     return EBSD_OK;
