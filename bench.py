@@ -792,7 +792,8 @@ def kernel_sha():
     csrc = os.path.join(ROOT, "paper_1907_05993_amd", "csrc")
     files = sorted(glob.glob(os.path.join(csrc, "k_demons*.hip"))) + [os.path.join(csrc, "demons_rows_impl.h"),
                                                                   os.path.join(csrc, "demons_region.h"),
-                                                                  os.path.join(csrc, "dev_util.h")]
+                                                                  os.path.join(csrc, "dev_util.h"),
+                                                                  os.path.join(csrc, "cell_index.h")]
     for f in files:
         h.update(open(f, "rb").read())
     return h.hexdigest()[:16]
